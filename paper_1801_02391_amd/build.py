@@ -11,6 +11,7 @@ import os
 import shutil
 import subprocess
 import sys
+from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -73,21 +74,22 @@ def _run(cmd, verbose):
 def build(verbose: bool = True) -> str:
     os.makedirs(BUILD, exist_ok=True)
     hipcc = _hipcc()
-    objs = []
-    k_obj = os.path.join(BUILD, "frbx_kernels.o")
-    _run([hipcc, "-c", "-O3", *COMMON, *DEVICE_FLAGS, *KERNEL_FLAGS,
-          os.path.join(CSRC, "frbx_kernels.hip"), "-o", k_obj], verbose)
-    objs.append(k_obj)
     write_rtc_source()
-    j_obj = os.path.join(BUILD, "frbx_jit.o")
-    _run([hipcc, "-c", "-O2", *COMMON, *DEVICE_FLAGS, os.path.join(CSRC, "frbx_jit.cpp"), "-o", j_obj], verbose)
-    objs.append(j_obj)
-    h_obj = os.path.join(BUILD, "frbx_host.o")
-    # float64 tables must not be contracted into FMAs: keep Eq. 2 rounding
-    # bit-identical to a plain evaluation of the formula.
-    _run([hipcc, "-c", "-O2", "-ffp-contract=off", *COMMON, *DEVICE_FLAGS,
-          os.path.join(CSRC, "frbx_host.cpp"), "-o", h_obj], verbose)
-    objs.append(h_obj)
+    units = [("frbx_kernels.hip", ["-O3", *KERNEL_FLAGS]),
+             ("frbx_screen.hip", ["-O3", *KERNEL_FLAGS]),
+             ("frbx_jit.cpp", ["-O2"]),
+             # float64 tables must not be contracted into FMAs: keep Eq. 2
+             # rounding bit-identical to a plain evaluation of the formula
+             ("frbx_host.cpp", ["-O2", "-ffp-contract=off"])]
+
+    def compile_unit(unit):
+        src, flags = unit
+        obj = os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
+        _run([hipcc, "-c", *flags, *COMMON, *DEVICE_FLAGS, os.path.join(CSRC, src), "-o", obj], verbose)
+        return obj
+
+    with ThreadPoolExecutor(len(units)) as pool:
+        objs = list(pool.map(compile_unit, units))
     tmp = LIB + ".tmp"
     _run([hipcc, "-shared", f"--offload-arch={ARCH}", "-fPIC", *objs, "-lhiprtc", "-o", tmp], verbose)
     os.replace(tmp, LIB)

@@ -389,6 +389,61 @@ __device__ __forceinline__ void mbd_column_max(const float2 (&z)[MB], unsigned &
   blk = m;
 }
 
+// ---------------------------------------------- candidates of a screened search
+// The units (16 SBD bins of one sub-grid) of a segment that its screening
+// records leave standing: first the one with the largest screened |G|, then,
+// once that one's own |G| is known, every other that could exceed it.
+struct Candidates {
+  const unsigned char *rec;   // the segment's R records
+  int R, units, per_c;        // per_c = J / 16 units per sub-grid
+  // the unit with the largest screened |G| as (rate * P + sub-grid, unit of
+  // the sub-grid); rc = -1 when no record knows one.  Every wave of the
+  // work-group finds the same (R and units are at most 64).
+  __device__ __forceinline__ void first(int lane, int P, int &rc, int &sb) const {
+    float top = -1.0f;
+    int r = lane;
+    if (lane < R && units > 0) {
+      const float2 ab = *reinterpret_cast<const float2 *>(rec + int64_t(lane) * screen_rec_bytes(units));
+      if (ab.y < __builtin_inff()) top = ab.x;
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+      const float ot = __shfl_xor(top, off, 64);
+      const int orr = __shfl_xor(r, off, 64);
+      if (ot > top || (ot == top && orr < r)) {
+        top = ot;
+        r = orr;
+      }
+    }
+    rc = -1;
+    sb = 0;
+    if (!(top > 0.0f)) return;
+    const unsigned char *q = rec + int64_t(r) * screen_rec_bytes(units) + 8;
+    const unsigned long long is_top = __ballot(lane < units && q[lane < units ? lane : 0] == 1);
+    if (!is_top) return;
+    const int u = __ffsll(is_top) - 1;
+    rc = r * P + u / per_c;
+    sb = u - (u / per_c) * per_c;
+  }
+  // the units whose |G| can reach `amp` (< 0: any), into the bit masks
+  // cand[rc] of the work-group's threads t of n (cleared before)
+  __device__ __forceinline__ void mark(int t, int n, int P, float amp, unsigned *cand) const {
+    if (units == 0) {
+      for (int i = t; i < R * P; i += n) cand[i] = (1u << per_c) - 1u;
+      return;
+    }
+    for (int i = t; i < R * units; i += n) {
+      const int r = i / units, u = i - (i / units) * units;
+      const unsigned char *q = rec + int64_t(r) * screen_rec_bytes(units);
+      const float2 ab = *reinterpret_cast<const float2 *>(q);
+      const unsigned v = q[8 + u];
+      if (v == 0) continue;
+      const bool known = ab.y < __builtin_inff();
+      const float most = ab.x - float(v - 1) * ab.y * (1.0f / 127.0f) + ab.y;
+      if (!known || most >= amp * 0.99999f) atomicOr(&cand[r * P + u / per_c], 1u << (u % per_c));
+    }
+  }
+};
+
 // CL (compact lattice): every IF sits at a lattice position below MB once
 // the positions are shifted by a common offset (which changes only the phase
 // of G, not |G|).  The first MBD pass then has one non-zero input per lane
@@ -401,7 +456,11 @@ __device__ __forceinline__ void mbd_column_max(const float2 (&z)[MB], unsigned &
 // (bit i1 for lattice positions MB i1 + i2), 0 for all; the pass then
 // reads and transforms only those rows (a kernel specialised to the IF
 // lattice when the search starts; the same sums).
-template <int J, int M, bool DUMP, bool CL, bool LIST = false, unsigned ROWS = 0u>
+// CAND (M = 256): only the candidate units of the segment's screening
+// records are transformed.  The result is the full search's: the sub-grid
+// with the largest |G|^2 (all bits; then the lowest), its cells keyed; with
+// fewer than 8 (rate, sub-grid) pairs the keys alone decide.
+template <int J, int M, bool DUMP, bool CL, bool LIST = false, unsigned ROWS = 0u, bool CAND = false>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(J <= 64 && !DUMP && !LIST ? 3 : 1)))
 void fringe_kernel(FringeArgs a) {
   using S = FringeShape<J, M>;
@@ -515,17 +574,19 @@ void fringe_kernel(FringeArgs a) {
   // MBD transform of every SBD column of sub-grid c (rate r); FIND: the
   // cells' keys and the running (value, packed index) of the lane, else
   // only the largest |G|^2 (float bits) into blk
-  auto mbd = [&](int r, int c, auto find_tag, unsigned &blk) {
-    constexpr bool FIND = decltype(find_tag)::value != 0;
+  // (FIND 2: keys and maximum, and only columns [from, to))
+  auto mbd = [&](int r, int c, auto find_tag, unsigned &blk, int from = 0, int to = J) {
+    constexpr int FIND = decltype(find_tag)::value;
     auto column = [&](const float2 (&z)[MB], int col) {
-      if constexpr (FIND)
+      if constexpr (FIND != 0)
         mbd_column_peak<M, MA, MB, DUMP>(z, r, c, col, gl, P, PJ, a.dump, best_v, best_i);
-      else
+      if constexpr (FIND != 1)
         mbd_column_max<MB>(z, blk);
     };
+    const int a_lo = FIND == 2 ? from : 0, a_hi = FIND == 2 ? to : J;
     if constexpr (CL) {
       // compact lattice: z[i2] = X(position i2) w_M^(i2 k1), MB-point DFT
-      for (int a0 = 0; a0 < J; a0 += COLS) {
+      for (int a0 = a_lo; a0 < a_hi; a0 += COLS) {
         const int col = a0 + grp;
         if (col < J && m_p2) {
           float2 z[MB];
@@ -541,8 +602,8 @@ void fringe_kernel(FringeArgs a) {
     } else {
       // MBD over the IF lattice, one column a of this SBD tile per group.
       // Unrolled by 4: the columns' LDS offsets become immediates.
-#pragma unroll 4
-      for (int a0 = 0; a0 < J; a0 += COLS) {
+#pragma unroll (CAND ? 1 : 4)
+      for (int a0 = a_lo; a0 < a_hi; a0 += COLS) {
         const int col = a0 + grp;
         if (col < J) {
           if (m_p1) {
@@ -585,50 +646,62 @@ void fringe_kernel(FringeArgs a) {
   // segment's power NaN (index -1).
   constexpr bool SCAN = !DUMP && !LIST;
   const bool scan = SCAN && R * P >= 8;
-  unsigned scan_v = 0u;
-  int scan_rc = 0;
-  for (int r = 0; r < R; ++r) {
-    sums(r);
-    for (int c = 0; c < P; ++c) {
+  if constexpr (CAND) {
+    static_assert(COLS == 16, "a unit is one round of columns");
+    unsigned *cand = reinterpret_cast<unsigned *>(lds + total);   // [R P] after the plan
+    const Candidates cs{a.screen + (int64_t(dl) * a.seg_total + seg) * R * screen_rec_bytes(a.screen_units), R,
+                        a.screen_units, J / 16};
+    for (int i = t; i < R * P; i += kBlock) cand[i] = 0u;
+    unsigned top = 0u;           // largest |G|^2 (bits) so far and its (rate, sub-grid)
+    int top_rc = 0x7fffffff, cur_r = -1;
+    float run_v = -1.0f;         // the lane's keyed peak over what counts so far
+    int32_t run_i = 0x7fffffff;
+    int rc0, sb0;
+    cs.first(t & 63, P, rc0, sb0);
+    for (int it = rc0 >= 0 ? -1 : 0; it < R * P; ++it) {
+      if (it == 0) {   // what the first unit leaves
+        __syncthreads();   // cand is cleared
+        cs.mark(t, kBlock, P, rc0 >= 0 ? sqrtf(__uint_as_float(top)) : -1.0f, cand);
+        __syncthreads();
+      }
+      const int rc = it < 0 ? rc0 : it;
+      // (the first unit's sub-grid: again with the first only if others are left)
+      const unsigned mask = it < 0 ? 1u << sb0 : cand[rc] == 1u << sb0 && rc == rc0 ? 0u : cand[rc];
+      if (!mask) continue;
+      const int r = rc / P, c = rc - (rc / P) * P;
+      if (r != cur_r) {
+        sums(r);
+        cur_r = r;
+      }
       sbd(c);
       unsigned blk = 0u;
-      if (!scan) {
-        mbd(r, c, Index<1>{}, blk);
-      } else {
-        mbd(r, c, Index<0>{}, blk);
-        if (blk > scan_v) {
-          scan_v = blk;
-          scan_rc = r * P + c;
+      best_v = -1.0f;
+      best_i = 0x7fffffff;
+      for (unsigned m = mask; m; m &= m - 1) {
+        const int a0 = 16 * (__ffs(int(m)) - 1);
+        mbd(r, c, Index<2>{}, blk, a0, a0 + 16);
+      }
+      for (int off = 32; off > 0; off >>= 1) blk = max(blk, unsigned(__shfl_xor(int(blk), off, 64)));
+      if ((t & 63) == 0) red_v[t >> 6] = __uint_as_float(blk);
+      __syncthreads();
+      for (int w = 0; w < kBlock / 64; ++w) blk = max(blk, __float_as_uint(red_v[w]));
+      // (the next sbd's first barrier ends the reads of red_v)
+      const bool better = blk > top || (blk == top && rc < top_rc);
+      if (scan && better && rc != top_rc) {
+        run_v = best_v;
+        run_i = best_i;
+      } else if (!scan || rc == top_rc) {
+        if (best_v > run_v || (best_v == run_v && best_i < run_i)) {
+          run_v = best_v;
+          run_i = best_i;
         }
       }
-    }
-  }
-  if (scan) {
-    // block maximum and its (rate, sub-grid): larger value, then lower
-    // (rate, sub-grid)
-    for (int off = 32; off > 0; off >>= 1) {
-      const unsigned ov = __shfl_xor(scan_v, off, 64);
-      const int orc = __shfl_xor(scan_rc, off, 64);
-      if (ov > scan_v || (ov == scan_v && orc < scan_rc)) {
-        scan_v = ov;
-        scan_rc = orc;
+      if (better) {
+        top = blk;
+        top_rc = rc;
       }
     }
-    if ((t & 63) == 0) {
-      red_v[t >> 6] = __uint_as_float(scan_v);
-      red_i[t >> 6] = scan_rc;
-    }
-    __syncthreads();
-    unsigned vmax = __float_as_uint(red_v[0]);
-    int rc = red_i[0];
-    for (int w = 1; w < kBlock / 64; ++w) {
-      const unsigned v = __float_as_uint(red_v[w]);
-      if (v > vmax || (v == vmax && red_i[w] < rc)) {
-        vmax = v;
-        rc = red_i[w];
-      }
-    }
-    if (vmax > 0x7F800000u) {   // a cell that is not a number (non-finite input)
+    if (scan && top > 0x7F800000u) {   // a cell that is not a number (non-finite input)
       if (t == 0) {
         const int64_t o = int64_t(dl) * a.seg_total + seg;
         a.power[o] = __builtin_nanf("");
@@ -636,11 +709,67 @@ void fringe_kernel(FringeArgs a) {
       }
       return;
     }
-    const int r = rc / P, c = rc - (rc / P) * P;
-    sums(r);
-    sbd(c);   // its first barrier also ends the reads of red_* above
-    unsigned unused = 0u;
-    mbd(r, c, Index<1>{}, unused);
+    best_v = run_v;
+    best_i = run_i;
+    __syncthreads();   // the reads of red_v are done
+  } else {
+    unsigned scan_v = 0u;
+    int scan_rc = 0;
+    for (int r = 0; r < R; ++r) {
+      sums(r);
+      for (int c = 0; c < P; ++c) {
+        sbd(c);
+        unsigned blk = 0u;
+        if (!scan) {
+          mbd(r, c, Index<1>{}, blk);
+        } else {
+          mbd(r, c, Index<0>{}, blk);
+          if (blk > scan_v) {
+            scan_v = blk;
+            scan_rc = r * P + c;
+          }
+        }
+      }
+    }
+    if (scan) {
+      // block maximum and its (rate, sub-grid): larger value, then lower
+      // (rate, sub-grid)
+      for (int off = 32; off > 0; off >>= 1) {
+        const unsigned ov = __shfl_xor(scan_v, off, 64);
+        const int orc = __shfl_xor(scan_rc, off, 64);
+        if (ov > scan_v || (ov == scan_v && orc < scan_rc)) {
+          scan_v = ov;
+          scan_rc = orc;
+        }
+      }
+      if ((t & 63) == 0) {
+        red_v[t >> 6] = __uint_as_float(scan_v);
+        red_i[t >> 6] = scan_rc;
+      }
+      __syncthreads();
+      unsigned vmax = __float_as_uint(red_v[0]);
+      int rc = red_i[0];
+      for (int w = 1; w < kBlock / 64; ++w) {
+        const unsigned v = __float_as_uint(red_v[w]);
+        if (v > vmax || (v == vmax && red_i[w] < rc)) {
+          vmax = v;
+          rc = red_i[w];
+        }
+      }
+      if (vmax > 0x7F800000u) {   // a cell that is not a number (non-finite input)
+        if (t == 0) {
+          const int64_t o = int64_t(dl) * a.seg_total + seg;
+          a.power[o] = __builtin_nanf("");
+          a.pidx[o] = -1;
+        }
+        return;
+      }
+      const int r = rc / P, c = rc - (rc / P) * P;
+      sums(r);
+      sbd(c);   // its first barrier also ends the reads of red_* above
+      unsigned unused = 0u;
+      mbd(r, c, Index<1>{}, unused);
+    }
   }
 
   // ---- block reduction: larger |G|^2 wins, ties -> lower packed index

@@ -82,6 +82,10 @@ struct frbx_ctx {
   unsigned rows_mask = 0;        // rows of the kernel in use (0: the statically built kernel)
   hipFunction_t rows_fn = nullptr;
   std::string rows_note;         // why the specialised kernel is not in use
+  int scr_blocks = 0;            // screened search: work-groups of the screening pass (0: not screened),
+  bool scr_half = false;         // its form, operand rows and the errors of its rounded matrices
+  int32_t scr_row_if[32];
+  double scr_err_s = 0, scr_err_m = 0;
   std::vector<int> rate_off;
   int dd_group = 1;          // DM trials per staged dedispersion tile
 
@@ -92,6 +96,9 @@ struct frbx_ctx {
   float vis_absmax = 0.f;
   bool loaded = false;
   void *d_mfma_hi = nullptr, *d_mfma_lo = nullptr;
+  void *d_scr_sbd = nullptr, *d_scr_mbd = nullptr;   // screening pass: constant MFMA operands
+  unsigned char *d_rec = nullptr;                    // and its records
+  size_t rec_cap = 0;
   void *d_sbd_a = nullptr;   // float16 form: SBD DFT matrix as MFMA A operands
   unsigned int *d_absmax = nullptr;
   int32_t *d_dk = nullptr;
@@ -219,6 +226,9 @@ struct frbx_ctx {
     dfree(d_mfma_hi);
     dfree(d_mfma_lo);
     dfree(d_sbd_a);
+    dfree(d_scr_sbd);
+    dfree(d_scr_mbd);
+    dfree(d_rec);
     dfree(d_absmax);
     dfree(d_dk);
     dfree(d_cal);
@@ -375,6 +385,18 @@ bool use_gemm(const frbx_ctx *c) {
          frbx::fringe_gemm_supported(c->J, c->n_mbd, c->N, c->sbd_pad);
 }
 
+// A screened search: the float16 screening pass names the candidate units of
+// every segment and the search's kernel evaluates those.  Every form but the
+// one with the SBD transform on the matrix cores, where the pass has the
+// shape (and the candidate masks fit beside the kernel's LDS plan).
+bool use_screen(const frbx_ctx *c) {
+  if (use_gemm(c) || !frbx::screen_supported(c->J, c->n_mbd, c->N, c->sbd_pad)) return false;
+  const size_t lds = c->precision == FRBX_PREC_F32
+                         ? frbx::fringe_lds_bytes(c->J, c->n_mbd, c->N, c->sbd_pad)
+                         : frbx::fringe_mfma_lds_bytes(c->J, c->N, c->sbd_pad, c->precision == FRBX_PREC_F16X3 ? 3 : 1);
+  return lds + size_t(c->n_rate) * c->sbd_pad * 4 <= 150 * 1024;
+}
+
 // The matrix-core fringe launch of the current precision (both transforms
 // on the matrix cores, or the MBD only).
 hipError_t launch_matrix_core(const frbx_ctx *c, frbx::FringeArgs &fa, int grid) {
@@ -384,8 +406,99 @@ hipError_t launch_matrix_core(const frbx_ctx *c, frbx::FringeArgs &fa, int grid)
                                     c->stream);
   }
   const int n_pass = c->precision == FRBX_PREC_F16X3 ? 3 : 1;
-  return frbx::launch_fringe_mfma(c->J, c->N, n_pass, fa, frbx::fringe_mfma_lds_bytes(c->J, c->N, c->sbd_pad, n_pass),
-                                  grid, c->stream);
+  const size_t lds = frbx::fringe_mfma_lds_bytes(c->J, c->N, c->sbd_pad, n_pass) +
+                     (fa.screened ? size_t(c->n_rate) * c->sbd_pad * 4 : 0);
+  return frbx::launch_fringe_mfma(c->J, c->N, n_pass, fa, lds, grid, c->stream);
+}
+
+// Constant operands of the screening pass in the per-lane order of
+// v_mfma_f32_16x16x32_f16 (lane ln: column ln % 16, group g = ln / 16,
+// element e; cos for e < 4 and sin for e >= 4 of the phase), and what
+// rounding them to float16 costs.
+//   SBD: unit pair p = sub-grid c = p / (J / 32), bins s' = c + P a with
+//   a = 16 (p % (J / 32)) + column < J / 2 (the pair's second unit is
+//   a + J / 2); chunk 2 kp + par, element e is channel 32 kp + 8 (e % 4) +
+//   2 g + par; phase 2 pi j s' / (P J).
+//   MBD: tile t, bins m = 16 t + column; chunk nt, element e is operand row
+//   16 nt + 4 g + e % 4, its IF row_if (zero for absent rows); phase
+//   2 pi q_n m / M.  With more than 16 IFs of which at most 16 have an even
+//   and at most 16 an odd lattice position, rows 0-15 take the even ones,
+//   rows 16-31 the odd ones and the bins stop at M / 2 (half).
+struct ScreenTables {
+  std::vector<_Float16> fs, fm;
+  int32_t row_if[32];
+  bool half = false;
+  double err_s = 0, err_m = 0;   // largest rms of a column's rounding error over a lane group's channels / over the rows
+};
+
+ScreenTables screen_tables(const frbx_ctx *c) {
+  ScreenTables T;
+  const int N = c->N, J = c->J, P = c->sbd_pad, PJ = P * J, KC = J / 16, KP = J / 32, pairs = PJ / 32, M = c->n_mbd;
+  const int NK = N <= 16 ? 1 : 2;
+  int n_odd = 0;
+  for (int n = 0; n < N; ++n) n_odd += int(c->q_if[n] & 1);
+  T.half = N > 16 && n_odd <= 16 && N - n_odd <= 16;
+  std::fill(T.row_if, T.row_if + 32, -1);
+  for (int n = 0, next[2] = {0, 16}, k = 0; n < N; ++n) {
+    if (T.half) T.row_if[next[c->q_if[n] & 1]++] = n;
+    else T.row_if[k++] = n;
+  }
+  const int tiles = T.half ? M / 32 : M / 16;
+  T.fs.assign(size_t(pairs) * KC * 64 * 8, _Float16(0));
+  T.fm.assign(size_t(tiles) * NK * 64 * 8, _Float16(0));
+  auto put = [](_Float16 &out, int64_t k, int64_t n, bool sine) {   // returns the squared rounding error
+    const double th = kTwoPi * double(k % n) / double(n), v = sine ? std::sin(th) : std::cos(th);
+    out = static_cast<_Float16>(v);
+    return (double(out) - v) * (double(out) - v);
+  };
+  for (int p = 0; p < pairs; ++p)
+    for (int ln = 0; ln < 64; ++ln) {
+      double e2 = 0;
+      for (int kc = 0; kc < KC; ++kc)
+        for (int e = 0; e < 8; ++e) {
+          const int j = 32 * (kc / 2) + 8 * (e % 4) + 2 * (ln / 16) + kc % 2;
+          const int sp = p / KP + P * (16 * (p % KP) + ln % 16);
+          e2 += put(T.fs[((size_t(p) * KC + kc) * 64 + ln) * 8 + e], int64_t(j) * sp, PJ, e >= 4);
+        }
+      T.err_s = std::max(T.err_s, std::sqrt(e2 / (4 * KC)));
+    }
+  for (int t = 0; t < tiles; ++t)
+    for (int col = 0; col < 16; ++col) {
+      double e2 = 0;
+      for (int nt = 0; nt < NK; ++nt)
+        for (int g = 0; g < 4; ++g)
+          for (int e = 0; e < 8; ++e) {
+            const int n = T.row_if[16 * nt + 4 * g + e % 4];
+            if (n >= 0)
+              e2 += put(T.fm[((size_t(t) * NK + nt) * 64 + 16 * g + col) * 8 + e], c->q_if[n] * (16 * t + col), M, e >= 4);
+          }
+      T.err_m = std::max(T.err_m, std::sqrt(e2 / N));
+    }
+  return T;
+}
+
+// Bound on | |G| of the screening pass - |G| of the search's form |, u =
+// 2^-11 the float16 rounding:
+//   eps_y sum |y|: the sums rounded (u) against the rounded SBD matrix
+//   (Cauchy-Schwarz over each lane's channels: err_s), float32 accumulation
+//   of both products (2 x 128 terms) and the float32 search's own rounding;
+//   eps_x sqrt(N) max |X|_2 >= (u + err_m) sum |X|: X rounded against the
+//   rounded MBD matrix; twice u more where the search's form rounds both;
+//   absolute: float16 operands below 2^-14, taken as lost, in units of this
+//   pass's scaled operands (every y and X) and of the search's (every X);
+//   infinite where the search's operands can overflow.
+void screen_bounds(const frbx_ctx *c, float scale, frbx::ScreenArgs &sa) {
+  const double u = std::ldexp(1.0, -11), tiny = 1.5 * std::ldexp(1.0, -14);
+  double ex = u + c->scr_err_m;
+  sa.abs_plain = 0.f;
+  if (c->precision != FRBX_PREC_F32) {
+    if (c->precision == FRBX_PREC_F16) ex += 2 * u;
+    const bool known = c->vis_absmax > 0 && std::isfinite(c->vis_absmax);
+    sa.abs_plain = known ? float(c->N * tiny / scale) : std::numeric_limits<float>::infinity();
+  }
+  sa.eps_y = float((u + c->scr_err_s) * 1.002 + 5e-5);
+  sa.eps_x = float(ex * 1.005);
+  sa.abs_scaled = float(c->N * (c->J + 1) * tiny);
 }
 
 frbx_status prepare(frbx_ctx *c) {
@@ -579,6 +692,17 @@ frbx_status prepare(frbx_ctx *c) {
       if ((s = up(c->d_sbd_a, fa)) != FRBX_OK) return s;
     }
   }
+  c->scr_blocks = 0;
+  if (use_screen(c)) {
+    const ScreenTables T = screen_tables(c);
+    std::copy(T.row_if, T.row_if + 32, c->scr_row_if);
+    c->scr_half = T.half;
+    c->scr_err_s = T.err_s;
+    c->scr_err_m = T.err_m;
+    if ((s = up(c->d_scr_sbd, T.fs)) != FRBX_OK || (s = up(c->d_scr_mbd, T.fm)) != FRBX_OK) return s;
+    if ((s = c->hip(frbx::screen_blocks(J, N, T.half, c->sbd_pad, c->device, &c->scr_blocks), "screening pass")) != FRBX_OK)
+      return s;
+  }
   // Float32 general form: the fringe kernel compiled for the rows of the
   // first MBD pass that hold an IF (the same sums, only those rows read
   // and transformed); the statically built kernel when every row holds an
@@ -593,7 +717,7 @@ frbx_status prepare(frbx_ctx *c) {
     for (int n = 0; n < N; ++n) rows |= 1u << (c->q_if[n] / MB);
     const unsigned all = MA >= 32 ? ~0u : (1u << MA) - 1u;
     if (rows != all) {
-      c->rows_fn = frbx::fringe_rows_kernel(c->device, J, M, rows, &c->rows_note);
+      c->rows_fn = frbx::fringe_rows_kernel(c->device, J, M, rows, c->scr_blocks > 0, &c->rows_note);
       if (c->rows_fn) c->rows_mask = rows;
     }
   }
@@ -1172,18 +1296,27 @@ frbx_status recheck_pass(frbx_ctx *c, const PassSpec &ps, frbx::StatsArgs &st, s
   return c->hip(frbx::launch_fringe_list(J, M, fa, lds, int(n), c->stream), "recheck launch");
 }
 
+// bytes of the screening records of one DM trial of S segments
+size_t rec_bytes(const frbx_ctx *c, int64_t S) {
+  return size_t(S) * c->n_rate * frbx::screen_rec_bytes(c->sbd_pad * c->J / 16);
+}
+
 // Dedispersion and fringe search of every (baseline, DM tile): the DM
 // trials are taken dt at a time through the dedispersed-tile buffer wbuf
 // ([dt][k_eff][N J]), and every segment's peak goes into the cube
-// power / pidx ([B][D][S]).
-frbx_status search_tiles(frbx_ctx *c, const PassSpec &ps, float2 *wbuf, int dt, float *power, int32_t *pidx) {
+// power / pidx ([B][D][S]).  A screened search writes the screening records
+// of a tile to rec (null: none, every unit of every segment is evaluated).
+frbx_status search_tiles(frbx_ctx *c, const PassSpec &ps, float2 *wbuf, int dt, unsigned char *rec, float *power,
+                         int32_t *pidx) {
   const int B = c->B, D = c->n_dm, NJ = c->N * c->J, nw = int(c->windows.size());
   const int64_t S = ps.S;
   const int64_t k_eff = ps.K - c->dk_max;
   const int J = c->J, M = c->n_mbd;
   frbx_status s;
   const bool use_mfma = c->precision != FRBX_PREC_F32;
-  const size_t lds = frbx::fringe_lds_bytes(J, M, c->N, c->sbd_pad);
+  const bool screened = c->scr_blocks > 0;
+  const size_t lds = frbx::fringe_lds_bytes(J, M, c->N, c->sbd_pad) +
+                     (screened ? size_t(c->n_rate) * c->sbd_pad * 4 : 0);
   const float scale = mfma_scale(c);
   const size_t in_bytes = ps.vis_f16 ? 4 : 8;
   if (S > 0 && k_eff > 0) {
@@ -1245,7 +1378,36 @@ frbx_status search_tiles(frbx_ctx *c, const PassSpec &ps, float2 *wbuf, int dt, 
         fa.mfma_b_hi = c->d_mfma_hi;
         fa.mfma_b_lo = c->d_mfma_lo;
         fa.mfma_scale = scale;
+        fa.screened = screened ? 1 : 0;
         sp = c->span_begin(0, int64_t(ndt) * S);
+        if (screened && rec) {
+          fa.screen = rec;
+          fa.screen_units = c->sbd_pad * J / 16;
+          frbx::ScreenArgs sa{};
+          sa.w = wbuf;
+          sa.w_dm_stride = fa.w_dm_stride;
+          sa.n_if = c->N;
+          sa.n_rate = c->n_rate;
+          sa.units = fa.screen_units;
+          sa.n_win = nw;
+          for (int w = 0; w < nw; ++w) {
+            sa.win_len[w] = fa.win_len[w];
+            sa.win_hop[w] = fa.win_hop[w];
+            sa.win_off[w] = fa.win_off[w];
+            sa.win_k0[w] = fa.win_k0[w];
+            sa.rate_off[w] = fa.rate_off[w];
+          }
+          sa.seg_total = fa.seg_total;
+          sa.n_task = int(int64_t(ndt) * S * c->n_rate);
+          sa.rate_ph = c->d_rate;
+          sa.half = c->scr_half ? 1 : 0;
+          std::copy(c->scr_row_if, c->scr_row_if + 32, sa.row_if);
+          sa.f_sbd = c->d_scr_sbd;
+          sa.f_mbd = c->d_scr_mbd;
+          screen_bounds(c, scale, sa);
+          sa.rec = rec;
+          if ((s = c->hip(frbx::launch_screen(J, sa, c->scr_blocks, c->stream), "screening launch")) != FRBX_OK) return s;
+        }
         const hipError_t le =
             use_mfma    ? launch_matrix_core(c, fa, int(ndt * S))
             : c->rows_fn ? frbx::launch_fringe_rows(c->rows_fn, fa, lds, int(ndt * S), c->stream)
@@ -1268,8 +1430,17 @@ frbx_status device_pass(frbx_ctx *c, const PassSpec &ps, std::vector<DevCrossing
     return c->fail(FRBX_E_NOMEM, "tile budget of " + std::to_string(c->w_budget) + " bytes is below one DM trial's " +
                                      "dedispersed tile (" + std::to_string(per_dm * sizeof(float2)) + " bytes)");
   c->dt = per_dm ? int(std::max<size_t>(1, std::min<size_t>(D, c->w_budget / (per_dm * sizeof(float2))))) : 1;
-  while (c->dt > 1 && int64_t(c->dt) * S > (int64_t(1) << 31) - 1) c->dt /= 2;
+  // (a screened tile has n_rate tasks per segment)
+  const int64_t per_seg = c->scr_blocks > 0 ? c->n_rate : 1;
+  while (c->dt > 1 && int64_t(c->dt) * S * per_seg > (int64_t(1) << 31) - 1) c->dt /= 2;
   if ((s = ensure(c, c->d_w, c->w_cap, per_dm * c->dt)) != FRBX_OK) return s;
+  // the screening records; without memory for them every unit is evaluated
+  unsigned char *rec = nullptr;
+  if (c->scr_blocks > 0 && S * c->dt * per_seg <= (int64_t(1) << 31) - 1) {
+    const std::string msg = c->err;
+    if (ensure(c, c->d_rec, c->rec_cap, rec_bytes(c, S) * c->dt) == FRBX_OK) rec = c->d_rec;
+    else c->err = msg, (void)hipGetLastError();
+  }
   const size_t cube = size_t(B) * D * std::max<int64_t>(S, 1);
   if ((s = ensure(c, c->d_power, c->cube_cap, cube)) != FRBX_OK) return s;
   if ((s = ensure(c, c->d_pidx, c->pidx_cap, cube)) != FRBX_OK) return s;
@@ -1288,7 +1459,7 @@ frbx_status device_pass(frbx_ctx *c, const PassSpec &ps, std::vector<DevCrossing
     c->cross_cap = want_cap;
   }
   const bool use_mfma = c->precision != FRBX_PREC_F32;
-  if ((s = search_tiles(c, ps, c->d_w, c->dt, c->d_power, c->d_pidx)) != FRBX_OK) return s;
+  if ((s = search_tiles(c, ps, c->d_w, c->dt, rec, c->d_power, c->d_pidx)) != FRBX_OK) return s;
   // Eq. 6 statistics and threshold crossings
   frbx::StatsArgs st{};
   st.power = c->d_power;
@@ -1408,8 +1579,12 @@ frbx_status frbx_run_cube_noalloc(frbx_ctx *c, float *power, int32_t *idx, int64
     return c->fail(FRBX_E_INVAL, "one DM trial's dedispersed tile (" + std::to_string(per_dm) +
                                      " bytes) exceeds the no-alloc workspace (" +
                                      std::to_string(frbx::kNoAllocBytes) + " bytes)");
-  int dt = int(std::min<size_t>(size_t(D), frbx::kNoAllocBytes / per_dm));
-  while (dt > 1 && int64_t(dt) * S > (int64_t(1) << 31) - 1) dt /= 2;
+  // screening records behind the tiles, where both fit
+  const size_t per_rec = c->scr_blocks > 0 ? (rec_bytes(c, S) + 255) & ~size_t(255) : 0;
+  const int64_t per_seg = c->scr_blocks > 0 ? c->n_rate : 1;
+  const bool rec_fit = per_rec > 0 && per_dm + per_rec <= frbx::kNoAllocBytes && S * per_seg <= (int64_t(1) << 31) - 1;
+  int dt = int(std::min<size_t>(size_t(D), frbx::kNoAllocBytes / (per_dm + (rec_fit ? per_rec : 0))));
+  while (dt > 1 && int64_t(dt) * S * (rec_fit ? per_seg : 1) > (int64_t(1) << 31) - 1) dt /= 2;
   if (int64_t(dt) * S > (int64_t(1) << 31) - 1) return c->fail(FRBX_E_INVAL, "too many segments per DM trial");
   const int nw = int(c->windows.size());
   PassSpec ps;
@@ -1424,7 +1599,8 @@ frbx_status frbx_run_cube_noalloc(frbx_ctx *c, float *power, int32_t *idx, int64
   // no timing events (their pool may grow): launches only
   const bool tm = c->timing;
   c->timing = false;
-  const frbx_status s = search_tiles(c, ps, static_cast<float2 *>(c->d_noalloc), dt, power, idx);
+  unsigned char *rec = rec_fit ? static_cast<unsigned char *>(c->d_noalloc) + size_t(dt) * per_dm : nullptr;
+  const frbx_status s = search_tiles(c, ps, static_cast<float2 *>(c->d_noalloc), dt, rec, power, idx);
   c->timing = tm;
   return s;
 }

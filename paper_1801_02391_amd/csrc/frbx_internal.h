@@ -105,10 +105,56 @@ struct FringeArgs {
   const void *mfma_b_hi;
   const void *mfma_b_lo;
   float mfma_scale;
+  // candidate forms of the fringe kernels (screened = 1): the records of
+  // screen_kernel for the segments of this launch, [n_dt][seg_total][R]
+  // records of screen_rec_bytes(units)
+  int32_t screened;
+  const unsigned char *screen;
+  int32_t screen_units;      // P J / 16; 0: no records, every unit is a candidate
   // matrix-core SBD transform (float16 form): the real-embedded J-point DFT
   // matrix as MFMA A operands, [2J/16 row tiles][J/16 K chunks][64 lanes] x
   // 8 halves
   const void *sbd_a;
+};
+
+// Screening pass of the fringe search (screen_kernel): every |G| of every
+// segment and rate in float16 on the matrix cores, and the units (16 SBD
+// bins of one sub-grid x every MBD bin) that can hold the segment's largest
+// |G| of the search's own arithmetic, given an upper bound on the
+// difference between the two.
+constexpr int kScreenWaves = 8;          // waves per work-group
+constexpr int kScreenUnitsMax = 64;
+// One record per (segment, rate): float largest screened |G| A, float bound
+// B on |screened |G| - the search's |G||, then one byte per unit: 0 where
+// the unit's screened maximum is below A - 2 B, else v >= 1 with that
+// maximum at most A - (v - 1) B / 127.  B = +inf: nothing is known (not
+// finite, zero or extreme input) and every unit is a candidate.
+constexpr int screen_rec_bytes(int units) { return 8 + ((units + 7) & ~7); }
+
+struct ScreenArgs {
+  const float2 *w;           // [n_dt][k_eff][NJ], as for the fringe search
+  int64_t w_dm_stride;
+  int32_t n_if, n_rate;
+  int32_t units;             // P J / 16, a multiple of 4
+  int32_t n_win;
+  int32_t win_len[kMaxWindows];
+  int32_t win_hop[kMaxWindows];
+  int32_t win_off[kMaxWindows];
+  int32_t win_k0[kMaxWindows];
+  int32_t rate_off[kMaxWindows];
+  int32_t seg_total;
+  int32_t n_task;            // n_dt * seg_total * n_rate
+  const float2 *rate_ph;
+  int32_t half;              // MBD columns m and m + M/2 from one product (n_if > 16): rows 0-15 are
+                             // IFs of even lattice position, rows 16-31 of odd position
+  int32_t row_if[32];        // IF of each operand row, -1: none
+  const void *f_sbd;         // [units / 2][J/16][64 lanes] x 8 halves
+  const void *f_mbd;         // [tiles of 16 MBD bins][n_if <= 16 ? 1 : 2][64 lanes] x 8 halves
+  float eps_y;               // error bound per unit of sum |y|,
+  float eps_x;               // of sqrt(N) times the largest 2-norm of X over the IFs,
+  float abs_scaled;          // and absolute: in the units of the scaled operands,
+  float abs_plain;           // in those of the data
+  unsigned char *rec;        // [n_task] records
 };
 
 struct StatsArgs {
@@ -142,6 +188,13 @@ int fringe_compact_rows(int n_mbd);
 hipError_t launch_fringe_list(int n_chan, int n_mbd, const FringeArgs &a, size_t lds_bytes, int n,
                               hipStream_t s);
 hipError_t launch_stats(const StatsArgs &a, int rows, hipStream_t s);
+
+// Screening pass: whether the shape has one, the work-groups that fill the
+// device (persistent over the tasks; `device` current), and its launch with
+// that many.
+bool screen_supported(int n_chan, int n_mbd, int n_if, int sbd_pad);
+hipError_t screen_blocks(int n_chan, int n_if, bool half, int sbd_pad, int device, int *blocks);
+hipError_t launch_screen(int n_chan, const ScreenArgs &a, int blocks, hipStream_t s);
 
 // matrix-core fringe kernel: n_pass = 1 (float16) or 3 (float16 high/low
 // split, float32-grade products); supports n_mbd = 256, n_chan >= 16,
@@ -246,7 +299,7 @@ hipError_t noalloc_workspace(int device, void **ptr);
 // frbx_jit.cpp).  The first call for a (device, n_chan, n_mbd, rows)
 // compiles and loads it; later calls return the loaded function.  nullptr
 // with the reason in *err when it cannot be built.
-hipFunction_t fringe_rows_kernel(int device, int n_chan, int n_mbd, unsigned rows, std::string *err);
+hipFunction_t fringe_rows_kernel(int device, int n_chan, int n_mbd, unsigned rows, bool screened, std::string *err);
 hipError_t launch_fringe_rows(hipFunction_t fn, const FringeArgs &a, size_t lds_bytes, int grid,
                               hipStream_t s);
 #endif  // !__HIPCC_RTC__

@@ -5,7 +5,7 @@
 // (frbx_fringe.h, embedded by the build as frbx_rtc_source.inc) and
 // computes the same sums (a separate compilation: multiply-add fusion, and
 // so the last bits, may differ).  Modules stay loaded until the process
-// ends; one per (device, J, M, rows).
+// ends; one per (device, J, M, rows, screened).
 #include <hip/hip_runtime.h>
 #include <hip/hiprtc.h>
 
@@ -28,13 +28,14 @@ struct JitEntry {
 };
 
 std::mutex g_mu;
-std::map<std::tuple<int, int, int, unsigned>, JitEntry> g_cache;
+std::map<std::tuple<int, int, int, unsigned, bool>, JitEntry> g_cache;
 
-// Compile fringe_kernel<J, M, false, false, false, rows> for the current
-// device's architecture; fills e.fn or e.err.
-void compile(int J, int M, unsigned rows, JitEntry &e) {
+// Compile fringe_kernel<J, M, false, false, false, rows, screened> for the
+// current device's architecture; fills e.fn or e.err.
+void compile(int J, int M, unsigned rows, bool screened, JitEntry &e) {
   const std::string expr = "frbx::fringe_kernel<" + std::to_string(J) + ", " + std::to_string(M) +
-                           ", false, false, false, " + std::to_string(rows) + "u>";
+                           ", false, false, false, " + std::to_string(rows) + "u, " +
+                           (screened ? "true>" : "false>");
   hiprtcProgram prog = nullptr;
   if (hiprtcCreateProgram(&prog, kFringeRtcSource, "frbx_fringe_rtc.hip", 0, nullptr, nullptr) !=
       HIPRTC_SUCCESS) {
@@ -90,10 +91,11 @@ void compile(int J, int M, unsigned rows, JitEntry &e) {
 
 }  // namespace
 
-hipFunction_t fringe_rows_kernel(int device, int n_chan, int n_mbd, unsigned rows, std::string *err) {
+hipFunction_t fringe_rows_kernel(int device, int n_chan, int n_mbd, unsigned rows, bool screened,
+                                 std::string *err) {
   std::lock_guard<std::mutex> lock(g_mu);
-  JitEntry &e = g_cache[std::make_tuple(device, n_chan, n_mbd, rows)];
-  if (!e.fn && e.err.empty()) compile(n_chan, n_mbd, rows, e);
+  JitEntry &e = g_cache[std::make_tuple(device, n_chan, n_mbd, rows, screened)];
+  if (!e.fn && e.err.empty()) compile(n_chan, n_mbd, rows, screened, e);
   if (!e.fn && err) *err = e.err;
   return e.fn;
 }

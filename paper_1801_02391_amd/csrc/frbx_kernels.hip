@@ -252,7 +252,10 @@ __host__ __device__ inline void mfma_lds_plan(int n_if, int sbd_pad, int n_pass,
 }
 
 // The three-product form runs three waves per SIMD (168 VGPRs, no spill).
-template <int J, int NK, int NP, bool DUMP>
+// CAND: only the candidate units of the segment's screening records are
+// transformed (a unit is one 16-row step of the MBD product); the peak is
+// the full search's: per lane the largest key, then the earliest unit.
+template <int J, int NK, int NP, bool DUMP, bool CAND = false>
 __global__ __launch_bounds__(kBlock)
 __attribute__((amdgpu_waves_per_eu(mfma_three_real(J, 16 * NK, NP) && !DUMP ? 3 : 1)))
 void fringe_mfma_kernel(FringeArgs a) {
@@ -318,119 +321,163 @@ void fringe_mfma_kernel(FringeArgs a) {
   unsigned best_key = 0u;
   int best_blk = 0;
 
-  for (int r = 0; r < R; ++r) {
-    float2 y[JA];
-    segment_sum<JA, JB>(y, wd, rph, r, N, J, l, R, s_p1, n1, i2s);
-    for (int c = 0; c < P; ++c) {
-      __syncthreads();
-      sbd_pass1<JA, JB>(y, a.pre_sbd, TW, Sc, c, P, PJ, s_p1, n1, i2s);
-      __syncthreads();
-      // SBD pass 2 -> A rows a = k1 + JA k2 (SBD bin s' = c + P a), columns 2n, 2n+1
-      for (int v = t; v < N * JA; v += kBlock) {
-        const int n2 = v / JA, k1 = v - (v / JA) * JA;
-        float2 z[JB];
-        static_for<0, JB>([&](auto i) {
-          constexpr int ii = decltype(i)::value;
-          z[ii] = Sc[(n2 * JA + k1) * (JB + 1) + ii];
-        });
-        dft<JB>(z);
-        static_for<0, JB>([&](auto k) {
-          constexpr int kk = decltype(k)::value;
-          const float xr = z[kk].x * scale, xi = z[kk].y * scale;
-          if constexpr (K3) {
-            // chunks Re X, Im X, Re X + Im X at K = n
-            const int o = (k1 + JA * kk) * AS + n2;
-            const float xs = xr + xi;
-            const _Float16 hr = _Float16(xr), hi_ = _Float16(xi), hs = _Float16(xs);
-            Ahi[o] = hr;
-            Ahi[o + 32] = hi_;
-            Ahi[o + 64] = hs;
-            Alo[o] = _Float16(xr - float(hr));
-            Alo[o + 32] = _Float16(xi - float(hi_));
-            Alo[o + 64] = _Float16(xs - float(hs));
-          } else {
-            h2_t hi;
-            hi.x = _Float16(xr);
-            hi.y = _Float16(xi);
-            const int o = (k1 + JA * kk) * AS + 2 * n2;
-            *reinterpret_cast<h2_t *>(Ahi + o) = hi;
-            if constexpr (NP == 3) {
-              h2_t lo;
-              lo.x = _Float16(xr - float(hi.x));
-              lo.y = _Float16(xi - float(hi.y));
-              *reinterpret_cast<h2_t *>(Alo + o) = lo;
-            }
+  float2 y[JA];
+  // SBD transform of sub-grid c -> A operand rows
+  auto sbd = [&](int c) {
+    __syncthreads();
+    sbd_pass1<JA, JB>(y, a.pre_sbd, TW, Sc, c, P, PJ, s_p1, n1, i2s);
+    __syncthreads();
+    // SBD pass 2 -> A rows a = k1 + JA k2 (SBD bin s' = c + P a), columns 2n, 2n+1
+    for (int v = t; v < N * JA; v += kBlock) {
+      const int n2 = v / JA, k1 = v - (v / JA) * JA;
+      float2 z[JB];
+      static_for<0, JB>([&](auto i) {
+        constexpr int ii = decltype(i)::value;
+        z[ii] = Sc[(n2 * JA + k1) * (JB + 1) + ii];
+      });
+      dft<JB>(z);
+      static_for<0, JB>([&](auto k) {
+        constexpr int kk = decltype(k)::value;
+        const float xr = z[kk].x * scale, xi = z[kk].y * scale;
+        if constexpr (K3) {
+          // chunks Re X, Im X, Re X + Im X at K = n
+          const int o = (k1 + JA * kk) * AS + n2;
+          const float xs = xr + xi;
+          const _Float16 hr = _Float16(xr), hi_ = _Float16(xi), hs = _Float16(xs);
+          Ahi[o] = hr;
+          Ahi[o + 32] = hi_;
+          Ahi[o + 64] = hs;
+          Alo[o] = _Float16(xr - float(hr));
+          Alo[o + 32] = _Float16(xi - float(hi_));
+          Alo[o + 64] = _Float16(xs - float(hs));
+        } else {
+          h2_t hi;
+          hi.x = _Float16(xr);
+          hi.y = _Float16(xi);
+          const int o = (k1 + JA * kk) * AS + 2 * n2;
+          *reinterpret_cast<h2_t *>(Ahi + o) = hi;
+          if constexpr (NP == 3) {
+            h2_t lo;
+            lo.x = _Float16(xr - float(hi.x));
+            lo.y = _Float16(xi - float(hi.y));
+            *reinterpret_cast<h2_t *>(Alo + o) = lo;
           }
+        }
+      });
+    }
+    __syncthreads();
+  };
+  // MBD on the matrix cores, 16 SBD rows at a time
+  auto unit = [&](int r, int c, int sb) {
+    h8_t ah[NKA], al[NKA];
+    const int arow = (16 * sb + (lane & 15)) * AS + 8 * (lane >> 4);
+    static_for<0, NKA>([&](auto kk) {
+      constexpr int kc = decltype(kk)::value;
+      ah[kc] = *reinterpret_cast<const h8_t *>(Ahi + arow + 32 * kc);
+      if constexpr (NP == 3) al[kc] = *reinterpret_cast<const h8_t *>(Alo + arow + 32 * kc);
+    });
+    // peak key of this lane's 16 cells: |G|^2 with its 4 lowest mantissa
+    // bits replaced by (15 - slot), so one unsigned max keeps the value
+    // (to 2^-19 relative) and the lowest slot among equal values
+    unsigned kmax = 0u;
+    static_for<0, 4>([&](auto pp) {
+      constexpr int p = decltype(pp)::value;
+      f4_t gr = {0.f, 0.f, 0.f, 0.f}, gi = {0.f, 0.f, 0.f, 0.f};
+      if constexpr (K3) {
+        f4_t p3 = {0.f, 0.f, 0.f, 0.f};
+        // small products first, as below
+        gr = __builtin_amdgcn_mfma_f32_16x16x32_f16(al[0], bh[p][0], gr, 0, 0, 0);
+        gi = __builtin_amdgcn_mfma_f32_16x16x32_f16(al[1], bh[p][1], gi, 0, 0, 0);
+        p3 = __builtin_amdgcn_mfma_f32_16x16x32_f16(al[2], bh[p][2], p3, 0, 0, 0);
+        gr = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[0], bl[p][0], gr, 0, 0, 0);
+        gi = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[1], bl[p][1], gi, 0, 0, 0);
+        p3 = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[2], bl[p][2], p3, 0, 0, 0);
+        gr = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[0], bh[p][0], gr, 0, 0, 0);
+        gi = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[1], bh[p][1], gi, 0, 0, 0);
+        p3 = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[2], bh[p][2], p3, 0, 0, 0);
+        // gr = P1, gi = P2 -> Re, Im
+        static_for<0, 4>([&](auto ii) {
+          constexpr int i = decltype(ii)::value;
+          const float p1 = gr[i], p2 = gi[i];
+          gr[i] = p1 - p2;
+          gi[i] = (p3[i] - p1) - p2;
+        });
+      } else {
+        static_for<0, NK>([&](auto kk) {
+          constexpr int kc = decltype(kk)::value;
+          if constexpr (NP == 3) {
+            gr = __builtin_amdgcn_mfma_f32_16x16x32_f16(al[kc], bh[p][kc], gr, 0, 0, 0);
+            gi = __builtin_amdgcn_mfma_f32_16x16x32_f16(al[kc], bh[4 + p][kc], gi, 0, 0, 0);
+            gr = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[kc], bl[p][kc], gr, 0, 0, 0);
+            gi = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[kc], bl[4 + p][kc], gi, 0, 0, 0);
+          }
+          gr = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[kc], bh[p][kc], gr, 0, 0, 0);
+          gi = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[kc], bh[4 + p][kc], gi, 0, 0, 0);
         });
       }
-      __syncthreads();
-      // MBD on the matrix cores, 16 SBD rows at a time
-      for (int sb = 0; sb < NSB; ++sb) {
-        h8_t ah[NKA], al[NKA];
-        const int arow = (16 * sb + (lane & 15)) * AS + 8 * (lane >> 4);
-        static_for<0, NKA>([&](auto kk) {
-          constexpr int kc = decltype(kk)::value;
-          ah[kc] = *reinterpret_cast<const h8_t *>(Ahi + arow + 32 * kc);
-          if constexpr (NP == 3) al[kc] = *reinterpret_cast<const h8_t *>(Alo + arow + 32 * kc);
-        });
-        // peak key of this lane's 16 cells: |G|^2 with its 4 lowest mantissa
-        // bits replaced by (15 - slot), so one unsigned max keeps the value
-        // (to 2^-19 relative) and the lowest slot among equal values
-        unsigned kmax = 0u;
-        static_for<0, 4>([&](auto pp) {
-          constexpr int p = decltype(pp)::value;
-          f4_t gr = {0.f, 0.f, 0.f, 0.f}, gi = {0.f, 0.f, 0.f, 0.f};
-          if constexpr (K3) {
-            f4_t p3 = {0.f, 0.f, 0.f, 0.f};
-            // small products first, as below
-            gr = __builtin_amdgcn_mfma_f32_16x16x32_f16(al[0], bh[p][0], gr, 0, 0, 0);
-            gi = __builtin_amdgcn_mfma_f32_16x16x32_f16(al[1], bh[p][1], gi, 0, 0, 0);
-            p3 = __builtin_amdgcn_mfma_f32_16x16x32_f16(al[2], bh[p][2], p3, 0, 0, 0);
-            gr = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[0], bl[p][0], gr, 0, 0, 0);
-            gi = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[1], bl[p][1], gi, 0, 0, 0);
-            p3 = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[2], bl[p][2], p3, 0, 0, 0);
-            gr = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[0], bh[p][0], gr, 0, 0, 0);
-            gi = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[1], bh[p][1], gi, 0, 0, 0);
-            p3 = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[2], bh[p][2], p3, 0, 0, 0);
-            // gr = P1, gi = P2 -> Re, Im
-            static_for<0, 4>([&](auto ii) {
-              constexpr int i = decltype(ii)::value;
-              const float p1 = gr[i], p2 = gi[i];
-              gr[i] = p1 - p2;
-              gi[i] = (p3[i] - p1) - p2;
-            });
-          } else {
-            static_for<0, NK>([&](auto kk) {
-              constexpr int kc = decltype(kk)::value;
-              if constexpr (NP == 3) {
-                gr = __builtin_amdgcn_mfma_f32_16x16x32_f16(al[kc], bh[p][kc], gr, 0, 0, 0);
-                gi = __builtin_amdgcn_mfma_f32_16x16x32_f16(al[kc], bh[4 + p][kc], gi, 0, 0, 0);
-                gr = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[kc], bl[p][kc], gr, 0, 0, 0);
-                gi = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[kc], bl[4 + p][kc], gi, 0, 0, 0);
-              }
-              gr = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[kc], bh[p][kc], gr, 0, 0, 0);
-              gi = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[kc], bh[4 + p][kc], gi, 0, 0, 0);
-            });
-          }
-          static_for<0, 4>([&](auto ii) {
-            constexpr int i = decltype(ii)::value;
-            const float v = gr[i] * gr[i] + gi[i] * gi[i];
-            const unsigned key = (__float_as_uint(v) & 0xFFFFFFF0u) | unsigned(15 - (p * 4 + i));
-            kmax = kmax > key ? kmax : key;
-            if constexpr (DUMP) {
-              const int arow_i = 16 * sb + 4 * (lane >> 4) + i;
-              const int s = (c + P * arow_i + (PJ >> 1)) & (PJ - 1);
-              const int m = (16 * (4 * wave + p) + (lane & 15) + (M >> 1)) & (M - 1);
-              a.dump[(r * PJ + s) * M + m] = v / (scale * scale);
-            }
-          });
-        });
-        const float bv = __uint_as_float(kmax & 0xFFFFFFF0u);
-        if (bv > best_v) {
-          best_v = bv;
-          best_key = kmax;
-          best_blk = (r * P + c) * NSB + sb;
+      static_for<0, 4>([&](auto ii) {
+        constexpr int i = decltype(ii)::value;
+        const float v = gr[i] * gr[i] + gi[i] * gi[i];
+        const unsigned key = (__float_as_uint(v) & 0xFFFFFFF0u) | unsigned(15 - (p * 4 + i));
+        kmax = kmax > key ? kmax : key;
+        if constexpr (DUMP) {
+          const int arow_i = 16 * sb + 4 * (lane >> 4) + i;
+          const int s = (c + P * arow_i + (PJ >> 1)) & (PJ - 1);
+          const int m = (16 * (4 * wave + p) + (lane & 15) + (M >> 1)) & (M - 1);
+          a.dump[(r * PJ + s) * M + m] = v / (scale * scale);
         }
+      });
+    });
+    const float bv = __uint_as_float(kmax & 0xFFFFFFF0u);
+    const int blk = (r * P + c) * NSB + sb;
+    if (bv > best_v || (CAND && bv == best_v && blk < best_blk)) {
+      best_v = bv;
+      best_key = kmax;
+      best_blk = blk;
+    }
+  };
+
+  if constexpr (CAND) {
+    unsigned *cand = reinterpret_cast<unsigned *>(reinterpret_cast<char *>(lds) + total);   // [R P] after the plan
+    const Candidates cs{a.screen + (int64_t(dl) * a.seg_total + seg) * R * screen_rec_bytes(a.screen_units), R,
+                        a.screen_units, NSB};
+    for (int i = t; i < R * P; i += kBlock) cand[i] = 0u;
+    int rc0, sb0, cur_r = -1;
+    cs.first(lane, P, rc0, sb0);
+    for (int it = rc0 >= 0 ? -1 : 0; it < R * P; ++it) {
+      if (it == 0) {   // what the first unit leaves
+        float amp = -1.0f;
+        if (rc0 >= 0) {
+          float v = best_v;
+          for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
+          if (lane == 0) red_v[wave] = v;
+          __syncthreads();
+          for (int w = 0; w < kBlock / 64; ++w) amp = fmaxf(amp, red_v[w]);
+          amp = amp >= 0.0f ? sqrtf(amp) / scale : -1.0f;
+        } else {
+          __syncthreads();   // cand is cleared
+        }
+        cs.mark(t, kBlock, P, amp, cand);
+        __syncthreads();
+      }
+      const int rc = it < 0 ? rc0 : it;
+      const unsigned mask = it < 0 ? 1u << sb0 : rc == rc0 ? cand[rc] & ~(1u << sb0) : cand[rc];
+      if (!mask) continue;
+      const int r = rc / P, c = rc - (rc / P) * P;
+      if (r != cur_r) {
+        segment_sum<JA, JB>(y, wd, rph, r, N, J, l, R, s_p1, n1, i2s);
+        cur_r = r;
+      }
+      sbd(c);
+      for (unsigned m = mask; m; m &= m - 1) unit(r, c, __ffs(int(m)) - 1);
+    }
+    __syncthreads();   // red_v has been read
+  } else {
+    for (int r = 0; r < R; ++r) {
+      segment_sum<JA, JB>(y, wd, rph, r, N, J, l, R, s_p1, n1, i2s);
+      for (int c = 0; c < P; ++c) {
+        sbd(c);
+        for (int sb = 0; sb < NSB; ++sb) unit(r, c, sb);
       }
     }
   }
@@ -1126,16 +1173,16 @@ hipError_t launch_dedisperse(const DedisperseArgs &a, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int J, int M, bool DUMP, bool CL, bool LIST = false>
+template <int J, int M, bool DUMP, bool CL, bool LIST = false, bool CAND = false>
 static hipError_t launch_fringe_t(const FringeArgs &a, size_t lds, int grid, hipStream_t s) {
   (void)hipGetLastError();  // start from a clean error state
   if (lds > 64 * 1024) {
     const hipError_t e =
-        hipFuncSetAttribute(reinterpret_cast<const void *>(&fringe_kernel<J, M, DUMP, CL, LIST>),
+        hipFuncSetAttribute(reinterpret_cast<const void *>(&fringe_kernel<J, M, DUMP, CL, LIST, 0u, CAND>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((fringe_kernel<J, M, DUMP, CL, LIST>), dim3(grid), dim3(kBlock), lds, s, a);
+  hipLaunchKernelGGL((fringe_kernel<J, M, DUMP, CL, LIST, 0u, CAND>), dim3(grid), dim3(kBlock), lds, s, a);
   return hipGetLastError();
 }
 
@@ -1168,6 +1215,12 @@ struct LaunchFn {
   int grid;
   hipStream_t s;
   template <int J, int M> hipError_t operator()() {
+    if (a.screened) {
+      if constexpr (M == 256 && (J == 32 || J == 64))
+        return a.mbd_pos ? launch_fringe_t<J, M, false, true, false, true>(a, lds, grid, s)
+                         : launch_fringe_t<J, M, false, false, false, true>(a, lds, grid, s);
+      return hipErrorInvalidValue;
+    }
     if (a.mbd_pos)
       return a.dump ? launch_fringe_t<J, M, true, true>(a, lds, grid, s)
                     : launch_fringe_t<J, M, false, true>(a, lds, grid, s);
@@ -1253,24 +1306,21 @@ hipError_t launch_stats(const StatsArgs &a, int rows, hipStream_t s) {
 template <int J, int NK, int NP>
 static hipError_t launch_mfma_t(const FringeArgs &a, size_t lds, int grid, hipStream_t s) {
   (void)hipGetLastError();
-  if (a.dump) {
+  auto go = [&](auto kern) -> hipError_t {
     if (lds > 64 * 1024) {
-      const hipError_t e = hipFuncSetAttribute(
-          reinterpret_cast<const void *>(&fringe_mfma_kernel<J, NK, NP, true>),
-          hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
       if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((fringe_mfma_kernel<J, NK, NP, true>), dim3(grid), dim3(kBlock), lds, s, a);
-  } else {
-    if (lds > 64 * 1024) {
-      const hipError_t e = hipFuncSetAttribute(
-          reinterpret_cast<const void *>(&fringe_mfma_kernel<J, NK, NP, false>),
-          hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
-      if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL((fringe_mfma_kernel<J, NK, NP, false>), dim3(grid), dim3(kBlock), lds, s, a);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), lds, s, a);
+    return hipGetLastError();
+  };
+  if (a.dump) return go(&fringe_mfma_kernel<J, NK, NP, true>);
+  if (a.screened) {
+    if constexpr (J == 32 || J == 64) return go(&fringe_mfma_kernel<J, NK, NP, false, true>);
+    return hipErrorInvalidValue;
   }
-  return hipGetLastError();
+  return go(&fringe_mfma_kernel<J, NK, NP, false>);
 }
 
 template <int J>
