@@ -37,7 +37,7 @@ SBD_GEMM_CHANNELS = (16, 32, 64)
 
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_vgos_6bl_20000.txt")
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_1801_02391_amd", "csrc", f)
-                  for f in ("frbx_kernels.hip", "frbx_fringe.h")]
+                  for f in ("frbx_kernels.hip", "frbx_screen.hip", "frbx_fringe.h")]
 
 
 def kernel_code_sha256():

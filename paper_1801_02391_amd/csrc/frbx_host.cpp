@@ -385,12 +385,28 @@ bool use_gemm(const frbx_ctx *c) {
          frbx::fringe_gemm_supported(c->J, c->n_mbd, c->N, c->sbd_pad);
 }
 
+// The halved MBD product: more than 16 IFs, at most 16 of them on even and 16
+// on odd lattice positions.
+bool screen_half(const frbx_ctx *c) {
+  int n_odd = 0;
+  for (int n = 0; n < c->N; ++n) n_odd += int(c->q_if[n] & 1);
+  return c->N > 16 && n_odd <= 16 && c->N - n_odd <= 16;
+}
+
 // A screened search: the float16 screening pass names the candidate units of
 // every segment and the search's kernel evaluates those.  Every form but the
 // one with the SBD transform on the matrix cores, where the pass has the
-// shape (and the candidate masks fit beside the kernel's LDS plan).
+// shape (and the candidate masks fit beside the kernel's LDS plan) and a
+// segment has enough units: with 16 the candidates are a tenth of the
+// search; with 8 (one rate, 32 channels, sbd_pad 4) they are a quarter and
+// the screened search is the slower one (20 s of the paper's set-up: 1.82
+// against 1.59 ms).  The float16 form's own products are the screening
+// pass's but for the halved MBD product, so it is screened only where that
+// applies (one baseline, 16 IFs or fewer: 3.38 against 3.11 ms).
 bool use_screen(const frbx_ctx *c) {
   if (use_gemm(c) || !frbx::screen_supported(c->J, c->n_mbd, c->N, c->sbd_pad)) return false;
+  if (c->n_rate * c->sbd_pad * c->J / 16 < 16) return false;
+  if (c->precision == FRBX_PREC_F16 && !screen_half(c)) return false;
   const size_t lds = c->precision == FRBX_PREC_F32
                          ? frbx::fringe_lds_bytes(c->J, c->n_mbd, c->N, c->sbd_pad)
                          : frbx::fringe_mfma_lds_bytes(c->J, c->N, c->sbd_pad, c->precision == FRBX_PREC_F16X3 ? 3 : 1);
@@ -413,8 +429,9 @@ hipError_t launch_matrix_core(const frbx_ctx *c, frbx::FringeArgs &fa, int grid)
 
 // Constant operands of the screening pass in the per-lane order of
 // v_mfma_f32_16x16x32_f16 (lane ln: column ln % 16, group g = ln / 16,
-// element e; cos for e < 4 and sin for e >= 4 of the phase), and what
-// rounding them to float16 costs.
+// element e; for the real part cos for e < 4 and sin for e >= 4 of the phase,
+// for the imaginary part -sin and cos), and what rounding them to float16
+// costs.
 //   SBD: unit pair p = sub-grid c = p / (J / 32), bins s' = c + P a with
 //   a = 16 (p % (J / 32)) + column < J / 2 (the pair's second unit is
 //   a + J / 2); chunk 2 kp + par, element e is channel 32 kp + 8 (e % 4) +
@@ -435,21 +452,37 @@ ScreenTables screen_tables(const frbx_ctx *c) {
   ScreenTables T;
   const int N = c->N, J = c->J, P = c->sbd_pad, PJ = P * J, KC = J / 16, KP = J / 32, pairs = PJ / 32, M = c->n_mbd;
   const int NK = N <= 16 ? 1 : 2;
-  int n_odd = 0;
-  for (int n = 0; n < N; ++n) n_odd += int(c->q_if[n] & 1);
-  T.half = N > 16 && n_odd <= 16 && N - n_odd <= 16;
+  T.half = screen_half(c);
   std::fill(T.row_if, T.row_if + 32, -1);
   for (int n = 0, next[2] = {0, 16}, k = 0; n < N; ++n) {
     if (T.half) T.row_if[next[c->q_if[n] & 1]++] = n;
     else T.row_if[k++] = n;
   }
   const int tiles = T.half ? M / 32 : M / 16;
-  T.fs.assign(size_t(pairs) * KC * 64 * 8, _Float16(0));
-  T.fm.assign(size_t(tiles) * NK * 64 * 8, _Float16(0));
-  auto put = [](_Float16 &out, int64_t k, int64_t n, bool sine) {   // returns the squared rounding error
-    const double th = kTwoPi * double(k % n) / double(n), v = sine ? std::sin(th) : std::cos(th);
-    out = static_cast<_Float16>(v);
-    return (double(out) - v) * (double(out) - v);
+  T.fs.assign(size_t(pairs) * KC * 2 * 64 * 8, _Float16(0));
+  T.fm.assign(size_t(tiles) * NK * 2 * 64 * 8, _Float16(0));
+  // cos, sin of 2 pi k / n as float16 and their squared rounding errors
+  struct Root {
+    _Float16 cs, sn;
+    double e_cs, e_sn;
+  };
+  auto roots = [](int n) {
+    std::vector<Root> w(n);
+    for (int k = 0; k < n; ++k) {
+      const double th = kTwoPi * double(k) / double(n), cs = std::cos(th), sn = std::sin(th);
+      w[k].cs = static_cast<_Float16>(cs);
+      w[k].sn = static_cast<_Float16>(sn);
+      w[k].e_cs = (double(w[k].cs) - cs) * (double(w[k].cs) - cs);
+      w[k].e_sn = (double(w[k].sn) - sn) * (double(w[k].sn) - sn);
+    }
+    return w;
+  };
+  const std::vector<Root> ws = roots(PJ), wm = roots(M);
+  // element e of both parts of a chunk; returns the squared rounding error of its cos (e < 4) or sin
+  auto put = [](_Float16 *re, _Float16 *im, int e, const Root &w) {
+    re[e] = e < 4 ? w.cs : w.sn;
+    im[e] = e < 4 ? -w.sn : w.cs;
+    return e < 4 ? w.e_cs : w.e_sn;
   };
   for (int p = 0; p < pairs; ++p)
     for (int ln = 0; ln < 64; ++ln) {
@@ -458,7 +491,8 @@ ScreenTables screen_tables(const frbx_ctx *c) {
         for (int e = 0; e < 8; ++e) {
           const int j = 32 * (kc / 2) + 8 * (e % 4) + 2 * (ln / 16) + kc % 2;
           const int sp = p / KP + P * (16 * (p % KP) + ln % 16);
-          e2 += put(T.fs[((size_t(p) * KC + kc) * 64 + ln) * 8 + e], int64_t(j) * sp, PJ, e >= 4);
+          _Float16 *re = &T.fs[((size_t(p) * KC + kc) * 2 * 64 + ln) * 8];
+          e2 += put(re, re + 64 * 8, e, ws[(j * sp) % PJ]);
         }
       T.err_s = std::max(T.err_s, std::sqrt(e2 / (4 * KC)));
     }
@@ -469,8 +503,8 @@ ScreenTables screen_tables(const frbx_ctx *c) {
         for (int g = 0; g < 4; ++g)
           for (int e = 0; e < 8; ++e) {
             const int n = T.row_if[16 * nt + 4 * g + e % 4];
-            if (n >= 0)
-              e2 += put(T.fm[((size_t(t) * NK + nt) * 64 + 16 * g + col) * 8 + e], c->q_if[n] * (16 * t + col), M, e >= 4);
+            _Float16 *re = &T.fm[((size_t(t) * NK + nt) * 2 * 64 + 16 * g + col) * 8];
+            if (n >= 0) e2 += put(re, re + 64 * 8, e, wm[(c->q_if[n] * (16 * t + col)) % M]);
           }
       T.err_m = std::max(T.err_m, std::sqrt(e2 / N));
     }

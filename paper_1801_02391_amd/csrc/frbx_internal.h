@@ -148,8 +148,8 @@ struct ScreenArgs {
   int32_t half;              // MBD columns m and m + M/2 from one product (n_if > 16): rows 0-15 are
                              // IFs of even lattice position, rows 16-31 of odd position
   int32_t row_if[32];        // IF of each operand row, -1: none
-  const void *f_sbd;         // [units / 2][J/16][64 lanes] x 8 halves
-  const void *f_mbd;         // [tiles of 16 MBD bins][n_if <= 16 ? 1 : 2][64 lanes] x 8 halves
+  const void *f_sbd;         // [units / 2][J/16][re, im][64 lanes] x 8 halves
+  const void *f_mbd;         // [tiles of 16 MBD bins][n_if <= 16 ? 1 : 2][re, im][64 lanes] x 8 halves
   float eps_y;               // error bound per unit of sum |y|,
   float eps_x;               // of sqrt(N) times the largest 2-norm of X over the IFs,
   float abs_scaled;          // and absolute: in the units of the scaled operands,

@@ -20,9 +20,8 @@
 // The accumulator of v_mfma_f32_16x16x32_f16 holds, per lane, one column
 // (s) and four rows (n); rounded to float16 these are exactly a lane's K
 // elements of the next product's A operand (row s), so X never leaves the
-// registers.  With A = [re, im] against B = [cos, sin] the product is the
-// real part, and with A' = [im, -re] against the same B the imaginary part:
-// one constant matrix serves both.
+// registers.  A = [re, im] against B = [cos, sin] is the real part of the
+// product, against [-sin, cos] the imaginary one.
 //
 // One wave takes one (segment, rate): it forms the segment sums in registers
 // in the A layout, and streams both constant matrices from LDS, where one
@@ -40,29 +39,22 @@ namespace frbx {
 namespace {
 
 typedef _Float16 h8_t __attribute__((ext_vector_type(8)));
-typedef _Float16 h2_t __attribute__((ext_vector_type(2)));
 typedef float f4_t __attribute__((ext_vector_type(4)));
-typedef unsigned u4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kScreenBlock = 64 * kScreenWaves;
 
-// The A operands of the real and the imaginary part from four complex
-// values: [re, im] and [im, -re].
-__device__ __forceinline__ void embed(const float (&re)[4], const float (&im)[4], h8_t &a, h8_t &b) {
-  const h2_t r0 = {_Float16(re[0]), _Float16(re[1])}, r1 = {_Float16(re[2]), _Float16(re[3])};
-  const h2_t i0 = {_Float16(im[0]), _Float16(im[1])}, i1 = {_Float16(im[2]), _Float16(im[3])};
-  const u4_t x = {__builtin_bit_cast(unsigned, r0), __builtin_bit_cast(unsigned, r1),
-                  __builtin_bit_cast(unsigned, i0), __builtin_bit_cast(unsigned, i1)};
-  const u4_t y = {x[2], x[3], x[0] ^ 0x80008000u, x[1] ^ 0x80008000u};
-  a = __builtin_bit_cast(h8_t, x);
-  b = __builtin_bit_cast(h8_t, y);
+// A operand [re, im] of four complex values.
+__device__ __forceinline__ h8_t pack(const float (&re)[4], const float (&im)[4]) {
+  return h8_t{_Float16(re[0]), _Float16(re[1]), _Float16(re[2]), _Float16(re[3]),
+              _Float16(im[0]), _Float16(im[1]), _Float16(im[2]), _Float16(im[3])};
 }
 
-// Largest value of the wave, in every lane (v >= 0).
+// Largest value of the wave, in every lane (v >= 0: its bits order like it).
 __device__ __forceinline__ float wave_max(float v) {
+  unsigned m = __float_as_uint(v);
   auto step = [&](auto ctrl) {
     constexpr int c = decltype(ctrl)::value;
-    v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), c, 0xf, 0xf, true)));
+    m = max(m, unsigned(__builtin_amdgcn_update_dpp(0, int(m), c, 0xf, 0xf, true)));
   };
   step(Index<0xb1>{});    // quad_perm 1 0 3 2
   step(Index<0x4e>{});    // quad_perm 2 3 0 1
@@ -70,7 +62,7 @@ __device__ __forceinline__ float wave_max(float v) {
   step(Index<0x140>{});   // row_mirror
   step(Index<0x142>{});   // row_bcast15
   step(Index<0x143>{});   // row_bcast31
-  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
+  return __uint_as_float(unsigned(__builtin_amdgcn_readlane(int(m), 63)));
 }
 
 // HALF: the MBD product on half of its columns.  Rows n hold the IFs of even
@@ -87,16 +79,17 @@ void screen_kernel(ScreenArgs a) {
   constexpr int MT = HALF ? 8 : 16;        // MBD column tiles
   constexpr int UP = 2;                    // unit pairs per pass over the MBD matrix
   extern __shared__ h8_t lds_h[];
-  h8_t *const Fm = lds_h;                  // [MT][NK][64]
-  h8_t *const Fs = lds_h + MT * NK * 64;   // [units / 2][2 KP][64]
+  h8_t *const Fm = lds_h;                      // [MT][NK][re, im][64]
+  h8_t *const Fs = lds_h + MT * NK * 2 * 64;   // [units / 2][2 KP][re, im][64]
+  __shared__ int next;                         // tasks taken by the work-group
   const int N = a.n_if, R = a.n_rate, NJ = N * J, units = a.units;
   {
     const h8_t *gm = static_cast<const h8_t *>(a.f_mbd), *gs = static_cast<const h8_t *>(a.f_sbd);
-    for (int i = threadIdx.x; i < MT * NK * 64; i += kScreenBlock) Fm[i] = gm[i];
-    for (int i = threadIdx.x; i < units * KP * 64; i += kScreenBlock) Fs[i] = gs[i];
+    for (int i = threadIdx.x; i < MT * NK * 2 * 64; i += kScreenBlock) Fm[i] = gm[i];
+    for (int i = threadIdx.x; i < units * KP * 2 * 64; i += kScreenBlock) Fs[i] = gs[i];
+    if (threadIdx.x == 0) next = 0;
   }
   __syncthreads();
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63, row = lane & 15, g = lane >> 4;
   // the IF of this lane's rows (absent rows read the first IF's data and are cleared)
   int rif[NK];
@@ -111,7 +104,15 @@ void screen_kernel(ScreenArgs a) {
   const int stride = (nb / n_x) * kScreenWaves;
   const int lo = int(int64_t(a.n_task) * xcd / n_x), hi = int(int64_t(a.n_task) * (xcd + 1) / n_x);
 
-  for (int task = lo + slot * kScreenWaves + wave; task < hi; task += stride) {
+  for (;;) {
+    // the work-group's next task: waves on one SIMD do not advance evenly (the
+    // older one issues first), so none has tasks of its own
+    int k = 0;
+    if (lane == 0) k = atomicAdd(&next, 1);
+    k = __builtin_amdgcn_readfirstlane(k);
+    const int64_t at = lo + int64_t(k / kScreenWaves) * stride + slot * kScreenWaves + k % kScreenWaves;
+    if (at >= hi) break;
+    const int task = int(at);
     const int sg = task / R, r = task - sg * R;
     const int dl = sg / a.seg_total, seg = sg - dl * a.seg_total;
     int wi = 0;
@@ -125,10 +126,6 @@ void screen_kernel(ScreenArgs a) {
     // row 16 nt + row, channels 32 kp + 8 h + 2 g + {0, 1}, h < 4:
     // y[nt][kp][4 h + {0, 1}] even, {2, 3} odd channel
     float y[NK][KP][16];
-    static_for<0, NK * KP * 16>([&](auto i) {
-      constexpr int k = decltype(i)::value;
-      y[k / (KP * 16)][(k / 16) % KP][k % 16] = 0.f;
-    });
     int off[NK], pho[NK];
     static_for<0, NK>([&](auto i) {
       constexpr int nt = decltype(i)::value;
@@ -136,7 +133,8 @@ void screen_kernel(ScreenArgs a) {
       off[nt] = n * J + 2 * g;
       pho[nt] = n * l;
     });
-    for (int u = 0; u < l; ++u) {
+    auto add_ap = [&](int u, auto first_tag) {
+      constexpr bool FIRST = decltype(first_tag)::value != 0;
       const float2 *src = wd + int64_t(u) * NJ;
       float4 v[NK][KP][4];
       float2 p[NK];
@@ -154,13 +152,15 @@ void screen_kernel(ScreenArgs a) {
           constexpr int k = decltype(kk)::value;
           const float4 x = v[nt][k / 4][k % 4];
           float *o = &y[nt][k / 4][4 * (k % 4)];
-          o[0] = fmaf(x.x, p[nt].x, fmaf(-x.y, p[nt].y, o[0]));
-          o[1] = fmaf(x.x, p[nt].y, fmaf(x.y, p[nt].x, o[1]));
-          o[2] = fmaf(x.z, p[nt].x, fmaf(-x.w, p[nt].y, o[2]));
-          o[3] = fmaf(x.z, p[nt].y, fmaf(x.w, p[nt].x, o[3]));
+          o[0] = fmaf(x.x, p[nt].x, FIRST ? -x.y * p[nt].y : fmaf(-x.y, p[nt].y, o[0]));
+          o[1] = fmaf(x.x, p[nt].y, FIRST ? x.y * p[nt].x : fmaf(x.y, p[nt].x, o[1]));
+          o[2] = fmaf(x.z, p[nt].x, FIRST ? -x.w * p[nt].y : fmaf(-x.w, p[nt].y, o[2]));
+          o[3] = fmaf(x.z, p[nt].y, FIRST ? x.w * p[nt].x : fmaf(x.w, p[nt].x, o[3]));
         });
       });
-    }
+    };
+    add_ap(0, Index<1>{});
+    for (int u = 1; u < l; ++u) add_ap(u, Index<0>{});
     static_for<0, NK>([&](auto i) {
       constexpr int nt = decltype(i)::value;
       if (g == 0) y[nt][0][0] = y[nt][0][1] = 0.f;   // the j = 0 point is not fitted
@@ -204,7 +204,7 @@ void screen_kernel(ScreenArgs a) {
     const float sc = __uint_as_float(unsigned(127 + 14 - e) << 23);
 
     // A operands: chunk 2 kp holds the even channels, 2 kp + 1 the odd ones
-    h8_t ya[NK][2 * KP], yb[NK][2 * KP];
+    h8_t ya[NK][2 * KP];
     static_for<0, NK * 2 * KP>([&](auto i) {
       constexpr int nt = decltype(i)::value / (2 * KP), kc = decltype(i)::value % (2 * KP);
       float re[4], im[4];
@@ -213,20 +213,20 @@ void screen_kernel(ScreenArgs a) {
         re[h] = y[nt][kc / 2][4 * h + 2 * (kc % 2)] * sc;
         im[h] = y[nt][kc / 2][4 * h + 2 * (kc % 2) + 1] * sc;
       });
-      embed(re, im, ya[nt][kc], yb[nt][kc]);
+      ya[nt][kc] = pack(re, im);
     });
 
     float mine = 0.f;   // largest |G|^2 of unit `lane`
     float x2 = 0.f;     // largest sum of |X|^2 over this lane's IFs
     for (int p0 = 0; p0 < units / 2; p0 += UP) {
       // SBD of UP unit pairs -> A operands of the MBD product
-      h8_t xa[2 * UP][NK], xb[2 * UP][NK];
+      h8_t xa[2 * UP][NK];
       static_for<0, UP>([&](auto pi) {
         constexpr int p = decltype(pi)::value;
-        h8_t b[2 * KP];
-        static_for<0, 2 * KP>([&](auto kk) {
-          constexpr int kc = decltype(kk)::value;
-          b[kc] = Fs[((p0 + p) * 2 * KP + kc) * 64 + lane];
+        h8_t b[2 * KP][2];
+        static_for<0, 4 * KP>([&](auto kk) {
+          constexpr int k = decltype(kk)::value;
+          b[k / 2][k % 2] = Fs[((p0 + p) * 4 * KP + k) * 64 + lane];
         });
         float z2[2] = {0.f, 0.f};
         static_for<0, NK>([&](auto i) {
@@ -234,10 +234,10 @@ void screen_kernel(ScreenArgs a) {
           f4_t er = {0.f, 0.f, 0.f, 0.f}, ei = er, dr = er, di = er;
           static_for<0, KP>([&](auto kk) {
             constexpr int k = 2 * decltype(kk)::value;
-            er = __builtin_amdgcn_mfma_f32_16x16x32_f16(ya[nt][k], b[k], er, 0, 0, 0);
-            ei = __builtin_amdgcn_mfma_f32_16x16x32_f16(yb[nt][k], b[k], ei, 0, 0, 0);
-            dr = __builtin_amdgcn_mfma_f32_16x16x32_f16(ya[nt][k + 1], b[k + 1], dr, 0, 0, 0);
-            di = __builtin_amdgcn_mfma_f32_16x16x32_f16(yb[nt][k + 1], b[k + 1], di, 0, 0, 0);
+            er = __builtin_amdgcn_mfma_f32_16x16x32_f16(ya[nt][k], b[k][0], er, 0, 0, 0);
+            ei = __builtin_amdgcn_mfma_f32_16x16x32_f16(ya[nt][k], b[k][1], ei, 0, 0, 0);
+            dr = __builtin_amdgcn_mfma_f32_16x16x32_f16(ya[nt][k + 1], b[k + 1][0], dr, 0, 0, 0);
+            di = __builtin_amdgcn_mfma_f32_16x16x32_f16(ya[nt][k + 1], b[k + 1][1], di, 0, 0, 0);
           });
           float re[2][4], im[2][4];
           static_for<0, 4>([&](auto q) {
@@ -249,51 +249,74 @@ void screen_kernel(ScreenArgs a) {
           });
           static_for<0, 2>([&](auto hh) {
             constexpr int h = decltype(hh)::value;
-            embed(re[h], im[h], xa[2 * p + h][nt], xb[2 * p + h][nt]);
-            const u4_t w = __builtin_bit_cast(u4_t, xa[2 * p + h][nt]);
+            xa[2 * p + h][nt] = pack(re[h], im[h]);
             static_for<0, 4>([&](auto q) {
-              const h2_t c = __builtin_bit_cast(h2_t, w[decltype(q)::value]);
-              z2[h] = __builtin_amdgcn_fdot2(c, c, z2[h], false);
+              constexpr int k = decltype(q)::value;
+              z2[h] = fmaf(re[h][k], re[h][k], fmaf(im[h][k], im[h][k], z2[h]));
             });
           });
         });
         x2 = fmaxf(x2, fmaxf(z2[0], z2[1]));
       });
-      // MBD of the units, 16 columns at a time
+      // MBD of the units, 16 columns at a time: the products of a step (one
+      // unit, 16 columns) are issued among the powers of the step before
       float mx[2 * UP];
       static_for<0, 2 * UP>([&](auto ui) { mx[decltype(ui)::value] = 0.f; });
-#pragma unroll 2
-      for (int ct = 0; ct < MT; ++ct) {
-        h8_t b[NK];
-        static_for<0, NK>([&](auto i) { b[decltype(i)::value] = Fm[(ct * NK + decltype(i)::value) * 64 + lane]; });
-        static_for<0, 2 * UP>([&](auto ui) {
-          constexpr int u = decltype(ui)::value;
-          const f4_t zero = {0.f, 0.f, 0.f, 0.f};
-          f4_t gr = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[u][0], b[0], zero, 0, 0, 0);
-          f4_t gi = __builtin_amdgcn_mfma_f32_16x16x32_f16(xb[u][0], b[0], zero, 0, 0, 0);
-          float v[4];
+      f4_t acc[2][4];   // HALF: re, im of a, re, im of b; else re, im
+      auto product = [&](auto ui, const h8_t (&b)[NK][2], f4_t (&o)[4]) {
+        constexpr int u = decltype(ui)::value;
+        const f4_t zero = {0.f, 0.f, 0.f, 0.f};
+        o[0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[u][0], b[0][0], zero, 0, 0, 0);
+        o[1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[u][0], b[0][1], zero, 0, 0, 0);
+        if constexpr (HALF) {
+          o[2] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[u][1], b[1][0], zero, 0, 0, 0);
+          o[3] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[u][1], b[1][1], zero, 0, 0, 0);
+        } else {
+          static_for<1, NK>([&](auto i) {
+            constexpr int nt = decltype(i)::value;
+            o[0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[u][nt], b[nt][0], o[0], 0, 0, 0);
+            o[1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[u][nt], b[nt][1], o[1], 0, 0, 0);
+          });
+        }
+      };
+      auto powers = [&](const f4_t (&o)[4], float &m) {
+        float v[4];
+        static_for<0, 4>([&](auto q) {
+          constexpr int k = decltype(q)::value;
+          v[k] = fmaf(o[1][k], o[1][k], o[0][k] * o[0][k]);
           if constexpr (HALF) {
-            const f4_t hr = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[u][1], b[1], zero, 0, 0, 0);
-            const f4_t hi_ = __builtin_amdgcn_mfma_f32_16x16x32_f16(xb[u][1], b[1], zero, 0, 0, 0);
-            static_for<0, 4>([&](auto q) {
-              constexpr int k = decltype(q)::value;
-              const float t = fmaf(hi_[k], hi_[k], fmaf(hr[k], hr[k], fmaf(gi[k], gi[k], gr[k] * gr[k])));
-              const float d = fmaf(gi[k], hi_[k], gr[k] * hr[k]);
-              v[k] = fmaf(2.f, fabsf(d), t);
-            });
-          } else {
-            static_for<1, NK>([&](auto i) {
-              constexpr int nt = decltype(i)::value;
-              gr = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[u][nt], b[nt], gr, 0, 0, 0);
-              gi = __builtin_amdgcn_mfma_f32_16x16x32_f16(xb[u][nt], b[nt], gi, 0, 0, 0);
-            });
-            static_for<0, 4>([&](auto q) {
-              constexpr int k = decltype(q)::value;
-              v[k] = fmaf(gr[k], gr[k], gi[k] * gi[k]);
-            });
+            v[k] = fmaf(o[3][k], o[3][k], fmaf(o[2][k], o[2][k], v[k]));
+            v[k] = fmaf(2.f, fabsf(fmaf(o[1][k], o[3][k], o[0][k] * o[2][k])), v[k]);
           }
-          mx[u] = fmaxf(fmaxf(mx[u], v[0]), v[1]);
-          mx[u] = fmaxf(fmaxf(mx[u], v[2]), v[3]);
+        });
+        m = fmaxf(fmaxf(m, v[0]), v[1]);
+        m = fmaxf(fmaxf(m, v[2]), v[3]);
+      };
+      h8_t b[NK][2], bn[NK][2];
+      auto operand = [&](int ct, h8_t (&o)[NK][2]) {
+        static_for<0, 2 * NK>([&](auto i) {
+          constexpr int k = decltype(i)::value;
+          o[k / 2][k % 2] = Fm[(ct * 2 * NK + k) * 64 + lane];
+        });
+      };
+      operand(0, b);
+      product(Index<0>{}, b, acc[0]);
+#pragma unroll 1
+      for (int ct = 0; ct < MT; ++ct) {
+        const int cn = ct + 1 < MT ? ct + 1 : 0;
+        operand(cn, bn);
+        static_for<0, 2 * UP>([&](auto ui) {
+          constexpr int u = decltype(ui)::value, un = (u + 1) % (2 * UP);
+          product(Index<un>{}, un == 0 ? bn : b, acc[(u + 1) & 1]);
+          powers(acc[u & 1], mx[u]);
+          static_for<0, (HALF ? 4 : 2 * NK)>([&](auto) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                            // one MFMA,
+            __builtin_amdgcn_sched_group_barrier(0x002, HALF ? 8 : NK == 2 ? 3 : 5, 0);   // its share of the powers
+          });
+        });
+        static_for<0, 2 * NK>([&](auto i) {
+          constexpr int k = decltype(i)::value;
+          b[k / 2][k % 2] = bn[k / 2][k % 2];
         });
       }
       // pair p is units sb and sb + NH of sub-grid c
@@ -326,7 +349,7 @@ void screen_kernel(ScreenArgs a) {
 constexpr size_t kScreenLdsMax = 150 * 1024;
 
 size_t screen_lds(int n_chan, int n_if, bool half, int units) {
-  return size_t((half ? 8 : 16) * (n_if <= 16 ? 1 : 2) + units * (n_chan / 32)) * 64 * sizeof(h8_t);
+  return size_t((half ? 8 : 16) * (n_if <= 16 ? 1 : 2) + units * (n_chan / 32)) * 2 * 64 * sizeof(h8_t);
 }
 
 // f(kernel) for the instantiation of a shape
