@@ -438,8 +438,7 @@ struct Candidates {
       const unsigned v = q[8 + u];
       if (v == 0) continue;
       const bool known = ab.y < __builtin_inff();
-      const float most = ab.x - float(v - 1) * ab.y * (1.0f / 127.0f) + ab.y;
-      if (!known || most >= amp * 0.99999f) atomicOr(&cand[r * P + u / per_c], 1u << (u % per_c));
+      if (!known || ab.x - float(v - 1) * ab.y >= amp * 0.99999f) atomicOr(&cand[r * P + u / per_c], 1u << (u % per_c));
     }
   }
 };

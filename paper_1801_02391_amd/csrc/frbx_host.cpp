@@ -27,6 +27,8 @@ using frbx::DevCrossing;
 namespace {
 
 constexpr double kTwoPi = 6.283185307179586476925286766559;
+// largest bound factor of a coarse screening grid (screen_grid)
+constexpr double kScreenGammaMax = 1.02;
 constexpr double kDefaultKdm = 4.149e6;  // ms MHz^2 per pc cm^-3
 
 bool pow2(int v) { return v > 0 && (v & (v - 1)) == 0; }
@@ -85,6 +87,8 @@ struct frbx_ctx {
   int scr_blocks = 0;            // screened search: work-groups of the screening pass (0: not screened),
   bool scr_half = false;         // its form, operand rows and the errors of its rounded matrices
   int32_t scr_row_if[32];
+  int scr_tiles = 16;            // its MBD grid
+  double scr_gamma = 1.0;
   double scr_err_s = 0, scr_err_m = 0;
   std::vector<int> rate_off;
   int dd_group = 1;          // DM trials per staged dedispersion tile
@@ -402,15 +406,39 @@ bool screen_half(const frbx_ctx *c) {
 // the screened search is the slower one (20 s of the paper's set-up: 1.82
 // against 1.59 ms).  The float16 form's own products are the screening
 // pass's but for the halved MBD product, so it is screened only where that
-// applies (one baseline, 16 IFs or fewer: 3.38 against 3.11 ms).
-bool use_screen(const frbx_ctx *c) {
-  if (use_gemm(c) || !frbx::screen_supported(c->J, c->n_mbd, c->N, c->sbd_pad)) return false;
+// applies, up to 64 channels (one baseline, 16 IFs or fewer: 3.38 against
+// 3.11 ms; with 128 channels the pass takes longer than the form itself).
+bool use_screen(const frbx_ctx *c, int tiles) {
+  const bool half = screen_half(c);
+  if (use_gemm(c) || !frbx::screen_supported(c->J, c->n_mbd, c->N, half, tiles, c->sbd_pad)) return false;
   if (c->n_rate * c->sbd_pad * c->J / 16 < 16) return false;
-  if (c->precision == FRBX_PREC_F16 && !screen_half(c)) return false;
+  if (c->precision == FRBX_PREC_F16 && !(half && c->J <= 64)) return false;
   const size_t lds = c->precision == FRBX_PREC_F32
                          ? frbx::fringe_lds_bytes(c->J, c->n_mbd, c->N, c->sbd_pad)
                          : frbx::fringe_mfma_lds_bytes(c->J, c->N, c->sbd_pad, c->precision == FRBX_PREC_F16X3 ? 3 : 1);
   return lds + size_t(c->n_rate) * c->sbd_pad * 4 <= 150 * 1024;
+}
+
+// The MBD grid of the screening pass.  On a compact lattice the IFs' positions
+// span L after a common shift, so for a fixed SBD bin G is a trigonometric
+// polynomial of degree L / 2 over the MBD axis (up to a phase); the largest
+// |G| over all delays is taken within half a step of a bin of any grid of
+// Mc bins and there falls by at most cos(pi L / (2 Mc)) (M. Riesz): the
+// pass needs only the coarsest grid whose bound costs few candidates.
+struct ScreenGrid {
+  int tiles = 16;
+  double gamma = 1.0;
+};
+
+ScreenGrid screen_grid(const frbx_ctx *c) {
+  ScreenGrid G;
+  if (c->mbd_pos.empty() || c->n_mbd != 256 || c->N > 16) return G;
+  const int L = *std::max_element(c->mbd_pos.begin(), c->mbd_pos.end());
+  for (int tiles = 1; tiles < 16; tiles *= 2) {
+    const double gamma = 1.0 / std::cos(0.5 * kTwoPi * L / (2.0 * 16 * tiles));
+    if (L < 16 * tiles && gamma > 0 && gamma <= kScreenGammaMax) return ScreenGrid{tiles, gamma * (1 + 1e-6)};
+  }
+  return G;
 }
 
 // The matrix-core fringe launch of the current precision (both transforms
@@ -432,11 +460,10 @@ hipError_t launch_matrix_core(const frbx_ctx *c, frbx::FringeArgs &fa, int grid)
 // element e; for the real part cos for e < 4 and sin for e >= 4 of the phase,
 // for the imaginary part -sin and cos), and what rounding them to float16
 // costs.
-//   SBD: unit pair p = sub-grid c = p / (J / 32), bins s' = c + P a with
-//   a = 16 (p % (J / 32)) + column < J / 2 (the pair's second unit is
-//   a + J / 2); chunk 2 kp + par, element e is channel 32 kp + 8 (e % 4) +
-//   2 g + par; phase 2 pi j s' / (P J).
-//   MBD: tile t, bins m = 16 t + column; chunk nt, element e is operand row
+//   SBD: sub-grid c, bins s0 = c + P column; residue p < RX = J / 16, element
+//   e is channel j = RX (4 (e % 4) + g) + p; phase 2 pi j s0 / (P J).
+//   MBD: tile t, bins m = (16 t + column) M / (16 tiles) (of the first half
+//   of the axis with 16 bins a tile for half); chunk nt, element e is operand row
 //   16 nt + 4 g + e % 4, its IF row_if (zero for absent rows); phase
 //   2 pi q_n m / M.  With more than 16 IFs of which at most 16 have an even
 //   and at most 16 an odd lattice position, rows 0-15 take the even ones,
@@ -448,9 +475,9 @@ struct ScreenTables {
   double err_s = 0, err_m = 0;   // largest rms of a column's rounding error over a lane group's channels / over the rows
 };
 
-ScreenTables screen_tables(const frbx_ctx *c) {
+ScreenTables screen_tables(const frbx_ctx *c, int grid_tiles) {
   ScreenTables T;
-  const int N = c->N, J = c->J, P = c->sbd_pad, PJ = P * J, KC = J / 16, KP = J / 32, pairs = PJ / 32, M = c->n_mbd;
+  const int N = c->N, J = c->J, P = c->sbd_pad, PJ = P * J, RX = J / 16, M = c->n_mbd;
   const int NK = N <= 16 ? 1 : 2;
   T.half = screen_half(c);
   std::fill(T.row_if, T.row_if + 32, -1);
@@ -458,8 +485,8 @@ ScreenTables screen_tables(const frbx_ctx *c) {
     if (T.half) T.row_if[next[c->q_if[n] & 1]++] = n;
     else T.row_if[k++] = n;
   }
-  const int tiles = T.half ? M / 32 : M / 16;
-  T.fs.assign(size_t(pairs) * KC * 2 * 64 * 8, _Float16(0));
+  const int tiles = T.half ? M / 32 : grid_tiles, step = T.half ? 1 : M / (16 * grid_tiles);
+  T.fs.assign(size_t(P) * RX * 2 * 64 * 8, _Float16(0));
   T.fm.assign(size_t(tiles) * NK * 2 * 64 * 8, _Float16(0));
   // cos, sin of 2 pi k / n as float16 and their squared rounding errors
   struct Root {
@@ -484,17 +511,16 @@ ScreenTables screen_tables(const frbx_ctx *c) {
     im[e] = e < 4 ? -w.sn : w.cs;
     return e < 4 ? w.e_cs : w.e_sn;
   };
-  for (int p = 0; p < pairs; ++p)
+  for (int cc = 0; cc < P; ++cc)
     for (int ln = 0; ln < 64; ++ln) {
       double e2 = 0;
-      for (int kc = 0; kc < KC; ++kc)
+      for (int p = 0; p < RX; ++p)
         for (int e = 0; e < 8; ++e) {
-          const int j = 32 * (kc / 2) + 8 * (e % 4) + 2 * (ln / 16) + kc % 2;
-          const int sp = p / KP + P * (16 * (p % KP) + ln % 16);
-          _Float16 *re = &T.fs[((size_t(p) * KC + kc) * 2 * 64 + ln) * 8];
-          e2 += put(re, re + 64 * 8, e, ws[(j * sp) % PJ]);
+          const int j = RX * (4 * (e % 4) + ln / 16) + p, s0 = cc + P * (ln % 16);
+          _Float16 *re = &T.fs[((size_t(cc) * RX + p) * 2 * 64 + ln) * 8];
+          e2 += put(re, re + 64 * 8, e, ws[(j * s0) % PJ]);
         }
-      T.err_s = std::max(T.err_s, std::sqrt(e2 / (4 * KC)));
+      T.err_s = std::max(T.err_s, std::sqrt(e2 / (4 * RX)));
     }
   for (int t = 0; t < tiles; ++t)
     for (int col = 0; col < 16; ++col) {
@@ -504,7 +530,7 @@ ScreenTables screen_tables(const frbx_ctx *c) {
           for (int e = 0; e < 8; ++e) {
             const int n = T.row_if[16 * nt + 4 * g + e % 4];
             _Float16 *re = &T.fm[((size_t(t) * NK + nt) * 2 * 64 + 16 * g + col) * 8];
-            if (n >= 0) e2 += put(re, re + 64 * 8, e, wm[(c->q_if[n] * (16 * t + col)) % M]);
+            if (n >= 0) e2 += put(re, re + 64 * 8, e, wm[(c->q_if[n] * (16 * t + col) * step) % M]);
           }
       T.err_m = std::max(T.err_m, std::sqrt(e2 / N));
     }
@@ -727,14 +753,18 @@ frbx_status prepare(frbx_ctx *c) {
     }
   }
   c->scr_blocks = 0;
-  if (use_screen(c)) {
-    const ScreenTables T = screen_tables(c);
+  const ScreenGrid SG = screen_grid(c);
+  if (use_screen(c, SG.tiles)) {
+    const ScreenTables T = screen_tables(c, SG.tiles);
     std::copy(T.row_if, T.row_if + 32, c->scr_row_if);
     c->scr_half = T.half;
+    c->scr_tiles = SG.tiles;
+    c->scr_gamma = SG.gamma;
     c->scr_err_s = T.err_s;
     c->scr_err_m = T.err_m;
     if ((s = up(c->d_scr_sbd, T.fs)) != FRBX_OK || (s = up(c->d_scr_mbd, T.fm)) != FRBX_OK) return s;
-    if ((s = c->hip(frbx::screen_blocks(J, N, T.half, c->sbd_pad, c->device, &c->scr_blocks), "screening pass")) != FRBX_OK)
+    if ((s = c->hip(frbx::screen_blocks(J, N, T.half, SG.tiles, c->sbd_pad, c->device, &c->scr_blocks),
+                    "screening pass")) != FRBX_OK)
       return s;
   }
   // Float32 general form: the fringe kernel compiled for the rows of the
@@ -1435,6 +1465,8 @@ frbx_status search_tiles(frbx_ctx *c, const PassSpec &ps, float2 *wbuf, int dt, 
           sa.n_task = int(int64_t(ndt) * S * c->n_rate);
           sa.rate_ph = c->d_rate;
           sa.half = c->scr_half ? 1 : 0;
+          sa.tiles = c->scr_tiles;
+          sa.gamma = float(c->scr_gamma);
           std::copy(c->scr_row_if, c->scr_row_if + 32, sa.row_if);
           sa.f_sbd = c->d_scr_sbd;
           sa.f_mbd = c->d_scr_mbd;

@@ -124,11 +124,11 @@ struct FringeArgs {
 // difference between the two.
 constexpr int kScreenWaves = 8;          // waves per work-group
 constexpr int kScreenUnitsMax = 64;
-// One record per (segment, rate): float largest screened |G| A, float bound
-// B on |screened |G| - the search's |G||, then one byte per unit: 0 where
-// the unit's screened maximum is below A - 2 B, else v >= 1 with that
-// maximum at most A - (v - 1) B / 127.  B = +inf: nothing is known (not
-// finite, zero or extreme input) and every unit is a candidate.
+// One record per (segment, rate): float T and float step, then one byte per
+// unit: 0 where the unit cannot hold the segment's largest |G|, else v >= 1
+// with its |G| at most T - (v - 1) step, 1 for the largest screened unit.
+// step = +inf: nothing is known (not finite, zero or extreme input) and
+// every unit is a candidate.
 constexpr int screen_rec_bytes(int units) { return 8 + ((units + 7) & ~7); }
 
 struct ScreenArgs {
@@ -147,9 +147,12 @@ struct ScreenArgs {
   const float2 *rate_ph;
   int32_t half;              // MBD columns m and m + M/2 from one product (n_if > 16): rows 0-15 are
                              // IFs of even lattice position, rows 16-31 of odd position
+  int32_t tiles;             // tiles of 16 MBD bins: 16, fewer for a coarse grid of a compact lattice
+                             // (half: 8)
+  float gamma;               // |G| on the full MBD grid <= gamma x largest |G| on the screened one
   int32_t row_if[32];        // IF of each operand row, -1: none
-  const void *f_sbd;         // [units / 2][J/16][re, im][64 lanes] x 8 halves
-  const void *f_mbd;         // [tiles of 16 MBD bins][n_if <= 16 ? 1 : 2][re, im][64 lanes] x 8 halves
+  const void *f_sbd;         // [P][J / 16][re, im][64 lanes] x 8 halves
+  const void *f_mbd;         // [tiles][n_if <= 16 ? 1 : 2][re, im][64 lanes] x 8 halves
   float eps_y;               // error bound per unit of sum |y|,
   float eps_x;               // of sqrt(N) times the largest 2-norm of X over the IFs,
   float abs_scaled;          // and absolute: in the units of the scaled operands,
@@ -192,8 +195,8 @@ hipError_t launch_stats(const StatsArgs &a, int rows, hipStream_t s);
 // Screening pass: whether the shape has one, the work-groups that fill the
 // device (persistent over the tasks; `device` current), and its launch with
 // that many.
-bool screen_supported(int n_chan, int n_mbd, int n_if, int sbd_pad);
-hipError_t screen_blocks(int n_chan, int n_if, bool half, int sbd_pad, int device, int *blocks);
+bool screen_supported(int n_chan, int n_mbd, int n_if, bool half, int tiles, int sbd_pad);
+hipError_t screen_blocks(int n_chan, int n_if, bool half, int tiles, int sbd_pad, int device, int *blocks);
 hipError_t launch_screen(int n_chan, const ScreenArgs &a, int blocks, hipStream_t s);
 
 // matrix-core fringe kernel: n_pass = 1 (float16) or 3 (float16 high/low

@@ -1216,7 +1216,7 @@ struct LaunchFn {
   hipStream_t s;
   template <int J, int M> hipError_t operator()() {
     if (a.screened) {
-      if constexpr (M == 256 && (J == 32 || J == 64))
+      if constexpr (M == 256 && J >= 16)
         return a.mbd_pos ? launch_fringe_t<J, M, false, true, false, true>(a, lds, grid, s)
                          : launch_fringe_t<J, M, false, false, false, true>(a, lds, grid, s);
       return hipErrorInvalidValue;
@@ -1316,10 +1316,7 @@ static hipError_t launch_mfma_t(const FringeArgs &a, size_t lds, int grid, hipSt
     return hipGetLastError();
   };
   if (a.dump) return go(&fringe_mfma_kernel<J, NK, NP, true>);
-  if (a.screened) {
-    if constexpr (J == 32 || J == 64) return go(&fringe_mfma_kernel<J, NK, NP, false, true>);
-    return hipErrorInvalidValue;
-  }
+  if (a.screened) return go(&fringe_mfma_kernel<J, NK, NP, false, true>);
   return go(&fringe_mfma_kernel<J, NK, NP, false>);
 }
 

@@ -65,28 +65,33 @@ __device__ __forceinline__ float wave_max(float v) {
   return __uint_as_float(unsigned(__builtin_amdgcn_readlane(int(m), 63)));
 }
 
+// SBD: with j = RX i + p (RX = J / 16 residues p of 16 channels i each) and
+// the bins s' = s0 + 16 P k of one sub-grid (s0 = c + P column, k < RX),
+// X(s') = sum_p w_RX^(p k) E_p(s0), E_p = sum_i y[RX i + p] w_PJ^(j s0): one
+// product of K = (16 i, re/im) per residue and an RX-point DFT in registers
+// give all RX units of the sub-grid.
 // HALF: the MBD product on half of its columns.  Rows n hold the IFs of even
 // lattice position in chunk 0 and of odd position in chunk 1; with a and b
 // their sums for bin m < M / 2, G(m) = a + b and G(m + M/2) = a - b, and only
 // the larger counts: max |a +- b|^2 = |a|^2 + |b|^2 + 2 |Re a conj(b)|.
-// The SBD product does the same over even and odd channels: with e and o
-// their sums for bin s' < PJ / 2, X(s') = e + o, X(s' + PJ/2) = e - o.
+// Otherwise the columns may be a coarser grid of the MBD axis (a.tiles x 16
+// bins), whose largest |G| bounds the full grid's (a.gamma).
 template <int J, int NK, bool HALF>
 __global__ __launch_bounds__(kScreenBlock) __attribute__((amdgpu_waves_per_eu(2)))
 void screen_kernel(ScreenArgs a) {
-  constexpr int KP = J / 32;               // pairs of SBD K chunks (16 even + 16 odd channels)
-  constexpr int NSB = J / 16, NH = NSB / 2;
-  constexpr int MT = HALF ? 8 : 16;        // MBD column tiles
-  constexpr int UP = 2;                    // unit pairs per pass over the MBD matrix
+  constexpr int RX = J / 16;
+  constexpr int CG = RX >= 4 ? 1 : 4 / RX;   // sub-grids per pass over the MBD matrix
+  constexpr int U = CG * RX;                 // units per pass
   extern __shared__ h8_t lds_h[];
-  h8_t *const Fm = lds_h;                      // [MT][NK][re, im][64]
-  h8_t *const Fs = lds_h + MT * NK * 2 * 64;   // [units / 2][2 KP][re, im][64]
-  __shared__ int next;                         // tasks taken by the work-group
   const int N = a.n_if, R = a.n_rate, NJ = N * J, units = a.units;
+  const int MT = HALF ? 8 : a.tiles;
+  h8_t *const Fm = lds_h;                      // [MT][NK][re, im][64]
+  h8_t *const Fs = lds_h + MT * NK * 2 * 64;   // [P][RX][re, im][64]
+  __shared__ int next;                         // tasks taken by the work-group
   {
     const h8_t *gm = static_cast<const h8_t *>(a.f_mbd), *gs = static_cast<const h8_t *>(a.f_sbd);
     for (int i = threadIdx.x; i < MT * NK * 2 * 64; i += kScreenBlock) Fm[i] = gm[i];
-    for (int i = threadIdx.x; i < units * KP * 2 * 64; i += kScreenBlock) Fs[i] = gs[i];
+    for (int i = threadIdx.x; i < units * 2 * 64; i += kScreenBlock) Fs[i] = gs[i];
     if (threadIdx.x == 0) next = 0;
   }
   __syncthreads();
@@ -123,39 +128,49 @@ void screen_kernel(ScreenArgs a) {
     const float2 *ph = a.rate_ph + a.rate_off[wi] + int64_t(r) * N * l;
 
     // ---- segment sums (Eq. 3 with the Eq. 4 rotation): lane (row, g) holds
-    // row 16 nt + row, channels 32 kp + 8 h + 2 g + {0, 1}, h < 4:
-    // y[nt][kp][4 h + {0, 1}] even, {2, 3} odd channel
-    float y[NK][KP][16];
+    // row 16 nt + row, channels RX (4 h + g) + p, h < 4: y[nt][p][2 h + re/im]
+    float y[NK][RX][8];
     int off[NK], pho[NK];
     static_for<0, NK>([&](auto i) {
       constexpr int nt = decltype(i)::value;
       const int n = max(rif[nt], 0);
-      off[nt] = n * J + 2 * g;
+      off[nt] = n * J + RX * g;
       pho[nt] = n * l;
     });
+    // one AP: loads of two channels at a time (one with RX = 1), at most 16 in flight
     auto add_ap = [&](int u, auto first_tag) {
       constexpr bool FIRST = decltype(first_tag)::value != 0;
+      constexpr int PP = RX > 1 ? RX / 2 : 1;             // loads per (row, h)
+      constexpr int NL = NK * 4 * PP, NB = NL < 16 ? NL : 16;
       const float2 *src = wd + int64_t(u) * NJ;
-      float4 v[NK][KP][4];
       float2 p[NK];
-      static_for<0, NK>([&](auto i) {
-        constexpr int nt = decltype(i)::value;
-        p[nt] = ph[pho[nt] + u];
-        static_for<0, KP * 4>([&](auto kk) {
-          constexpr int k = decltype(kk)::value;
-          v[nt][k / 4][k % 4] = *reinterpret_cast<const float4 *>(src + off[nt] + 8 * k);
+      static_for<0, NK>([&](auto i) { p[decltype(i)::value] = ph[pho[decltype(i)::value] + u]; });
+      static_for<0, NL / NB>([&](auto bi) {
+        float4 v[NB];
+        static_for<0, NB>([&](auto kk) {
+          constexpr int q = decltype(bi)::value * NB + decltype(kk)::value;
+          constexpr int nt = q / (4 * PP), h = (q / PP) % 4, pp = q % PP;
+          const float2 *at2 = src + off[nt] + 4 * RX * h + 2 * pp;
+          if constexpr (RX > 1) {
+            v[decltype(kk)::value] = *reinterpret_cast<const float4 *>(at2);
+          } else {
+            const float2 z = *at2;
+            v[decltype(kk)::value] = make_float4(z.x, z.y, 0.f, 0.f);
+          }
         });
-      });
-      static_for<0, NK>([&](auto i) {
-        constexpr int nt = decltype(i)::value;
-        static_for<0, KP * 4>([&](auto kk) {
-          constexpr int k = decltype(kk)::value;
-          const float4 x = v[nt][k / 4][k % 4];
-          float *o = &y[nt][k / 4][4 * (k % 4)];
+        if constexpr (NL > NB) __builtin_amdgcn_sched_barrier(0);
+        static_for<0, NB>([&](auto kk) {
+          constexpr int q = decltype(bi)::value * NB + decltype(kk)::value;
+          constexpr int nt = q / (4 * PP), h = (q / PP) % 4, pp = q % PP;
+          const float4 x = v[decltype(kk)::value];
+          float *o = &y[nt][2 * pp < RX ? 2 * pp : 0][2 * h];
           o[0] = fmaf(x.x, p[nt].x, FIRST ? -x.y * p[nt].y : fmaf(-x.y, p[nt].y, o[0]));
           o[1] = fmaf(x.x, p[nt].y, FIRST ? x.y * p[nt].x : fmaf(x.y, p[nt].x, o[1]));
-          o[2] = fmaf(x.z, p[nt].x, FIRST ? -x.w * p[nt].y : fmaf(-x.w, p[nt].y, o[2]));
-          o[3] = fmaf(x.z, p[nt].y, FIRST ? x.w * p[nt].x : fmaf(x.w, p[nt].x, o[3]));
+          if constexpr (RX > 1) {
+            float *o2 = &y[nt][2 * pp + 1 < RX ? 2 * pp + 1 : 0][2 * h];
+            o2[0] = fmaf(x.z, p[nt].x, FIRST ? -x.w * p[nt].y : fmaf(-x.w, p[nt].y, o2[0]));
+            o2[1] = fmaf(x.z, p[nt].y, FIRST ? x.w * p[nt].x : fmaf(x.w, p[nt].x, o2[1]));
+          }
         });
       });
     };
@@ -165,24 +180,24 @@ void screen_kernel(ScreenArgs a) {
       constexpr int nt = decltype(i)::value;
       if (g == 0) y[nt][0][0] = y[nt][0][1] = 0.f;   // the j = 0 point is not fitted
       if (rif[nt] < 0) {
-        static_for<0, KP * 16>([&](auto kk) {
-          constexpr int k = decltype(kk)::value;
-          y[nt][k / 16][k % 16] = 0.f;
+        static_for<0, RX * 8>([&](auto kk) {
+          constexpr int q = decltype(kk)::value;
+          y[nt][q / 8][q % 8] = 0.f;
         });
       }
     });
     // bounds from above: row_max on sum_j |y[n][j]| (so on |X[n]|) of every
-    // IF, s1 on sum |y|, by Cauchy-Schwarz over each lane's 8 KP values; a
+    // IF, s1 on sum |y|, by Cauchy-Schwarz over each lane's 4 RX values; a
     // NaN or infinite component leaves s1 not finite
     float s1 = 0.f, row_max = 0.f;
     static_for<0, NK>([&](auto i) {
       constexpr int nt = decltype(i)::value;
       float e2 = 0.f;
-      static_for<0, KP * 16>([&](auto kk) {
-        constexpr int k = decltype(kk)::value;
-        e2 = fmaf(y[nt][k / 16][k % 16], y[nt][k / 16][k % 16], e2);
+      static_for<0, RX * 8>([&](auto kk) {
+        constexpr int q = decltype(kk)::value;
+        e2 = fmaf(y[nt][q / 8][q % 8], y[nt][q / 8][q % 8], e2);
       });
-      float t = sqrtf(e2 * float(8 * KP));
+      float t = sqrtf(e2 * float(4 * RX));
       t += __shfl_xor(t, 16, 64);
       t += __shfl_xor(t, 32, 64);
       row_max = fmaxf(row_max, t);
@@ -203,65 +218,78 @@ void screen_kernel(ScreenArgs a) {
     const int e = int(__float_as_uint(row_max * 1.0001f) >> 23) - 127;
     const float sc = __uint_as_float(unsigned(127 + 14 - e) << 23);
 
-    // A operands: chunk 2 kp holds the even channels, 2 kp + 1 the odd ones
-    h8_t ya[NK][2 * KP];
-    static_for<0, NK * 2 * KP>([&](auto i) {
-      constexpr int nt = decltype(i)::value / (2 * KP), kc = decltype(i)::value % (2 * KP);
+    // A operands, one chunk per residue
+    h8_t ya[NK][RX];
+    static_for<0, NK * RX>([&](auto i) {
+      constexpr int nt = decltype(i)::value / RX, p = decltype(i)::value % RX;
       float re[4], im[4];
       static_for<0, 4>([&](auto q) {
         constexpr int h = decltype(q)::value;
-        re[h] = y[nt][kc / 2][4 * h + 2 * (kc % 2)] * sc;
-        im[h] = y[nt][kc / 2][4 * h + 2 * (kc % 2) + 1] * sc;
+        re[h] = y[nt][p][2 * h] * sc;
+        im[h] = y[nt][p][2 * h + 1] * sc;
       });
-      ya[nt][kc] = pack(re, im);
+      ya[nt][p] = pack(re, im);
     });
 
     float mine = 0.f;   // largest |G|^2 of unit `lane`
     float x2 = 0.f;     // largest sum of |X|^2 over this lane's IFs
-    for (int p0 = 0; p0 < units / 2; p0 += UP) {
-      // SBD of UP unit pairs -> A operands of the MBD product
-      h8_t xa[2 * UP][NK];
-      static_for<0, UP>([&](auto pi) {
-        constexpr int p = decltype(pi)::value;
-        h8_t b[2 * KP][2];
-        static_for<0, 4 * KP>([&](auto kk) {
-          constexpr int k = decltype(kk)::value;
-          b[k / 2][k % 2] = Fs[((p0 + p) * 4 * KP + k) * 64 + lane];
-        });
-        float z2[2] = {0.f, 0.f};
+    h8_t b[NK][2], bn[NK][2];   // MBD operands of a tile (tile 0 here and after every pass) and the next
+    auto operand = [&](int ct, h8_t (&o)[NK][2]) {
+      static_for<0, 2 * NK>([&](auto i) {
+        constexpr int q = decltype(i)::value;
+        o[q / 2][q % 2] = Fm[(ct * 2 * NK + q) * 64 + lane];
+      });
+    };
+    operand(0, b);
+    for (int c0 = 0; c0 * RX < units; c0 += CG) {
+      // SBD of CG sub-grids -> A operands of the MBD product
+      h8_t xa[U][NK];
+      static_for<0, CG>([&](auto ci) {
+        constexpr int cc = decltype(ci)::value;
+        float z2[RX];
         static_for<0, NK>([&](auto i) {
           constexpr int nt = decltype(i)::value;
-          f4_t er = {0.f, 0.f, 0.f, 0.f}, ei = er, dr = er, di = er;
-          static_for<0, KP>([&](auto kk) {
-            constexpr int k = 2 * decltype(kk)::value;
-            er = __builtin_amdgcn_mfma_f32_16x16x32_f16(ya[nt][k], b[k][0], er, 0, 0, 0);
-            ei = __builtin_amdgcn_mfma_f32_16x16x32_f16(ya[nt][k], b[k][1], ei, 0, 0, 0);
-            dr = __builtin_amdgcn_mfma_f32_16x16x32_f16(ya[nt][k + 1], b[k + 1][0], dr, 0, 0, 0);
-            di = __builtin_amdgcn_mfma_f32_16x16x32_f16(ya[nt][k + 1], b[k + 1][1], di, 0, 0, 0);
+          f4_t er[RX], ei[RX];
+          const h8_t *const fs = Fs + (c0 + cc) * RX * 2 * 64 + lane;
+          h8_t bs[2][2] = {{fs[0], fs[64]}};
+          static_for<0, RX>([&](auto pi) {
+            constexpr int p = decltype(pi)::value;
+            const f4_t zero = {0.f, 0.f, 0.f, 0.f};
+            if constexpr (p + 1 < RX) {
+              bs[(p + 1) & 1][0] = fs[(p + 1) * 128];
+              bs[(p + 1) & 1][1] = fs[(p + 1) * 128 + 64];
+            }
+            er[p] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ya[nt][p], bs[p & 1][0], zero, 0, 0, 0);
+            ei[p] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ya[nt][p], bs[p & 1][1], zero, 0, 0, 0);
+            // (keeps the operands of later residues out of the registers)
+            if constexpr (RX >= 8) __builtin_amdgcn_sched_barrier(0);
           });
-          float re[2][4], im[2][4];
+          // RX-point DFT over the residues, for each of the lane's four IFs
+          float2 x[4][RX];
           static_for<0, 4>([&](auto q) {
-            constexpr int k = decltype(q)::value;
-            re[0][k] = er[k] + dr[k];
-            im[0][k] = ei[k] + di[k];
-            re[1][k] = er[k] - dr[k];
-            im[1][k] = ei[k] - di[k];
+            constexpr int h = decltype(q)::value;
+            static_for<0, RX>([&](auto pi) { x[h][decltype(pi)::value] = make_float2(er[decltype(pi)::value][h], ei[decltype(pi)::value][h]); });
+            dft<RX>(x[h]);
           });
-          static_for<0, 2>([&](auto hh) {
-            constexpr int h = decltype(hh)::value;
-            xa[2 * p + h][nt] = pack(re[h], im[h]);
+          static_for<0, RX>([&](auto ki) {
+            constexpr int kx = decltype(ki)::value;
+            const float re[4] = {x[0][kx].x, x[1][kx].x, x[2][kx].x, x[3][kx].x};
+            const float im[4] = {x[0][kx].y, x[1][kx].y, x[2][kx].y, x[3][kx].y};
+            xa[cc * RX + kx][nt] = pack(re, im);
+            float z = nt == 0 ? 0.f : z2[kx];
             static_for<0, 4>([&](auto q) {
-              constexpr int k = decltype(q)::value;
-              z2[h] = fmaf(re[h][k], re[h][k], fmaf(im[h][k], im[h][k], z2[h]));
+              constexpr int h = decltype(q)::value;
+              z = fmaf(re[h], re[h], fmaf(im[h], im[h], z));
             });
+            z2[kx] = z;
           });
         });
-        x2 = fmaxf(x2, fmaxf(z2[0], z2[1]));
+        static_for<0, RX>([&](auto ki) { x2 = fmaxf(x2, z2[decltype(ki)::value]); });
       });
       // MBD of the units, 16 columns at a time: the products of a step (one
       // unit, 16 columns) are issued among the powers of the step before
-      float mx[2 * UP];
-      static_for<0, 2 * UP>([&](auto ui) { mx[decltype(ui)::value] = 0.f; });
+      float mx[U];
+      static_for<0, U>([&](auto ui) { mx[decltype(ui)::value] = 0.f; });
       f4_t acc[2][4];   // HALF: re, im of a, re, im of b; else re, im
       auto product = [&](auto ui, const h8_t (&b)[NK][2], f4_t (&o)[4]) {
         constexpr int u = decltype(ui)::value;
@@ -282,31 +310,22 @@ void screen_kernel(ScreenArgs a) {
       auto powers = [&](const f4_t (&o)[4], float &m) {
         float v[4];
         static_for<0, 4>([&](auto q) {
-          constexpr int k = decltype(q)::value;
-          v[k] = fmaf(o[1][k], o[1][k], o[0][k] * o[0][k]);
+          constexpr int h = decltype(q)::value;
+          v[h] = fmaf(o[1][h], o[1][h], o[0][h] * o[0][h]);
           if constexpr (HALF) {
-            v[k] = fmaf(o[3][k], o[3][k], fmaf(o[2][k], o[2][k], v[k]));
-            v[k] = fmaf(2.f, fabsf(fmaf(o[1][k], o[3][k], o[0][k] * o[2][k])), v[k]);
+            v[h] = fmaf(o[3][h], o[3][h], fmaf(o[2][h], o[2][h], v[h]));
+            v[h] = fmaf(2.f, fabsf(fmaf(o[1][h], o[3][h], o[0][h] * o[2][h])), v[h]);
           }
         });
         m = fmaxf(fmaxf(m, v[0]), v[1]);
         m = fmaxf(fmaxf(m, v[2]), v[3]);
       };
-      h8_t b[NK][2], bn[NK][2];
-      auto operand = [&](int ct, h8_t (&o)[NK][2]) {
-        static_for<0, 2 * NK>([&](auto i) {
-          constexpr int k = decltype(i)::value;
-          o[k / 2][k % 2] = Fm[(ct * 2 * NK + k) * 64 + lane];
-        });
-      };
-      operand(0, b);
       product(Index<0>{}, b, acc[0]);
 #pragma unroll 1
       for (int ct = 0; ct < MT; ++ct) {
-        const int cn = ct + 1 < MT ? ct + 1 : 0;
-        operand(cn, bn);
-        static_for<0, 2 * UP>([&](auto ui) {
-          constexpr int u = decltype(ui)::value, un = (u + 1) % (2 * UP);
+        operand(ct + 1 < MT ? ct + 1 : 0, bn);
+        static_for<0, U>([&](auto ui) {
+          constexpr int u = decltype(ui)::value, un = (u + 1) % U;
           product(Index<un>{}, un == 0 ? bn : b, acc[(u + 1) & 1]);
           powers(acc[u & 1], mx[u]);
           static_for<0, (HALF ? 4 : 2 * NK)>([&](auto) {
@@ -315,17 +334,14 @@ void screen_kernel(ScreenArgs a) {
           });
         });
         static_for<0, 2 * NK>([&](auto i) {
-          constexpr int k = decltype(i)::value;
-          b[k / 2][k % 2] = bn[k / 2][k % 2];
+          constexpr int q = decltype(i)::value;
+          b[q / 2][q % 2] = bn[q / 2][q % 2];
         });
       }
-      // pair p is units sb and sb + NH of sub-grid c
-      static_for<0, 2 * UP>([&](auto ui) {
+      static_for<0, U>([&](auto ui) {
         constexpr int u = decltype(ui)::value;
-        const int p = p0 + u / 2;
-        const int id = (p / NH) * NSB + p % NH + (u % 2) * NH;
         const float m = wave_max(mx[u]);
-        mine = lane == id ? m : mine;
+        mine = lane == c0 * RX + u ? m : mine;
       });
     }
     // |screened G - G| <= eps_y sum |y| + eps_x sqrt(N) max_s |X(s)|_2 + ...
@@ -336,11 +352,13 @@ void screen_kernel(ScreenArgs a) {
     x2 += __shfl_xor(x2, 16, 64);
     x2 += __shfl_xor(x2, 32, 64);
     const float bound = a.eps_y * s1 * sc + a.eps_x * sqrtf(x2 * float(N)) + a.abs_scaled + a.abs_plain * sc;
-    // the record: A, B and per unit its distance below A in steps of B / 127
+    // the record: a unit with screened maximum u has |G| <= gamma (u + bound);
+    // it counts where that reaches A - bound, below the segment's largest |G|
     const float A = sqrtf(wave_max(mine));
-    if (lane == 0) *reinterpret_cast<float2 *>(rec) = make_float2(A / sc, bound / sc);
+    const float width = A + bound - (A - bound) / a.gamma;
+    if (lane == 0) *reinterpret_cast<float2 *>(rec) = make_float2(a.gamma * (A + bound) / sc, a.gamma * width / (254.f * sc));
     if (lane < units) {
-      const float d = (A - sqrtf(mine)) * (127.f / bound);
+      const float d = (A - sqrtf(mine)) * (254.f / width);
       rec[8 + lane] = d <= 254.f ? (unsigned char)(1 + int(d)) : (unsigned char)0;
     }
   }
@@ -348,32 +366,41 @@ void screen_kernel(ScreenArgs a) {
 
 constexpr size_t kScreenLdsMax = 150 * 1024;
 
-size_t screen_lds(int n_chan, int n_if, bool half, int units) {
-  return size_t((half ? 8 : 16) * (n_if <= 16 ? 1 : 2) + units * (n_chan / 32)) * 2 * 64 * sizeof(h8_t);
+size_t screen_lds(int n_if, bool half, int tiles, int units) {
+  return size_t((half ? 8 : tiles) * (n_if <= 16 ? 1 : 2) + units) * 2 * 64 * sizeof(h8_t);
 }
 
 // f(kernel) for the instantiation of a shape
+template <int J, typename F>
+hipError_t with_kernel_j(int n_if, bool half, F &&f) {
+  if (n_if <= 16) return f(&screen_kernel<J, 1, false>);
+  if constexpr (J <= 128) return half ? f(&screen_kernel<J, 2, true>) : f(&screen_kernel<J, 2, false>);
+  return hipErrorInvalidValue;
+}
+
 template <typename F>
 hipError_t with_kernel(int n_chan, int n_if, bool half, F &&f) {
-  const bool two = n_if > 16;
   switch (n_chan) {
-    case 32: return half ? f(&screen_kernel<32, 2, true>) : two ? f(&screen_kernel<32, 2, false>) : f(&screen_kernel<32, 1, false>);
-    case 64: return half ? f(&screen_kernel<64, 2, true>) : two ? f(&screen_kernel<64, 2, false>) : f(&screen_kernel<64, 1, false>);
+    case 16: return with_kernel_j<16>(n_if, half, f);
+    case 32: return with_kernel_j<32>(n_if, half, f);
+    case 64: return with_kernel_j<64>(n_if, half, f);
+    case 128: return with_kernel_j<128>(n_if, half, f);
+    case 256: return with_kernel_j<256>(n_if, half, f);
     default: return hipErrorInvalidValue;
   }
 }
 
 }  // namespace
 
-bool screen_supported(int n_chan, int n_mbd, int n_if, int sbd_pad) {
-  if (n_mbd != 256 || n_if < 1 || n_if > 32) return false;
-  if (n_chan != 32 && n_chan != 64) return false;
+bool screen_supported(int n_chan, int n_mbd, int n_if, bool half, int tiles, int sbd_pad) {
+  if (n_mbd != 256 || n_if < 1 || n_if > (n_chan == 256 ? 16 : 32)) return false;
+  if (n_chan != 16 && n_chan != 32 && n_chan != 64 && n_chan != 128 && n_chan != 256) return false;
   const int units = sbd_pad * n_chan / 16;
-  return units >= 4 && units <= kScreenUnitsMax && screen_lds(n_chan, n_if, false, units) <= kScreenLdsMax;
+  return units >= 4 && units <= kScreenUnitsMax && screen_lds(n_if, half, tiles, units) <= kScreenLdsMax;
 }
 
-hipError_t screen_blocks(int n_chan, int n_if, bool half, int sbd_pad, int device, int *blocks) {
-  const size_t lds = screen_lds(n_chan, n_if, half, sbd_pad * n_chan / 16);
+hipError_t screen_blocks(int n_chan, int n_if, bool half, int tiles, int sbd_pad, int device, int *blocks) {
+  const size_t lds = screen_lds(n_if, half, tiles, sbd_pad * n_chan / 16);
   (void)hipGetLastError();
   return with_kernel(n_chan, n_if, half, [&](auto kern) -> hipError_t {
     const void *fn = reinterpret_cast<const void *>(kern);
@@ -391,9 +418,10 @@ hipError_t screen_blocks(int n_chan, int n_if, bool half, int sbd_pad, int devic
 hipError_t launch_screen(int n_chan, const ScreenArgs &a, int blocks, hipStream_t s) {
   if (a.n_task <= 0) return hipSuccess;
   if (a.units < 4 || a.units % 4 || a.units > kScreenUnitsMax || a.n_if < 1 || a.n_if > 32 || blocks < 1 || !a.rec ||
-      !a.f_sbd || !a.f_mbd || (a.half && a.n_if <= 16))
+      !a.f_sbd || !a.f_mbd || (a.half && a.n_if <= 16) ||
+      a.tiles < 1 || a.tiles > 16 || !(a.gamma >= 1.f))
     return hipErrorInvalidValue;
-  const size_t lds = screen_lds(n_chan, a.n_if, a.half != 0, a.units);
+  const size_t lds = screen_lds(a.n_if, a.half != 0, a.tiles, a.units);
   if (lds > kScreenLdsMax) return hipErrorInvalidValue;
   const int need = (a.n_task + kScreenWaves - 1) / kScreenWaves;
   (void)hipGetLastError();

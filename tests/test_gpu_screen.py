@@ -5,8 +5,9 @@ must be the reported power and sit at the reported cell.
 
 Shapes at the edges of the pass: one and two blocks of 16 operand rows, IFs
 that split evenly by the parity of their lattice position and ones that do
-not, a single IF (every MBD bin alike), compact and spread lattices, 32 and 64
-channels, the smallest and largest unit counts.  Data at the edges of its
+not, a single IF (every MBD bin alike), compact lattices (coarse MBD grids of
+1 to 8 tiles) and spread ones, every channel count, the smallest and largest
+unit counts.  Data at the edges of its
 bound: noise with one overwhelming channel (many near-equal units), one
 overwhelming sample, zeros, magnitudes at both ends of float32, and NaN and
 infinite samples.
@@ -34,6 +35,8 @@ LATTICES = {
     "1if": [3000.0],
     "3if-spread": [3000.0, 3032.0, 5240.0],
     "16if-compact": [3000.0 + 32.0 * i for i in range(16)],
+    "9if-compact": [3000.0 + 32.0 * i for i in range(9)],
+    "5if-compact": [3000.0 + 32.0 * i for i in (0, 1, 2, 3, 6)],
     "17if": VGOS[:17],
     "20if-even": [3000.0 + 64.0 * i for i in range(19)] + [3032.0],   # 19 even positions, 1 odd
     "32if-vgos": VGOS,
@@ -74,7 +77,9 @@ def _check(s, windows, n_check=14):
 @pytest.mark.parametrize("precision", ["f32", "f16x3", "f16"])
 @pytest.mark.parametrize("name,J,P,R", [("1if", 32, 4, 2), ("3if-spread", 64, 1, 4), ("16if-compact", 32, 8, 2),
                                         ("17if", 32, 2, 4), ("20if-even", 64, 2, 3), ("32if-vgos", 64, 4, 8),
-                                        ("32if-vgos", 32, 4, 9)])
+                                        ("32if-vgos", 32, 4, 9), ("32if-vgos", 16, 4, 4), ("32if-vgos", 128, 4, 3),
+                                        ("20if-even", 128, 1, 2), ("16if-compact", 256, 4, 2), ("3if-spread", 256, 1, 1),
+                                        ("9if-compact", 64, 4, 4), ("5if-compact", 16, 8, 3)])
 def test_screened_peak_is_the_largest_cell(name, J, P, R, precision):
     f0, windows = LATTICES[name], [1, 2, 5]
     note(f"screen {name} J={J} P={P} R={R} {precision}")
