@@ -203,12 +203,14 @@ template <> struct Split<64> { static constexpr int A = 8, B = 8; };
 template <> struct Split<128> { static constexpr int A = 16, B = 8; };
 template <> struct Split<256> { static constexpr int A = 16, B = 16; };
 
-template <int J, int M>
+// BLK threads search one segment: a work-group of kBlock, or one wave (four
+// segments to a work-group).
+template <int J, int M, int BLK = kBlock>
 struct FringeShape {
   static constexpr int JA = Split<J>::A, JB = Split<J>::B;
   static constexpr int MA = Split<M>::A, MB = Split<M>::B;
   static constexpr int G = MA > MB ? MA : MB;    // lanes per MBD column group
-  static constexpr int COLS = kBlock / G;        // columns per round
+  static constexpr int COLS = BLK / G;           // columns per round
   static constexpr int SG = MA * MB + 16;        // float2 per group scratch
 };
 
@@ -216,11 +218,12 @@ struct FringeShape {
 // zero), or [max(N+1, MB)][J+1] in the compact form (rows of lattice
 // positions, those without an IF kept zero), a scratch area shared by the
 // SBD transpose and the MBD transposes, and the PJ-point SBD twiddle table.
-// The host sizes the launch with the larger plan (CL = true).
-template <int J, int M, bool CL = true>
+// The host sizes the launch with the larger plan (CL = true), once per
+// segment of the work-group.
+template <int J, int M, bool CL = true, int BLK = kBlock>
 __host__ __device__ inline void fringe_lds_plan(int n_if, int sbd_pad, int &x_off, int &s_off,
                                                 int &t_off, int &total) {
-  using S = FringeShape<J, M>;
+  using S = FringeShape<J, M, BLK>;
   const int xs = J + 1;
   const int x_rows = CL && S::MB > n_if + 1 ? S::MB : n_if + 1;
   const int x_sz = x_rows * xs;
@@ -236,9 +239,13 @@ __host__ __device__ inline void fringe_lds_plan(int n_if, int sbd_pad, int &x_of
 
 // ------------------------------------------------------- shared fringe steps
 // Which segment a work-group handles.  Work-groups are dealt to the 8 XCDs
-// round-robin; when the grid splits evenly, XCD x gets the contiguous range
-// [x nb/8, (x+1) nb/8) so that overlapping segments share an L2.
-__device__ __forceinline__ void block_segment(const FringeArgs &a, bool dump, int &dl, int &seg) {
+// round-robin; every XCD gets runs of kXcdRun consecutive ones, so that
+// overlapping segments share an L2 and the windows of a DM trial (longer
+// windows cost more) are spread over all XCDs.
+constexpr int kXcdRun = 32;
+// A work-group that takes `per` segments takes consecutive ones (slot w).
+__device__ __forceinline__ void block_segment(const FringeArgs &a, bool dump, int &dl, int &seg, int per = 1,
+                                              int w = 0) {
   if (dump) {
     dl = a.dump_dl;
     seg = a.dump_seg;
@@ -246,7 +253,11 @@ __device__ __forceinline__ void block_segment(const FringeArgs &a, bool dump, in
   }
   const int nb = gridDim.x;
   const int bx = blockIdx.x;
-  const int lb = (nb & 7) == 0 ? (bx & 7) * (nb >> 3) + (bx >> 3) : bx;
+  const int i = bx >> 3;
+  const int run = bx < nb / (8 * kXcdRun) * (8 * kXcdRun)
+                      ? ((i / kXcdRun) * 8 + (bx & 7)) * kXcdRun + i % kXcdRun
+                      : bx;
+  const int lb = run * per + w;
   dl = lb / a.seg_total;
   seg = lb - dl * a.seg_total;
 }
@@ -459,20 +470,33 @@ struct Candidates {
 // records are transformed.  The result is the full search's: the sub-grid
 // with the largest |G|^2 (all bits; then the lowest), its cells keyed; with
 // fewer than 8 (rate, sub-grid) pairs the keys alone decide.
-template <int J, int M, bool DUMP, bool CL, bool LIST = false, unsigned ROWS = 0u, bool CAND = false>
+// BLK = 64: one wave per segment, for shapes whose SBD pass has at most 64
+// lanes' work (N x JB): in a work-group of 256 most threads would wait at its
+// barriers, while four independent waves need none.
+template <int J, int M, bool DUMP, bool CL, bool LIST = false, unsigned ROWS = 0u, bool CAND = false, int BLK = kBlock>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(J <= 64 && !DUMP && !LIST ? 3 : 1)))
 void fringe_kernel(FringeArgs a) {
-  using S = FringeShape<J, M>;
+  static_assert(BLK == kBlock || (BLK == 64 && !DUMP && !LIST), "one wave per segment: plain and candidate searches");
+  using S = FringeShape<J, M, BLK>;
   constexpr int JA = S::JA, JB = S::JB, MA = S::MA, MB = S::MB, G = S::G, COLS = S::COLS;
   constexpr unsigned RMASK = ROWS ? ROWS : (MA >= 32 ? ~0u : (1u << MA) - 1u);
-  extern __shared__ float2 lds[];
-  __shared__ float red_v[kBlock / 64];
-  __shared__ int32_t red_i[kBlock / 64];
+  constexpr int NW = BLK / 64;              // waves per segment
+  constexpr int PER = kBlock / BLK;         // segments per work-group
+  extern __shared__ float2 lds_all[];
+  __shared__ float red_v_all[kBlock / 64];
+  __shared__ int32_t red_i_all[kBlock / 64];
 
   const int N = a.n_if, R = a.n_rate, P = a.sbd_pad;
   const int PJ = P * J;
   const int NJ = N * J;
-  const int t = threadIdx.x;
+  const int t = threadIdx.x % BLK;
+  const int slot = PER > 1 ? __builtin_amdgcn_readfirstlane(int(threadIdx.x) / BLK) : 0;
+  float *const red_v = red_v_all + slot * NW;
+  int32_t *const red_i = red_i_all + slot * NW;
+  auto sync = [&]() {
+    if constexpr (BLK == kBlock) __syncthreads();
+    else wave_lds_sync();
+  };
 
   // ---- which segment: spread consecutive segments over the 8 XCDs in
   // contiguous ranges so that overlapping segments share an L2.
@@ -484,7 +508,8 @@ void fringe_kernel(FringeArgs a) {
     seg = a.seg_list[3 * blockIdx.x + 2];
     dl = lb * a.n_dm + ld;   // cube row
   } else {
-    block_segment(a, DUMP, dl, seg);
+    block_segment(a, DUMP, dl, seg, PER, slot);
+    if (PER > 1 && dl >= a.n_dt) return;   // (no barriers follow)
   }
   int wi = 0;
   while (wi + 1 < a.n_win && a.win_off[wi + 1] <= seg) ++wi;
@@ -495,19 +520,21 @@ void fringe_kernel(FringeArgs a) {
   const float2 *rph = a.rate_ph + a.rate_off[wi];
 
   int x_off, s_off, t_off, total;
-  fringe_lds_plan<J, M, CL>(N, P, x_off, s_off, t_off, total);
+  fringe_lds_plan<J, M, CL, BLK>(N, P, x_off, s_off, t_off, total);
+  // (the candidate masks, R P words, follow the plan)
+  float2 *const lds = lds_all + slot * (total + (CAND ? (R * P + 1) / 2 : 0));
   float2 *X = lds + x_off;
   float2 *Sc = lds + s_off;
   float2 *TW = lds + t_off;
   constexpr int XS = J + 1;
 
-  for (int i = t; i < PJ; i += kBlock) TW[i] = a.tw_sbd[i];
+  for (int i = t; i < PJ; i += BLK) TW[i] = a.tw_sbd[i];
   if constexpr (CL) {
     // rows of lattice positions without an IF stay zero
-    for (int i = t; i < MB * XS; i += kBlock) X[i] = make_float2(0.f, 0.f);
+    for (int i = t; i < MB * XS; i += BLK) X[i] = make_float2(0.f, 0.f);
   } else {
     // the zero row read for empty lattice points
-    for (int i = t; i < XS; i += kBlock) X[N * XS + i] = make_float2(0.f, 0.f);
+    for (int i = t; i < XS; i += BLK) X[N * XS + i] = make_float2(0.f, 0.f);
   }
 
   // ---- per-lane constants of the MBD transform
@@ -549,12 +576,12 @@ void fringe_kernel(FringeArgs a) {
   };
   // SBD transform of sub-grid c -> X
   auto sbd = [&](int c) {
-    __syncthreads();
+    sync();
     sbd_pass1<JA, JB>(y, a.pre_sbd, TW, Sc, c, P, PJ, s_p1, n1, i2s);
-    __syncthreads();
+    sync();
     // SBD pass 2: JB-point DFT over i2 -> X[n][a = k1 + JA k2], the SBD
     // bin s' = c + P a of the standard (unshifted) transform.
-    for (int v = t; v < N * JA; v += kBlock) {
+    for (int v = t; v < N * JA; v += BLK) {
       const int n2 = v / JA, k1 = v - (v / JA) * JA;
       float2 z[JB];
       static_for<0, JB>([&](auto i) {
@@ -568,7 +595,7 @@ void fringe_kernel(FringeArgs a) {
         X[xrow * XS + k1 + JA * kk] = z[kk];
       });
     }
-    __syncthreads();
+    sync();
   };
   // MBD transform of every SBD column of sub-grid c (rate r); FIND: the
   // cells' keys and the running (value, packed index) of the lane, else
@@ -646,11 +673,11 @@ void fringe_kernel(FringeArgs a) {
   constexpr bool SCAN = !DUMP && !LIST;
   const bool scan = SCAN && R * P >= 8;
   if constexpr (CAND) {
-    static_assert(COLS == 16, "a unit is one round of columns");
+    static_assert(M == 256 && 16 % COLS == 0, "a unit is 16 columns");
     unsigned *cand = reinterpret_cast<unsigned *>(lds + total);   // [R P] after the plan
     const Candidates cs{a.screen + (int64_t(dl) * a.seg_total + seg) * R * screen_rec_bytes(a.screen_units), R,
                         a.screen_units, J / 16};
-    for (int i = t; i < R * P; i += kBlock) cand[i] = 0u;
+    for (int i = t; i < R * P; i += BLK) cand[i] = 0u;
     unsigned top = 0u;           // largest |G|^2 (bits) so far and its (rate, sub-grid)
     int top_rc = 0x7fffffff, cur_r = -1;
     float run_v = -1.0f;         // the lane's keyed peak over what counts so far
@@ -659,9 +686,9 @@ void fringe_kernel(FringeArgs a) {
     cs.first(t & 63, P, rc0, sb0);
     for (int it = rc0 >= 0 ? -1 : 0; it < R * P; ++it) {
       if (it == 0) {   // what the first unit leaves
-        __syncthreads();   // cand is cleared
-        cs.mark(t, kBlock, P, rc0 >= 0 ? sqrtf(__uint_as_float(top)) : -1.0f, cand);
-        __syncthreads();
+        sync();   // cand is cleared
+        cs.mark(t, BLK, P, rc0 >= 0 ? sqrtf(__uint_as_float(top)) : -1.0f, cand);
+        sync();
       }
       const int rc = it < 0 ? rc0 : it;
       // (the first unit's sub-grid: again with the first only if others are left)
@@ -682,8 +709,8 @@ void fringe_kernel(FringeArgs a) {
       }
       for (int off = 32; off > 0; off >>= 1) blk = max(blk, unsigned(__shfl_xor(int(blk), off, 64)));
       if ((t & 63) == 0) red_v[t >> 6] = __uint_as_float(blk);
-      __syncthreads();
-      for (int w = 0; w < kBlock / 64; ++w) blk = max(blk, __float_as_uint(red_v[w]));
+      sync();
+      for (int w = 0; w < NW; ++w) blk = max(blk, __float_as_uint(red_v[w]));
       // (the next sbd's first barrier ends the reads of red_v)
       const bool better = blk > top || (blk == top && rc < top_rc);
       if (scan && better && rc != top_rc) {
@@ -710,7 +737,7 @@ void fringe_kernel(FringeArgs a) {
     }
     best_v = run_v;
     best_i = run_i;
-    __syncthreads();   // the reads of red_v are done
+    sync();   // the reads of red_v are done
   } else {
     unsigned scan_v = 0u;
     int scan_rc = 0;
@@ -745,10 +772,10 @@ void fringe_kernel(FringeArgs a) {
         red_v[t >> 6] = __uint_as_float(scan_v);
         red_i[t >> 6] = scan_rc;
       }
-      __syncthreads();
+      sync();
       unsigned vmax = __float_as_uint(red_v[0]);
       int rc = red_i[0];
-      for (int w = 1; w < kBlock / 64; ++w) {
+      for (int w = 1; w < NW; ++w) {
         const unsigned v = __float_as_uint(red_v[w]);
         if (v > vmax || (v == vmax && red_i[w] < rc)) {
           vmax = v;
@@ -784,11 +811,11 @@ void fringe_kernel(FringeArgs a) {
     red_v[t >> 6] = best_v;
     red_i[t >> 6] = best_i;
   }
-  __syncthreads();
+  sync();
   if (t == 0 && !DUMP) {
     float bv = red_v[0];
     int32_t bi = red_i[0];
-    for (int w = 1; w < kBlock / 64; ++w) {
+    for (int w = 1; w < NW; ++w) {
       if (red_v[w] > bv || (red_v[w] == bv && red_i[w] < bi)) {
         bv = red_v[w];
         bi = red_i[w];

@@ -27,6 +27,8 @@ using frbx::DevCrossing;
 namespace {
 
 constexpr double kTwoPi = 6.283185307179586476925286766559;
+// dedispersed tiles that share a launch between baselines, bytes
+constexpr size_t kTileBaselines = size_t(256) << 20;
 // largest bound factor of a coarse screening grid (screen_grid)
 constexpr double kScreenGammaMax = 1.02;
 constexpr double kDefaultKdm = 4.149e6;  // ms MHz^2 per pc cm^-3
@@ -389,6 +391,26 @@ bool use_gemm(const frbx_ctx *c) {
          frbx::fringe_gemm_supported(c->J, c->n_mbd, c->N, c->sbd_pad);
 }
 
+// Whether a run has enough segments to fill the device's 1024 SIMDs several
+// times over (grids set for a run shorter than the stream's chunks: unknown,
+// taken as enough).  A search of 978 segments takes 219 us with a work-group
+// per segment and no screening pass, 223 us with a wave each and one.
+bool many_segments(const frbx_ctx *c) {
+  return c->seg_total <= 0 || int64_t(c->B) * c->n_dm * c->seg_total >= 4096;
+}
+
+// The float32 search takes one wave per segment where the shape allows it and
+// the four segments of a work-group fit its LDS.
+bool use_wave(const frbx_ctx *c, bool screened) {
+  return frbx::fringe_wave(c->J, c->N) && many_segments(c) &&
+         frbx::fringe_lds_bytes(c->J, c->n_mbd, c->N, c->sbd_pad, true, screened ? c->n_rate * c->sbd_pad : 0) <= 80 * 1024;
+}
+
+size_t fringe_lds(const frbx_ctx *c, bool screened) {
+  return frbx::fringe_lds_bytes(c->J, c->n_mbd, c->N, c->sbd_pad, use_wave(c, screened),
+                                screened ? c->n_rate * c->sbd_pad : 0);
+}
+
 // The halved MBD product: more than 16 IFs, at most 16 of them on even and 16
 // on odd lattice positions.
 bool screen_half(const frbx_ctx *c) {
@@ -401,21 +423,21 @@ bool screen_half(const frbx_ctx *c) {
 // every segment and the search's kernel evaluates those.  Every form but the
 // one with the SBD transform on the matrix cores, where the pass has the
 // shape (and the candidate masks fit beside the kernel's LDS plan) and a
-// segment has enough units: with 16 the candidates are a tenth of the
-// search; with 8 (one rate, 32 channels, sbd_pad 4) they are a quarter and
-// the screened search is the slower one (20 s of the paper's set-up: 1.82
-// against 1.59 ms).  The float16 form's own products are the screening
-// pass's but for the halved MBD product, so it is screened only where that
-// applies, up to 64 channels (one baseline, 16 IFs or fewer: 3.38 against
-// 3.11 ms; with 128 channels the pass takes longer than the form itself).
+// segment has enough units: with 16 the candidates are a tenth of the search,
+// with 8 on a coarse MBD grid (one rate, 32 channels, sbd_pad 4: 8 IFs x 1 s x
+// 64 DM trials 3.19 -> 2.46 ms, the paper's set-up x 20 s 1.59 -> 1.29 ms) a
+// fifth; on the full grid the pass itself then costs what it saves.  The
+// float16 form's own products are the screening pass's but for the halved MBD
+// product, so it is screened only where that applies, up to 64 channels (one
+// baseline, 16 IFs or fewer: 3.38 against 3.11 ms; with 128 channels the pass
+// takes longer than the form itself).
 bool use_screen(const frbx_ctx *c, int tiles) {
   const bool half = screen_half(c);
   if (use_gemm(c) || !frbx::screen_supported(c->J, c->n_mbd, c->N, half, tiles, c->sbd_pad)) return false;
-  if (c->n_rate * c->sbd_pad * c->J / 16 < 16) return false;
+  if (c->n_rate * c->sbd_pad * c->J / 16 < (tiles < 16 ? 8 : 16) || !many_segments(c)) return false;
   if (c->precision == FRBX_PREC_F16 && !(half && c->J <= 64)) return false;
-  const size_t lds = c->precision == FRBX_PREC_F32
-                         ? frbx::fringe_lds_bytes(c->J, c->n_mbd, c->N, c->sbd_pad)
-                         : frbx::fringe_mfma_lds_bytes(c->J, c->N, c->sbd_pad, c->precision == FRBX_PREC_F16X3 ? 3 : 1);
+  if (c->precision == FRBX_PREC_F32) return fringe_lds(c, true) <= 150 * 1024;
+  const size_t lds = frbx::fringe_mfma_lds_bytes(c->J, c->N, c->sbd_pad, c->precision == FRBX_PREC_F16X3 ? 3 : 1);
   return lds + size_t(c->n_rate) * c->sbd_pad * 4 <= 150 * 1024;
 }
 
@@ -781,7 +803,8 @@ frbx_status prepare(frbx_ctx *c) {
     for (int n = 0; n < N; ++n) rows |= 1u << (c->q_if[n] / MB);
     const unsigned all = MA >= 32 ? ~0u : (1u << MA) - 1u;
     if (rows != all) {
-      c->rows_fn = frbx::fringe_rows_kernel(c->device, J, M, rows, c->scr_blocks > 0, &c->rows_note);
+      c->rows_fn = frbx::fringe_rows_kernel(c->device, J, M, rows, c->scr_blocks > 0, use_wave(c, c->scr_blocks > 0),
+                                            &c->rows_note);
       if (c->rows_fn) c->rows_mask = rows;
     }
   }
@@ -1367,8 +1390,8 @@ size_t rec_bytes(const frbx_ctx *c, int64_t S) {
 
 // Dedispersion and fringe search of every (baseline, DM tile): the DM
 // trials are taken dt at a time through the dedispersed-tile buffer wbuf
-// ([dt][k_eff][N J]), and every segment's peak goes into the cube
-// power / pidx ([B][D][S]).  A screened search writes the screening records
+// ([dt][k_eff][N J]; dt a multiple of D: whole baselines), and every
+// segment's peak goes into the cube power / pidx ([B][D][S]).  A screened search writes the screening records
 // of a tile to rec (null: none, every unit of every segment is evaluated).
 frbx_status search_tiles(frbx_ctx *c, const PassSpec &ps, float2 *wbuf, int dt, unsigned char *rec, float *power,
                          int32_t *pidx) {
@@ -1379,41 +1402,45 @@ frbx_status search_tiles(frbx_ctx *c, const PassSpec &ps, float2 *wbuf, int dt, 
   frbx_status s;
   const bool use_mfma = c->precision != FRBX_PREC_F32;
   const bool screened = c->scr_blocks > 0;
-  const size_t lds = frbx::fringe_lds_bytes(J, M, c->N, c->sbd_pad) +
-                     (screened ? size_t(c->n_rate) * c->sbd_pad * 4 : 0);
+  const bool wave = use_wave(c, screened);
+  const size_t lds = fringe_lds(c, screened);
   const float scale = mfma_scale(c);
   const size_t in_bytes = ps.vis_f16 ? 4 : 8;
   if (S > 0 && k_eff > 0) {
-    for (int b = 0; b < B; ++b) {
+    const int nb = std::max(1, dt / D);   // baselines per tile
+    for (int b = 0; b < B; b += nb) {
       for (int d0 = 0; d0 < D; d0 += dt) {
-        const int ndt = std::min(dt, D - d0);
-        frbx::DedisperseArgs da{};
-        da.vis = static_cast<const char *>(ps.vis) + size_t(b) * NJ * size_t(ps.stride) * in_bytes;
-        da.in_f16 = ps.vis_f16;
-        da.n_frames = ps.K;
-        da.row_stride = ps.stride;
-        da.dk = c->d_dk;
-        da.d0 = d0;
-        da.n_dt = ndt;
-        da.cal = c->d_cal + size_t(b) * NJ;
-        da.out = wbuf;
-        da.k_eff = k_eff;
-        da.nj = NJ;
-        da.group = c->dd_group;
-        int sp = c->span_begin(1, int64_t(ndt) * k_eff);
-        if (sp >= 0) {
-          // writes: ndt x k_eff spectra; reads: each channel's span of
-          // k_eff + (offset spread of the group) APs once per group
-          int64_t bytes = int64_t(ndt) * k_eff * NJ * 8;
-          for (int g0 = 0; g0 < ndt; g0 += c->dd_group) {
-            const int g1 = std::min(ndt, g0 + c->dd_group) - 1;
-            const int32_t *a0 = c->dk.data() + size_t(d0 + g0) * NJ, *a1 = c->dk.data() + size_t(d0 + g1) * NJ;
-            for (int i = 0; i < NJ; ++i) bytes += (k_eff + (a1[i] - a0[i])) * int64_t(in_bytes);
+        const int n_bl = std::min(nb, B - b), n_d = std::min(dt, D - d0), ndt = n_bl * n_d;
+        int sp;
+        for (int i = 0; i < n_bl; ++i) {
+          frbx::DedisperseArgs da{};
+          da.vis = static_cast<const char *>(ps.vis) + size_t(b + i) * NJ * size_t(ps.stride) * in_bytes;
+          da.in_f16 = ps.vis_f16;
+          da.n_frames = ps.K;
+          da.row_stride = ps.stride;
+          da.dk = c->d_dk;
+          da.d0 = d0;
+          da.n_dt = n_d;
+          da.cal = c->d_cal + size_t(b + i) * NJ;
+          da.out = wbuf + size_t(i) * n_d * k_eff * NJ;
+          da.k_eff = k_eff;
+          da.nj = NJ;
+          da.group = c->dd_group;
+          sp = c->span_begin(1, int64_t(n_d) * k_eff);
+          if (sp >= 0) {
+            // writes: n_d x k_eff spectra; reads: each channel's span of
+            // k_eff + (offset spread of the group) APs once per group
+            int64_t bytes = int64_t(n_d) * k_eff * NJ * 8;
+            for (int g0 = 0; g0 < n_d; g0 += c->dd_group) {
+              const int g1 = std::min(n_d, g0 + c->dd_group) - 1;
+              const int32_t *a0 = c->dk.data() + size_t(d0 + g0) * NJ, *a1 = c->dk.data() + size_t(d0 + g1) * NJ;
+              for (int q = 0; q < NJ; ++q) bytes += (k_eff + (a1[q] - a0[q])) * int64_t(in_bytes);
+            }
+            c->spans[sp].bytes = bytes;
           }
-          c->spans[sp].bytes = bytes;
+          if ((s = c->hip(frbx::launch_dedisperse(da, c->stream), "dedisperse launch")) != FRBX_OK) return s;
+          c->span_end(sp);
         }
-        if ((s = c->hip(frbx::launch_dedisperse(da, c->stream), "dedisperse launch")) != FRBX_OK) return s;
-        c->span_end(sp);
         frbx::FringeArgs fa{};
         fa.w = wbuf;
         fa.w_dm_stride = k_eff * NJ;
@@ -1476,14 +1503,25 @@ frbx_status search_tiles(frbx_ctx *c, const PassSpec &ps, float2 *wbuf, int dt, 
         }
         const hipError_t le =
             use_mfma    ? launch_matrix_core(c, fa, int(ndt * S))
-            : c->rows_fn ? frbx::launch_fringe_rows(c->rows_fn, fa, lds, int(ndt * S), c->stream)
-                         : frbx::launch_fringe(J, M, fa, lds, int(ndt * S), c->stream);
+            : c->rows_fn ? frbx::launch_fringe_rows(c->rows_fn, fa, wave, lds, int(ndt * S), c->stream)
+                         : frbx::launch_fringe(J, M, fa, wave, lds, int(ndt * S), c->stream);
         if ((s = c->hip(le, "fringe launch")) != FRBX_OK) return s;
         c->span_end(sp);
       }
     }
   }
   return FRBX_OK;
+}
+
+// A tile that holds every DM trial of a baseline takes further baselines as
+// long as it stays within `most` bytes (and its tasks within an int): few
+// trials of a short scan would otherwise be one small launch per baseline.
+int whole_baselines(const frbx_ctx *c, int dt, size_t per_dm, int64_t per_trial, size_t most) {
+  const int D = c->n_dm;
+  if (dt < D || per_dm == 0) return dt;
+  int nb = int(std::min<size_t>(size_t(c->B), std::max<size_t>(1, most / (per_dm * size_t(D)))));
+  while (nb > 1 && int64_t(nb) * D * per_trial > (int64_t(1) << 31) - 1) --nb;
+  return nb * D;
 }
 
 frbx_status device_pass(frbx_ctx *c, const PassSpec &ps, std::vector<DevCrossing> &hc) {
@@ -1499,6 +1537,7 @@ frbx_status device_pass(frbx_ctx *c, const PassSpec &ps, std::vector<DevCrossing
   // (a screened tile has n_rate tasks per segment)
   const int64_t per_seg = c->scr_blocks > 0 ? c->n_rate : 1;
   while (c->dt > 1 && int64_t(c->dt) * S * per_seg > (int64_t(1) << 31) - 1) c->dt /= 2;
+  c->dt = whole_baselines(c, c->dt, per_dm * sizeof(float2), S * per_seg, std::min(c->w_budget, kTileBaselines));
   if ((s = ensure(c, c->d_w, c->w_cap, per_dm * c->dt)) != FRBX_OK) return s;
   // the screening records; without memory for them every unit is evaluated
   unsigned char *rec = nullptr;
@@ -1651,6 +1690,7 @@ frbx_status frbx_run_cube_noalloc(frbx_ctx *c, float *power, int32_t *idx, int64
   const bool rec_fit = per_rec > 0 && per_dm + per_rec <= frbx::kNoAllocBytes && S * per_seg <= (int64_t(1) << 31) - 1;
   int dt = int(std::min<size_t>(size_t(D), frbx::kNoAllocBytes / (per_dm + (rec_fit ? per_rec : 0))));
   while (dt > 1 && int64_t(dt) * S * (rec_fit ? per_seg : 1) > (int64_t(1) << 31) - 1) dt /= 2;
+  dt = whole_baselines(c, dt, per_dm + (rec_fit ? per_rec : 0), S * (rec_fit ? per_seg : 1), frbx::kNoAllocBytes);
   if (int64_t(dt) * S > (int64_t(1) << 31) - 1) return c->fail(FRBX_E_INVAL, "too many segments per DM trial");
   const int nw = int(c->windows.size());
   PassSpec ps;
@@ -1957,7 +1997,7 @@ frbx_status frbx_dump_segment(frbx_ctx *c, int32_t b, int32_t d, int32_t w, int6
     le = launch_matrix_core(c, fa, 1);
   } else {
     const size_t lds = frbx::fringe_lds_bytes(c->J, c->n_mbd, c->N, c->sbd_pad);
-    le = frbx::launch_fringe(c->J, c->n_mbd, fa, lds, 1, c->stream);
+    le = frbx::launch_fringe(c->J, c->n_mbd, fa, false, lds, 1, c->stream);
   }
   if ((s = c->hip(le, "fringe launch")) != FRBX_OK) return s;
   return c->hip(hipStreamSynchronize(c->stream), "dump");

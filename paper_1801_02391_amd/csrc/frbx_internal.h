@@ -180,9 +180,13 @@ struct StatsArgs {
 // Launch wrappers (defined in frbx_kernels.hip).  They return the HIP status
 // of the launch.
 hipError_t launch_dedisperse(const DedisperseArgs &a, hipStream_t s);
-hipError_t launch_fringe(int n_chan, int n_mbd, const FringeArgs &a, size_t lds_bytes,
+// wave: one wave per segment (four segments to a work-group) instead of a
+// work-group per segment, where the shape allows it; masks: words for the
+// candidate masks of a screened search
+hipError_t launch_fringe(int n_chan, int n_mbd, const FringeArgs &a, bool wave, size_t lds_bytes,
                          int grid, hipStream_t s);
-size_t fringe_lds_bytes(int n_chan, int n_mbd, int n_if, int sbd_pad);
+size_t fringe_lds_bytes(int n_chan, int n_mbd, int n_if, int sbd_pad, bool wave = false, int masks = 0);
+bool fringe_wave(int n_chan, int n_if);
 bool fringe_supported(int n_chan, int n_mbd, int n_if, int sbd_pad);
 // Lattice rows of the compact MBD form for n_mbd points (0 if unsupported).
 int fringe_compact_rows(int n_mbd);
@@ -302,8 +306,9 @@ hipError_t noalloc_workspace(int device, void **ptr);
 // frbx_jit.cpp).  The first call for a (device, n_chan, n_mbd, rows)
 // compiles and loads it; later calls return the loaded function.  nullptr
 // with the reason in *err when it cannot be built.
-hipFunction_t fringe_rows_kernel(int device, int n_chan, int n_mbd, unsigned rows, bool screened, std::string *err);
-hipError_t launch_fringe_rows(hipFunction_t fn, const FringeArgs &a, size_t lds_bytes, int grid,
+hipFunction_t fringe_rows_kernel(int device, int n_chan, int n_mbd, unsigned rows, bool screened, bool wave,
+                                 std::string *err);
+hipError_t launch_fringe_rows(hipFunction_t fn, const FringeArgs &a, bool wave, size_t lds_bytes, int grid,
                               hipStream_t s);
 #endif  // !__HIPCC_RTC__
 

@@ -5,7 +5,7 @@
 // (frbx_fringe.h, embedded by the build as frbx_rtc_source.inc) and
 // computes the same sums (a separate compilation: multiply-add fusion, and
 // so the last bits, may differ).  Modules stay loaded until the process
-// ends; one per (device, J, M, rows, screened).
+// ends; one per (device, J, M, rows, screened, wave).
 #include <hip/hip_runtime.h>
 #include <hip/hiprtc.h>
 
@@ -28,14 +28,14 @@ struct JitEntry {
 };
 
 std::mutex g_mu;
-std::map<std::tuple<int, int, int, unsigned, bool>, JitEntry> g_cache;
+std::map<std::tuple<int, int, int, unsigned, bool, bool>, JitEntry> g_cache;
 
-// Compile fringe_kernel<J, M, false, false, false, rows, screened> for the
-// current device's architecture; fills e.fn or e.err.
-void compile(int J, int M, unsigned rows, bool screened, JitEntry &e) {
+// Compile fringe_kernel<J, M, false, false, false, rows, screened, threads per
+// segment> for the current device's architecture; fills e.fn or e.err.
+void compile(int J, int M, unsigned rows, bool screened, bool wave, JitEntry &e) {
   const std::string expr = "frbx::fringe_kernel<" + std::to_string(J) + ", " + std::to_string(M) +
                            ", false, false, false, " + std::to_string(rows) + "u, " +
-                           (screened ? "true>" : "false>");
+                           (screened ? "true, " : "false, ") + (wave ? "64>" : "256>");
   hiprtcProgram prog = nullptr;
   if (hiprtcCreateProgram(&prog, kFringeRtcSource, "frbx_fringe_rtc.hip", 0, nullptr, nullptr) !=
       HIPRTC_SUCCESS) {
@@ -91,22 +91,23 @@ void compile(int J, int M, unsigned rows, bool screened, JitEntry &e) {
 
 }  // namespace
 
-hipFunction_t fringe_rows_kernel(int device, int n_chan, int n_mbd, unsigned rows, bool screened,
+hipFunction_t fringe_rows_kernel(int device, int n_chan, int n_mbd, unsigned rows, bool screened, bool wave,
                                  std::string *err) {
   std::lock_guard<std::mutex> lock(g_mu);
-  JitEntry &e = g_cache[std::make_tuple(device, n_chan, n_mbd, rows, screened)];
-  if (!e.fn && e.err.empty()) compile(n_chan, n_mbd, rows, screened, e);
+  JitEntry &e = g_cache[std::make_tuple(device, n_chan, n_mbd, rows, screened, wave)];
+  if (!e.fn && e.err.empty()) compile(n_chan, n_mbd, rows, screened, wave, e);
   if (!e.fn && err) *err = e.err;
   return e.fn;
 }
 
-hipError_t launch_fringe_rows(hipFunction_t fn, const FringeArgs &a, size_t lds_bytes, int grid,
+hipError_t launch_fringe_rows(hipFunction_t fn, const FringeArgs &a, bool wave, size_t lds_bytes, int grid,
                               hipStream_t s) {
   (void)hipGetLastError();
   if (!fn || grid <= 0) return grid <= 0 ? hipSuccess : hipErrorInvalidValue;
   FringeArgs arg = a;
   void *params[] = {&arg};
-  return hipModuleLaunchKernel(fn, unsigned(grid), 1, 1, unsigned(kBlock), 1, 1, unsigned(lds_bytes), s, params,
+  const int per = wave ? kBlock / 64 : 1;
+  return hipModuleLaunchKernel(fn, unsigned((grid + per - 1) / per), 1, 1, unsigned(kBlock), 1, 1, unsigned(lds_bytes), s, params,
                                nullptr);
 }
 

@@ -1186,18 +1186,24 @@ hipError_t launch_dedisperse(const DedisperseArgs &a, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int J, int M, bool DUMP, bool CL, bool LIST = false, bool CAND = false>
+template <int J, int M, bool DUMP, bool CL, bool LIST = false, bool CAND = false, int BLK = kBlock>
 static hipError_t launch_fringe_t(const FringeArgs &a, size_t lds, int grid, hipStream_t s) {
   (void)hipGetLastError();  // start from a clean error state
   if (lds > 64 * 1024) {
     const hipError_t e =
-        hipFuncSetAttribute(reinterpret_cast<const void *>(&fringe_kernel<J, M, DUMP, CL, LIST, 0u, CAND>),
+        hipFuncSetAttribute(reinterpret_cast<const void *>(&fringe_kernel<J, M, DUMP, CL, LIST, 0u, CAND, BLK>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((fringe_kernel<J, M, DUMP, CL, LIST, 0u, CAND>), dim3(grid), dim3(kBlock), lds, s, a);
+  constexpr int PER = kBlock / BLK;
+  hipLaunchKernelGGL((fringe_kernel<J, M, DUMP, CL, LIST, 0u, CAND, BLK>), dim3((grid + PER - 1) / PER), dim3(kBlock), lds,
+                     s, a);
   return hipGetLastError();
 }
+
+// One wave per segment where the SBD pass has at most 64 lanes' work.
+template <int J>
+constexpr bool fringe_wave_shape(int n_if) { return n_if * Split<J>::B <= 64; }
 
 #define FRBX_FOR_M(J)                                              \
   switch (n_mbd) {                                                 \
@@ -1224,31 +1230,37 @@ static auto dispatch(int n_chan, int n_mbd, Fn &&fn) {
 
 struct LaunchFn {
   const FringeArgs &a;
+  bool wave;
   size_t lds;
   int grid;
   hipStream_t s;
+  template <int J, int M, bool CL, bool CAND> hipError_t plain() {
+    if constexpr (J <= 64)
+      if (wave) return launch_fringe_t<J, M, false, CL, false, CAND, 64>(a, lds, grid, s);
+    return launch_fringe_t<J, M, false, CL, false, CAND>(a, lds, grid, s);
+  }
   template <int J, int M> hipError_t operator()() {
     if (a.screened) {
-      if constexpr (M == 256 && J >= 16)
-        return a.mbd_pos ? launch_fringe_t<J, M, false, true, false, true>(a, lds, grid, s)
-                         : launch_fringe_t<J, M, false, false, false, true>(a, lds, grid, s);
+      if constexpr (M == 256 && J >= 16) return a.mbd_pos ? plain<J, M, true, true>() : plain<J, M, false, true>();
       return hipErrorInvalidValue;
     }
-    if (a.mbd_pos)
-      return a.dump ? launch_fringe_t<J, M, true, true>(a, lds, grid, s)
-                    : launch_fringe_t<J, M, false, true>(a, lds, grid, s);
-    return a.dump ? launch_fringe_t<J, M, true, false>(a, lds, grid, s)
-                  : launch_fringe_t<J, M, false, false>(a, lds, grid, s);
+    if (a.dump)
+      return a.mbd_pos ? launch_fringe_t<J, M, true, true>(a, lds, grid, s)
+                       : launch_fringe_t<J, M, true, false>(a, lds, grid, s);
+    return a.mbd_pos ? plain<J, M, true, false>() : plain<J, M, false, false>();
   }
   hipError_t fail() { return hipErrorInvalidValue; }
 };
 
 struct LdsFn {
   int n_if, sbd_pad;
+  bool wave;
+  int masks;   // candidate masks (words)
   template <int J, int M> size_t operator()() {
     int xo, so, to, tot;
-    fringe_lds_plan<J, M>(n_if, sbd_pad, xo, so, to, tot);
-    return size_t(tot) * sizeof(float2);
+    if (wave) fringe_lds_plan<J, M, true, 64>(n_if, sbd_pad, xo, so, to, tot);
+    else fringe_lds_plan<J, M>(n_if, sbd_pad, xo, so, to, tot);
+    return size_t(tot + (masks + 1) / 2) * sizeof(float2) * (wave ? kBlock / 64 : 1);
   }
   size_t fail() { return 0; }
 };
@@ -1264,13 +1276,24 @@ struct SupportFn {
   bool fail() { return false; }
 };
 
-hipError_t launch_fringe(int n_chan, int n_mbd, const FringeArgs &a, size_t lds_bytes, int grid,
+hipError_t launch_fringe(int n_chan, int n_mbd, const FringeArgs &a, bool wave, size_t lds_bytes, int grid,
                          hipStream_t s) {
-  return dispatch(n_chan, n_mbd, LaunchFn{a, lds_bytes, grid, s});
+  if (wave && (a.dump || !fringe_wave(n_chan, a.n_if))) return hipErrorInvalidValue;
+  return dispatch(n_chan, n_mbd, LaunchFn{a, wave, lds_bytes, grid, s});
 }
 
-size_t fringe_lds_bytes(int n_chan, int n_mbd, int n_if, int sbd_pad) {
-  return dispatch(n_chan, n_mbd, LdsFn{n_if, sbd_pad});
+size_t fringe_lds_bytes(int n_chan, int n_mbd, int n_if, int sbd_pad, bool wave, int masks) {
+  return dispatch(n_chan, n_mbd, LdsFn{n_if, sbd_pad, wave, masks});
+}
+
+bool fringe_wave(int n_chan, int n_if) {
+  switch (n_chan) {
+    case 8: return fringe_wave_shape<8>(n_if);
+    case 16: return fringe_wave_shape<16>(n_if);
+    case 32: return fringe_wave_shape<32>(n_if);
+    case 64: return fringe_wave_shape<64>(n_if);
+    default: return false;
+  }
 }
 
 bool fringe_supported(int n_chan, int n_mbd, int n_if, int sbd_pad) {

@@ -99,15 +99,12 @@ void screen_kernel(ScreenArgs a) {
   // the IF of this lane's rows (absent rows read the first IF's data and are cleared)
   int rif[NK];
   static_for<0, NK>([&](auto i) { rif[decltype(i)::value] = a.row_if[16 * decltype(i)::value + row]; });
-  // Tasks (segment, rate), rate fastest.  Work-groups are dealt to the 8
-  // XCDs round-robin: XCD x takes a contiguous eighth of the tasks, so that
-  // the waves in flight on it read the same few segments from its L2.
+  // Tasks (segment, rate), rate fastest, dealt out in sweeps over the grid.
+  // Work-groups go to the 8 XCDs round-robin: those of one XCD take
+  // consecutive tasks of a sweep, so that the waves in flight on it read the
+  // same few segments from its L2.
   const int nb = gridDim.x;
-  const bool split = (nb & 7) == 0;
-  const int xcd = split ? blockIdx.x & 7 : 0, n_x = split ? 8 : 1;
-  const int slot = split ? blockIdx.x >> 3 : blockIdx.x;
-  const int stride = (nb / n_x) * kScreenWaves;
-  const int lo = int(int64_t(a.n_task) * xcd / n_x), hi = int(int64_t(a.n_task) * (xcd + 1) / n_x);
+  const int slot = (nb & 7) == 0 ? (blockIdx.x & 7) * (nb >> 3) + (blockIdx.x >> 3) : blockIdx.x;
 
   for (;;) {
     // the work-group's next task: waves on one SIMD do not advance evenly (the
@@ -115,8 +112,8 @@ void screen_kernel(ScreenArgs a) {
     int k = 0;
     if (lane == 0) k = atomicAdd(&next, 1);
     k = __builtin_amdgcn_readfirstlane(k);
-    const int64_t at = lo + int64_t(k / kScreenWaves) * stride + slot * kScreenWaves + k % kScreenWaves;
-    if (at >= hi) break;
+    const int64_t at = (int64_t(k / kScreenWaves) * nb + slot) * kScreenWaves + k % kScreenWaves;
+    if (at >= a.n_task) break;
     const int task = int(at);
     const int sg = task / R, r = task - sg * R;
     const int dl = sg / a.seg_total, seg = sg - dl * a.seg_total;
@@ -137,45 +134,57 @@ void screen_kernel(ScreenArgs a) {
       off[nt] = n * J + RX * g;
       pho[nt] = n * l;
     });
-    // one AP: loads of two channels at a time (one with RX = 1), at most 16 in flight
-    auto add_ap = [&](int u, auto first_tag) {
+    // loads of two channels at a time (one with RX = 1), 16 in flight: several
+    // APs together where one AP has fewer, parts of an AP where it has more
+    constexpr int PP = RX > 1 ? RX / 2 : 1;               // loads per (row, h)
+    constexpr int NL = NK * 4 * PP, UA = NL < 16 ? 16 / NL : 1, NB = NL < 16 ? NL : 16;
+    auto add_aps = [&](int u0, auto first_tag) {
       constexpr bool FIRST = decltype(first_tag)::value != 0;
-      constexpr int PP = RX > 1 ? RX / 2 : 1;             // loads per (row, h)
-      constexpr int NL = NK * 4 * PP, NB = NL < 16 ? NL : 16;
-      const float2 *src = wd + int64_t(u) * NJ;
-      float2 p[NK];
-      static_for<0, NK>([&](auto i) { p[decltype(i)::value] = ph[pho[decltype(i)::value] + u]; });
+      const float2 *src[UA];
+      float2 p[UA][NK];
+      static_for<0, UA>([&](auto ai) {
+        constexpr int ua = decltype(ai)::value;
+        const int u = min(u0 + ua, l - 1);   // past the segment: its last AP with weight 0
+        src[ua] = wd + int64_t(u) * NJ;
+        static_for<0, NK>([&](auto i) {
+          constexpr int nt = decltype(i)::value;
+          p[ua][nt] = ph[pho[nt] + u];
+          if (ua > 0 && u0 + ua >= l) p[ua][nt] = make_float2(0.f, 0.f);
+        });
+      });
       static_for<0, NL / NB>([&](auto bi) {
-        float4 v[NB];
-        static_for<0, NB>([&](auto kk) {
-          constexpr int q = decltype(bi)::value * NB + decltype(kk)::value;
+        float4 v[UA][NB];
+        static_for<0, UA * NB>([&](auto kk) {
+          constexpr int ua = decltype(kk)::value / NB, q = decltype(bi)::value * NB + decltype(kk)::value % NB;
           constexpr int nt = q / (4 * PP), h = (q / PP) % 4, pp = q % PP;
-          const float2 *at2 = src + off[nt] + 4 * RX * h + 2 * pp;
+          const float2 *at2 = src[ua] + off[nt] + 4 * RX * h + 2 * pp;
           if constexpr (RX > 1) {
-            v[decltype(kk)::value] = *reinterpret_cast<const float4 *>(at2);
+            v[ua][q % NB] = *reinterpret_cast<const float4 *>(at2);
           } else {
             const float2 z = *at2;
-            v[decltype(kk)::value] = make_float4(z.x, z.y, 0.f, 0.f);
+            v[ua][q % NB] = make_float4(z.x, z.y, 0.f, 0.f);
           }
         });
         if constexpr (NL > NB) __builtin_amdgcn_sched_barrier(0);
-        static_for<0, NB>([&](auto kk) {
-          constexpr int q = decltype(bi)::value * NB + decltype(kk)::value;
+        static_for<0, UA * NB>([&](auto kk) {
+          constexpr int ua = decltype(kk)::value / NB, q = decltype(bi)::value * NB + decltype(kk)::value % NB;
           constexpr int nt = q / (4 * PP), h = (q / PP) % 4, pp = q % PP;
-          const float4 x = v[decltype(kk)::value];
+          constexpr bool SET = FIRST && ua == 0;
+          const float4 x = v[ua][q % NB];
+          const float2 w = p[ua][nt];
           float *o = &y[nt][2 * pp < RX ? 2 * pp : 0][2 * h];
-          o[0] = fmaf(x.x, p[nt].x, FIRST ? -x.y * p[nt].y : fmaf(-x.y, p[nt].y, o[0]));
-          o[1] = fmaf(x.x, p[nt].y, FIRST ? x.y * p[nt].x : fmaf(x.y, p[nt].x, o[1]));
+          o[0] = fmaf(x.x, w.x, SET ? -x.y * w.y : fmaf(-x.y, w.y, o[0]));
+          o[1] = fmaf(x.x, w.y, SET ? x.y * w.x : fmaf(x.y, w.x, o[1]));
           if constexpr (RX > 1) {
             float *o2 = &y[nt][2 * pp + 1 < RX ? 2 * pp + 1 : 0][2 * h];
-            o2[0] = fmaf(x.z, p[nt].x, FIRST ? -x.w * p[nt].y : fmaf(-x.w, p[nt].y, o2[0]));
-            o2[1] = fmaf(x.z, p[nt].y, FIRST ? x.w * p[nt].x : fmaf(x.w, p[nt].x, o2[1]));
+            o2[0] = fmaf(x.z, w.x, SET ? -x.w * w.y : fmaf(-x.w, w.y, o2[0]));
+            o2[1] = fmaf(x.z, w.y, SET ? x.w * w.x : fmaf(x.w, w.x, o2[1]));
           }
         });
       });
     };
-    add_ap(0, Index<1>{});
-    for (int u = 1; u < l; ++u) add_ap(u, Index<0>{});
+    add_aps(0, Index<1>{});
+    for (int u = UA; u < l; u += UA) add_aps(u, Index<0>{});
     static_for<0, NK>([&](auto i) {
       constexpr int nt = decltype(i)::value;
       if (g == 0) y[nt][0][0] = y[nt][0][1] = 0.f;   // the j = 0 point is not fitted

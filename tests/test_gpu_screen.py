@@ -28,6 +28,7 @@ from gpu_helpers import note
 pytestmark = pytest.mark.gpu
 
 POWER_TOL = 4e-6
+N_DM = 80   # enough segments (4096) for a search to be screened
 CELL_TOL = 2.0 ** -18 + 2 * POWER_TOL
 
 VGOS = [b + 32.0 * i for b in (3000.0, 5240.0, 6360.0, 10200.0) for i in range(8)]
@@ -47,7 +48,7 @@ def _search(f0, J, P, R, precision, V, windows, t_ap=1.0):
     lay = dict(n_baselines=V.shape[0], if_freq_mhz=f0, n_if=len(f0), n_chan=J, chan_bw_mhz=32.0 / J, t_ap_ms=t_ap,
                n_frames=V.shape[-1])
     s = frbx.Search(lay)
-    s.configure(dict(dm_lo=0.0, dm_step=30.0, n_dm=2, sbd_pad=P, n_mbd=256, n_rate=R, windows=windows, threshold=3.0,
+    s.configure(dict(dm_lo=0.0, dm_step=0.5, n_dm=N_DM, sbd_pad=P, n_mbd=256, n_rate=R, windows=windows, threshold=3.0,
                      n_win_min=1, n_bl_min=1, precision=precision))
     s.load(torch.from_numpy(V).to("cuda:0"))
     s.run()
@@ -66,7 +67,7 @@ def _check(s, windows, n_check=14):
     off = np.cumsum([0] + seg["n_seg"])
     for wi in range(len(windows)):
         for q in np.unique(np.linspace(0, seg["n_seg"][wi] - 1, n_check).astype(int)):
-            for d in range(2):
+            for d in (0, N_DM - 1):
                 p, i = float(P[0, d, off[wi] + q]), int(I[0, d, off[wi] + q])
                 g2 = s.dump_segment(0, d, wi, int(q)).reshape(-1).astype(np.float64)
                 top = np.sqrt(g2.max())
