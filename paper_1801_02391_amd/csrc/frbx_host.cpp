@@ -433,7 +433,7 @@ bool screen_half(const frbx_ctx *c) {
 // takes longer than the form itself).
 bool use_screen(const frbx_ctx *c, int tiles) {
   const bool half = screen_half(c);
-  if (use_gemm(c) || !frbx::screen_supported(c->J, c->n_mbd, c->N, half, tiles, c->sbd_pad)) return false;
+  if (use_gemm(c) || !frbx::screen_supported(c->J, c->n_mbd, c->N, c->n_rate, half, tiles, c->sbd_pad)) return false;
   if (c->n_rate * c->sbd_pad * c->J / 16 < (tiles < 16 ? 8 : 16) || !many_segments(c)) return false;
   if (c->precision == FRBX_PREC_F16 && !(half && c->J <= 64)) return false;
   if (c->precision == FRBX_PREC_F32) return fringe_lds(c, true) <= 150 * 1024;
@@ -785,7 +785,7 @@ frbx_status prepare(frbx_ctx *c) {
     c->scr_err_s = T.err_s;
     c->scr_err_m = T.err_m;
     if ((s = up(c->d_scr_sbd, T.fs)) != FRBX_OK || (s = up(c->d_scr_mbd, T.fm)) != FRBX_OK) return s;
-    if ((s = c->hip(frbx::screen_blocks(J, N, T.half, SG.tiles, c->sbd_pad, c->device, &c->scr_blocks),
+    if ((s = c->hip(frbx::screen_blocks(J, N, c->n_rate, T.half, SG.tiles, c->sbd_pad, c->device, &c->scr_blocks),
                     "screening pass")) != FRBX_OK)
       return s;
   }
@@ -1495,6 +1495,7 @@ frbx_status search_tiles(frbx_ctx *c, const PassSpec &ps, float2 *wbuf, int dt, 
           sa.tiles = c->scr_tiles;
           sa.gamma = float(c->scr_gamma);
           std::copy(c->scr_row_if, c->scr_row_if + 32, sa.row_if);
+          sa.tw_sbd = c->d_tw_sbd;
           sa.f_sbd = c->d_scr_sbd;
           sa.f_mbd = c->d_scr_mbd;
           screen_bounds(c, scale, sa);

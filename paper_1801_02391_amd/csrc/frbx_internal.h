@@ -151,6 +151,7 @@ struct ScreenArgs {
                              // (half: 8)
   float gamma;               // |G| on the full MBD grid <= gamma x largest |G| on the screened one
   int32_t row_if[32];        // IF of each operand row, -1: none
+  const float2 *tw_sbd;      // [P J] exp(-2 pi i k / (P J))
   const void *f_sbd;         // [P][J / 16][re, im][64 lanes] x 8 halves
   const void *f_mbd;         // [tiles][n_if <= 16 ? 1 : 2][re, im][64 lanes] x 8 halves
   float eps_y;               // error bound per unit of sum |y|,
@@ -199,8 +200,9 @@ hipError_t launch_stats(const StatsArgs &a, int rows, hipStream_t s);
 // Screening pass: whether the shape has one, the work-groups that fill the
 // device (persistent over the tasks; `device` current), and its launch with
 // that many.
-bool screen_supported(int n_chan, int n_mbd, int n_if, bool half, int tiles, int sbd_pad);
-hipError_t screen_blocks(int n_chan, int n_if, bool half, int tiles, int sbd_pad, int device, int *blocks);
+bool screen_supported(int n_chan, int n_mbd, int n_if, int n_rate, bool half, int tiles, int sbd_pad);
+hipError_t screen_blocks(int n_chan, int n_if, int n_rate, bool half, int tiles, int sbd_pad, int device,
+                         int *blocks);
 hipError_t launch_screen(int n_chan, const ScreenArgs &a, int blocks, hipStream_t s);
 
 // matrix-core fringe kernel: n_pass = 1 (float16) or 3 (float16 high/low

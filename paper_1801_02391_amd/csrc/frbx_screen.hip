@@ -25,8 +25,15 @@
 //
 // One wave takes one (segment, rate): it forms the segment sums in registers
 // in the A layout, and streams both constant matrices from LDS, where one
-// work-group of eight waves per CU keeps them for the whole launch; waves
-// never wait for each other.
+// work-group of eight waves per CU keeps them for the whole launch.
+//
+// Where the sums are large (64 channels or more, at least four rates) the
+// eight waves take consecutive tasks, mostly the rates of one segment, and
+// read its spectra from an LDS ring that they fill together, direct from
+// memory, while they are still at the tasks before: every rate for itself
+// fetched each spectrum again (45 GB a launch at 32 IFs x 128 channels, where
+// the sums then took half the pass).  Elsewhere waves never wait for each
+// other.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -76,22 +83,66 @@ __device__ __forceinline__ float wave_max(float v) {
 // the larger counts: max |a +- b|^2 = |a|^2 + |b|^2 + 2 |Re a conj(b)|.
 // Otherwise the columns may be a coarser grid of the MBD axis (a.tiles x 16
 // bins), whose largest |G| bounds the full grid's (a.gamma).
-template <int J, int NK, bool HALF>
+// RING: the spectra come through the LDS ring.  With 256 channels the ring's
+// room comes from the SBD matrix: E_p = w_PJ^(p s0) sum_i y[RX i + p]
+// w_PJ^(RX i s0) with one matrix per sub-grid and the factor applied in
+// float32.
+constexpr int kRing = 3;   // slabs
+
+// What one slab of the ring holds: NTS x 16 operand rows of CH chunks of two
+// channels (NP slabs to an AP), then every wave's rate phasors of the AP's
+// rows.  The chunks of a row are stored in XOR order so that the 16 rows a
+// read touches lie in different banks.
+template <int J, int NK>
+struct Slab {
+  static constexpr int NP = (J == 128 && NK == 2) || J == 256 ? 2 : 1;
+  static constexpr int NTS = J == 128 ? 1 : NK;               // 16-row tiles
+  static constexpr int HS = J == 256 ? 2 : 4;                 // h of a lane's channels
+  static constexpr int CH = HS * 4 * (J / 16) / 2;            // 16-byte chunks per row
+  static constexpr int BYTES = NTS * 16 * CH * 16;
+  static constexpr int LOADS = BYTES / 1024 / kScreenWaves;   // per wave, 1 KiB each
+  static constexpr int STRIDE = BYTES + kScreenWaves * 256;
+};
+
+// 64 lanes x 16 (4) bytes from each lane's address to LDS offset `lds` + 16
+// (4) lane, without passing through registers; completion counts in vmcnt.
+__device__ __forceinline__ void load_lds16(const void *src, unsigned lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(src) : "memory", "m0");
+}
+__device__ __forceinline__ void load_lds4(const void *src, unsigned lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(lds), "v"(src) : "memory", "m0");
+}
+
+// A position in the sequence of slabs of the work-group's blocks of eight
+// tasks: block, segment, AP and part.
+struct SlabCursor {
+  int block, sg, last_sg, u, l, part;
+  const float2 *wd, *ph;   // the segment's spectra and its window's phasors
+};
+
+template <int J, int NK, bool HALF, bool RING>
 __global__ __launch_bounds__(kScreenBlock) __attribute__((amdgpu_waves_per_eu(2)))
 void screen_kernel(ScreenArgs a) {
   constexpr int RX = J / 16;
   constexpr int CG = RX >= 4 ? 1 : 4 / RX;   // sub-grids per pass over the MBD matrix
   constexpr int U = CG * RX;                 // units per pass
+  constexpr bool TWIDDLE = RING && J == 256;
+  constexpr int NF = TWIDDLE ? 1 : RX;       // SBD matrices per sub-grid
   extern __shared__ h8_t lds_h[];
-  const int N = a.n_if, R = a.n_rate, NJ = N * J, units = a.units;
+  const int N = a.n_if, R = a.n_rate, NJ = N * J, units = a.units, P = units / RX;
   const int MT = HALF ? 8 : a.tiles;
-  h8_t *const Fm = lds_h;                      // [MT][NK][re, im][64]
-  h8_t *const Fs = lds_h + MT * NK * 2 * 64;   // [P][RX][re, im][64]
-  __shared__ int next;                         // tasks taken by the work-group
+  char *const ring = reinterpret_cast<char *>(lds_h);   // first: its offsets stay within 64 KiB
+  h8_t *const Fm = lds_h + (RING ? kRing * Slab<J, NK>::STRIDE / 16 : 0);   // [MT][NK][re, im][64]
+  h8_t *const Fs = Fm + MT * NK * 2 * 64;                                   // [P][NF][re, im][64]
+  float2 *const TW = reinterpret_cast<float2 *>(Fs + P * NF * 2 * 64);      // TWIDDLE: [P J]
+  __shared__ int next;                                  // tasks taken by the work-group
   {
     const h8_t *gm = static_cast<const h8_t *>(a.f_mbd), *gs = static_cast<const h8_t *>(a.f_sbd);
     for (int i = threadIdx.x; i < MT * NK * 2 * 64; i += kScreenBlock) Fm[i] = gm[i];
-    for (int i = threadIdx.x; i < units * 2 * 64; i += kScreenBlock) Fs[i] = gs[i];
+    for (int i = threadIdx.x; i < P * NF * 2 * 64; i += kScreenBlock)
+      Fs[i] = gs[i / (NF * 128) * (RX * 128) + i % (NF * 128)];
+    if constexpr (TWIDDLE)
+      for (int i = threadIdx.x; i < P * J; i += kScreenBlock) TW[i] = a.tw_sbd[i];
     if (threadIdx.x == 0) next = 0;
   }
   __syncthreads();
@@ -106,27 +157,167 @@ void screen_kernel(ScreenArgs a) {
   const int nb = gridDim.x;
   const int slot = (nb & 7) == 0 ? (blockIdx.x & 7) * (nb >> 3) + (blockIdx.x >> 3) : blockIdx.x;
 
-  for (;;) {
-    // the work-group's next task: waves on one SIMD do not advance evenly (the
-    // older one issues first), so none has tasks of its own
-    int k = 0;
-    if (lane == 0) k = atomicAdd(&next, 1);
-    k = __builtin_amdgcn_readfirstlane(k);
-    const int64_t at = (int64_t(k / kScreenWaves) * nb + slot) * kScreenWaves + k % kScreenWaves;
-    if (at >= a.n_task) break;
-    const int task = int(at);
-    const int sg = task / R, r = task - sg * R;
+  // window and address of a segment
+  auto segment = [&](int sg, int &l, const float2 *&wd, const float2 *&ph) {
     const int dl = sg / a.seg_total, seg = sg - dl * a.seg_total;
     int wi = 0;
     while (wi + 1 < a.n_win && a.win_off[wi + 1] <= seg) ++wi;
-    const int l = a.win_len[wi];
+    l = a.win_len[wi];
     const int64_t k0 = a.win_k0[wi] + int64_t(seg - a.win_off[wi]) * a.win_hop[wi];
-    const float2 *wd = a.w + int64_t(dl) * a.w_dm_stride + k0 * NJ;
-    const float2 *ph = a.rate_ph + a.rate_off[wi] + int64_t(r) * N * l;
+    wd = a.w + int64_t(dl) * a.w_dm_stride + k0 * NJ;
+    ph = a.rate_ph + a.rate_off[wi];
+  };
+
+  // ---- the ring: slab n of the sequence lies in slot n % kRing; slab n + 2
+  // is asked for when every wave has finished with slab n - 1
+  using SL = Slab<J, NK>;
+  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+  const int n_block = (a.n_task + kScreenWaves - 1) / kScreenWaves;
+  const unsigned ring_at = unsigned(reinterpret_cast<uintptr_t>(
+      (__attribute__((address_space(3))) char *)ring));
+  unsigned goff[SL::NP][RING && SL::LOADS > 0 ? SL::LOADS : 1];   // this lane's elements of a part, from the AP's start
+  unsigned poff = 0;                                              // and of the phasors: row, and re or im
+  if constexpr (RING) {
+    static_for<0, SL::NP * SL::LOADS>([&](auto i) {
+      constexpr int part = decltype(i)::value / SL::LOADS, q = decltype(i)::value % SL::LOADS;
+      const int pos = (wave * SL::LOADS + q) * 64 + lane;
+      const int rw = pos / SL::CH, c = (pos % SL::CH) ^ (rw & 15);
+      const int rt = SL::NTS < NK ? part * 16 + rw : rw;
+      const int n = max(a.row_if[rt], 0), j0 = SL::HS < 4 ? part * SL::CH * 2 : 0;
+      goff[part][q] = unsigned(n * J + j0 + 2 * c);
+    });
+    const int prow = lane / 2 < 16 * NK ? max(a.row_if[lane / 2], 0) : 0;
+    poff = unsigned(prow);
+  }
+  auto open_block = [&](SlabCursor &c) {
+    const int t0 = c.block * kScreenWaves;
+    c.sg = t0 / R;
+    c.last_sg = min(t0 + kScreenWaves - 1, a.n_task - 1) / R;
+    c.u = c.part = 0;
+    segment(c.sg, c.l, c.wd, c.ph);
+  };
+  // to the next slab; false at the end of the block
+  auto advance = [&](SlabCursor &c) -> bool {
+    if (++c.part < SL::NP) return true;
+    c.part = 0;
+    if (++c.u < c.l) return true;
+    c.u = 0;
+    if (++c.sg > c.last_sg) return false;
+    segment(c.sg, c.l, c.wd, c.ph);
+    return true;
+  };
+  auto fetch = [&](const SlabCursor &c, int at) {
+    const unsigned dst = ring_at + unsigned(at) * SL::STRIDE;
+    const float2 *ap = c.wd + int64_t(c.u) * NJ;
+    static_for<0, (RING ? SL::LOADS : 0)>([&](auto i) {
+      constexpr int q = decltype(i)::value;
+      unsigned o = goff[0][q];
+      if constexpr (SL::NP > 1) o = c.part ? goff[1][q] : o;
+      load_lds16(ap + o, dst + unsigned(wave * SL::LOADS + q) * 1024u);
+    });
+    // the phasors of this wave's rate (of any rate where the segment is not its own)
+    const int task = min(c.block * kScreenWaves + wave, a.n_task - 1), rr = task % R;
+    const float *pv = reinterpret_cast<const float *>(c.ph + (int64_t(rr) * N + poff) * c.l + c.u) + (lane & 1);
+    load_lds4(pv, dst + SL::BYTES + unsigned(wave) * 256u);
+  };
+  SlabCursor ld{}, use{};      // next slab to fetch, next to use
+  int ld_at = 0, use_at = 0;   // their slots
+  bool more = false;           // ld is valid
+  auto fetch_next = [&]() {
+    if (!more) return;
+    fetch(ld, ld_at);
+    ld_at = ld_at + 1 == kRing ? 0 : ld_at + 1;
+    if (!advance(ld)) {
+      ld.block += nb;
+      more = ld.block < n_block;
+      if (more) open_block(ld);
+    }
+  };
+  if constexpr (RING) {
+    ld.block = use.block = slot;
+    more = slot < n_block;
+    if (more) open_block(ld);
+    fetch_next();
+    fetch_next();
+  }
+
+  for (;;) {
+    int task;
+    bool live = true;   // (RING: the last block may have fewer tasks than waves)
+    if constexpr (RING) {
+      if (use.block >= n_block) break;
+      task = use.block * kScreenWaves + wave;
+      live = task < a.n_task;
+    } else {
+      // the work-group's next task: waves on one SIMD do not advance evenly (the
+      // older one issues first), so none has tasks of its own
+      int k = 0;
+      if (lane == 0) k = atomicAdd(&next, 1);
+      k = __builtin_amdgcn_readfirstlane(k);
+      const int64_t at = (int64_t(k / kScreenWaves) * nb + slot) * kScreenWaves + k % kScreenWaves;
+      if (at >= a.n_task) break;
+      task = int(at);
+    }
+    const int sg = task / R, r = task - sg * R;
+    int l;
+    const float2 *wd, *ph;
+    if constexpr (!RING) {
+      segment(sg, l, wd, ph);
+      ph += int64_t(r) * N * l;
+    }
 
     // ---- segment sums (Eq. 3 with the Eq. 4 rotation): lane (row, g) holds
     // row 16 nt + row, channels RX (4 h + g) + p, h < 4: y[nt][p][2 h + re/im]
     float y[NK][RX][8];
+    if constexpr (RING) {
+      static_for<0, NK * RX * 8>([&](auto kk) {
+        constexpr int q = decltype(kk)::value;
+        y[q / (RX * 8)][(q / 8) % RX][q % 8] = 0.f;
+      });
+      open_block(use);
+      for (bool in_block = true; in_block;) {
+        // this wave's loads of the slab are done (one newer slab may be on its
+        // way) and its reads of the slab before; then everyone's
+        if (more) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(SL::LOADS + 1) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        fetch_next();
+        if (use.sg == sg && live) {
+          const char *sl = ring + use_at * SL::STRIDE;
+          const float2 *pw = reinterpret_cast<const float2 *>(sl + SL::BYTES + wave * 256);
+          const float4 *rows = reinterpret_cast<const float4 *>(sl);
+          auto part = [&](auto pt) {
+            constexpr int PT = decltype(pt)::value;
+            static_for<0, SL::NTS>([&](auto ti) {
+              constexpr int tl = decltype(ti)::value, nt = SL::NTS < NK ? PT : tl;
+              const float2 w = pw[16 * nt + row];
+              static_for<0, SL::HS * RX / 2>([&](auto kk) {
+                constexpr int hl = decltype(kk)::value / (RX / 2), pp = decltype(kk)::value % (RX / 2);
+                constexpr int h = (SL::HS < 4 ? SL::HS * PT : 0) + hl;
+                const float4 x = rows[(16 * tl + row) * SL::CH + (((4 * hl + g) * (RX / 2) + pp) ^ row)];
+                float *o = &y[nt][2 * pp][2 * h], *o2 = &y[nt][2 * pp + 1][2 * h];
+                o[0] = fmaf(x.x, w.x, fmaf(-x.y, w.y, o[0]));
+                o[1] = fmaf(x.x, w.y, fmaf(x.y, w.x, o[1]));
+                o2[0] = fmaf(x.z, w.x, fmaf(-x.w, w.y, o2[0]));
+                o2[1] = fmaf(x.z, w.y, fmaf(x.w, w.x, o2[1]));
+              });
+            });
+          };
+          if constexpr (SL::NP == 1) {
+            part(Index<0>{});
+          } else {
+            if (use.part == 0) part(Index<0>{});
+            else part(Index<1>{});
+          }
+        }
+        use_at = use_at + 1 == kRing ? 0 : use_at + 1;
+        in_block = advance(use);
+      }
+      use.block += nb;
+      if (!live) continue;
+    }
+    if constexpr (!RING) {
     int off[NK], pho[NK];
     static_for<0, NK>([&](auto i) {
       constexpr int nt = decltype(i)::value;
@@ -185,6 +376,7 @@ void screen_kernel(ScreenArgs a) {
     };
     add_aps(0, Index<1>{});
     for (int u = UA; u < l; u += UA) add_aps(u, Index<0>{});
+    }
     static_for<0, NK>([&](auto i) {
       constexpr int nt = decltype(i)::value;
       if (g == 0) y[nt][0][0] = y[nt][0][1] = 0.f;   // the j = 0 point is not fitted
@@ -259,17 +451,27 @@ void screen_kernel(ScreenArgs a) {
         static_for<0, NK>([&](auto i) {
           constexpr int nt = decltype(i)::value;
           f4_t er[RX], ei[RX];
-          const h8_t *const fs = Fs + (c0 + cc) * RX * 2 * 64 + lane;
+          const h8_t *const fs = Fs + (c0 + cc) * NF * 2 * 64 + lane;
           h8_t bs[2][2] = {{fs[0], fs[64]}};
+          const int s0 = c0 + cc + P * row;
           static_for<0, RX>([&](auto pi) {
-            constexpr int p = decltype(pi)::value;
+            constexpr int p = decltype(pi)::value, q = TWIDDLE ? 0 : p & 1;
             const f4_t zero = {0.f, 0.f, 0.f, 0.f};
-            if constexpr (p + 1 < RX) {
+            if constexpr (p + 1 < NF) {
               bs[(p + 1) & 1][0] = fs[(p + 1) * 128];
               bs[(p + 1) & 1][1] = fs[(p + 1) * 128 + 64];
             }
-            er[p] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ya[nt][p], bs[p & 1][0], zero, 0, 0, 0);
-            ei[p] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ya[nt][p], bs[p & 1][1], zero, 0, 0, 0);
+            er[p] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ya[nt][p], bs[q][0], zero, 0, 0, 0);
+            ei[p] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ya[nt][p], bs[q][1], zero, 0, 0, 0);
+            if constexpr (TWIDDLE && p > 0) {
+              const float2 w = TW[(p * s0) & (P * J - 1)];
+              static_for<0, 4>([&](auto hh) {
+                constexpr int h = decltype(hh)::value;
+                const float2 z = cmul(make_float2(er[p][h], ei[p][h]), w);
+                er[p][h] = z.x;
+                ei[p][h] = z.y;
+              });
+            }
             // (keeps the operands of later residues out of the registers)
             if constexpr (RX >= 8) __builtin_amdgcn_sched_barrier(0);
           });
@@ -373,45 +575,61 @@ void screen_kernel(ScreenArgs a) {
   }
 }
 
-constexpr size_t kScreenLdsMax = 150 * 1024;
+constexpr size_t kScreenLdsMax = 156 * 1024;
 
-size_t screen_lds(int n_if, bool half, int tiles, int units) {
-  return size_t((half ? 8 : tiles) * (n_if <= 16 ? 1 : 2) + units) * 2 * 64 * sizeof(h8_t);
+// The ring form: 64 channels or more and at least four rates.
+bool screen_ring(int n_chan, int n_rate) { return n_chan >= 64 && n_rate >= 4; }
+
+size_t screen_lds(int n_chan, int n_if, int n_rate, bool half, int tiles, int units) {
+  const int nk = n_if <= 16 ? 1 : 2;
+  size_t ring = 0, sbd = size_t(units);
+  size_t tw = 0;
+  if (screen_ring(n_chan, n_rate)) {
+    ring = kRing * (n_chan == 64 ? (nk == 1 ? Slab<64, 1>::STRIDE : Slab<64, 2>::STRIDE)
+                    : n_chan == 128 ? (nk == 1 ? Slab<128, 1>::STRIDE : Slab<128, 2>::STRIDE)
+                                    : Slab<256, 1>::STRIDE);
+    if (n_chan == 256) {
+      sbd = size_t(units) / 16;
+      tw = size_t(units) * 16 * sizeof(float2);
+    }
+  }
+  return ring + (size_t(half ? 8 : tiles) * nk + sbd) * 2 * 64 * sizeof(h8_t) + tw;
 }
 
 // f(kernel) for the instantiation of a shape
-template <int J, typename F>
+template <int J, bool RING, typename F>
 hipError_t with_kernel_j(int n_if, bool half, F &&f) {
-  if (n_if <= 16) return f(&screen_kernel<J, 1, false>);
-  if constexpr (J <= 128) return half ? f(&screen_kernel<J, 2, true>) : f(&screen_kernel<J, 2, false>);
+  if (n_if <= 16) return f(&screen_kernel<J, 1, false, RING>);
+  if constexpr (J <= 128) return half ? f(&screen_kernel<J, 2, true, RING>) : f(&screen_kernel<J, 2, false, RING>);
   return hipErrorInvalidValue;
 }
 
 template <typename F>
-hipError_t with_kernel(int n_chan, int n_if, bool half, F &&f) {
+hipError_t with_kernel(int n_chan, int n_if, int n_rate, bool half, F &&f) {
+  const bool ring = screen_ring(n_chan, n_rate);
   switch (n_chan) {
-    case 16: return with_kernel_j<16>(n_if, half, f);
-    case 32: return with_kernel_j<32>(n_if, half, f);
-    case 64: return with_kernel_j<64>(n_if, half, f);
-    case 128: return with_kernel_j<128>(n_if, half, f);
-    case 256: return with_kernel_j<256>(n_if, half, f);
+    case 16: return with_kernel_j<16, false>(n_if, half, f);
+    case 32: return with_kernel_j<32, false>(n_if, half, f);
+    case 64: return ring ? with_kernel_j<64, true>(n_if, half, f) : with_kernel_j<64, false>(n_if, half, f);
+    case 128: return ring ? with_kernel_j<128, true>(n_if, half, f) : with_kernel_j<128, false>(n_if, half, f);
+    case 256: return ring ? with_kernel_j<256, true>(n_if, half, f) : with_kernel_j<256, false>(n_if, half, f);
     default: return hipErrorInvalidValue;
   }
 }
 
 }  // namespace
 
-bool screen_supported(int n_chan, int n_mbd, int n_if, bool half, int tiles, int sbd_pad) {
+bool screen_supported(int n_chan, int n_mbd, int n_if, int n_rate, bool half, int tiles, int sbd_pad) {
   if (n_mbd != 256 || n_if < 1 || n_if > (n_chan == 256 ? 16 : 32)) return false;
   if (n_chan != 16 && n_chan != 32 && n_chan != 64 && n_chan != 128 && n_chan != 256) return false;
   const int units = sbd_pad * n_chan / 16;
-  return units >= 4 && units <= kScreenUnitsMax && screen_lds(n_if, half, tiles, units) <= kScreenLdsMax;
+  return units >= 4 && units <= kScreenUnitsMax && screen_lds(n_chan, n_if, n_rate, half, tiles, units) <= kScreenLdsMax;
 }
 
-hipError_t screen_blocks(int n_chan, int n_if, bool half, int tiles, int sbd_pad, int device, int *blocks) {
-  const size_t lds = screen_lds(n_if, half, tiles, sbd_pad * n_chan / 16);
+hipError_t screen_blocks(int n_chan, int n_if, int n_rate, bool half, int tiles, int sbd_pad, int device, int *blocks) {
+  const size_t lds = screen_lds(n_chan, n_if, n_rate, half, tiles, sbd_pad * n_chan / 16);
   (void)hipGetLastError();
-  return with_kernel(n_chan, n_if, half, [&](auto kern) -> hipError_t {
+  return with_kernel(n_chan, n_if, n_rate, half, [&](auto kern) -> hipError_t {
     const void *fn = reinterpret_cast<const void *>(kern);
     // (the largest any shape needs: the attribute belongs to the function, not to this context)
     hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, int(kScreenLdsMax));
@@ -427,14 +645,14 @@ hipError_t screen_blocks(int n_chan, int n_if, bool half, int tiles, int sbd_pad
 hipError_t launch_screen(int n_chan, const ScreenArgs &a, int blocks, hipStream_t s) {
   if (a.n_task <= 0) return hipSuccess;
   if (a.units < 4 || a.units % 4 || a.units > kScreenUnitsMax || a.n_if < 1 || a.n_if > 32 || blocks < 1 || !a.rec ||
-      !a.f_sbd || !a.f_mbd || (a.half && a.n_if <= 16) ||
+      !a.f_sbd || !a.f_mbd || !a.tw_sbd || a.n_rate < 1 || (a.half && a.n_if <= 16) ||
       a.tiles < 1 || a.tiles > 16 || !(a.gamma >= 1.f))
     return hipErrorInvalidValue;
-  const size_t lds = screen_lds(a.n_if, a.half != 0, a.tiles, a.units);
+  const size_t lds = screen_lds(n_chan, a.n_if, a.n_rate, a.half != 0, a.tiles, a.units);
   if (lds > kScreenLdsMax) return hipErrorInvalidValue;
   const int need = (a.n_task + kScreenWaves - 1) / kScreenWaves;
   (void)hipGetLastError();
-  return with_kernel(n_chan, a.n_if, a.half != 0, [&](auto kern) -> hipError_t {
+  return with_kernel(n_chan, a.n_if, a.n_rate, a.half != 0, [&](auto kern) -> hipError_t {
     hipLaunchKernelGGL(kern, dim3(std::min(blocks, need)), dim3(kScreenBlock), lds, s, a);
     return hipGetLastError();
   });

@@ -7,7 +7,8 @@ Shapes at the edges of the pass: one and two blocks of 16 operand rows, IFs
 that split evenly by the parity of their lattice position and ones that do
 not, a single IF (every MBD bin alike), compact lattices (coarse MBD grids of
 1 to 8 tiles) and spread ones, every channel count, the smallest and largest
-unit counts.  Data at the edges of its
+unit counts; rates that fill the blocks of eight tasks evenly and ones that do
+not, windows shorter and longer than the ring of spectra.  Data at the edges of its
 bound: noise with one overwhelming channel (many near-equal units), one
 overwhelming sample, zeros, magnitudes at both ends of float32, and NaN and
 infinite samples.
@@ -80,7 +81,10 @@ def _check(s, windows, n_check=14):
                                         ("17if", 32, 2, 4), ("20if-even", 64, 2, 3), ("32if-vgos", 64, 4, 8),
                                         ("32if-vgos", 32, 4, 9), ("32if-vgos", 16, 4, 4), ("32if-vgos", 128, 4, 3),
                                         ("20if-even", 128, 1, 2), ("16if-compact", 256, 4, 2), ("3if-spread", 256, 1, 1),
-                                        ("9if-compact", 64, 4, 4), ("5if-compact", 16, 8, 3)])
+                                        ("9if-compact", 64, 4, 4), ("5if-compact", 16, 8, 3),
+                                        ("32if-vgos", 64, 4, 5), ("17if", 64, 1, 11), ("20if-even", 128, 2, 4),
+                                        ("32if-vgos", 128, 4, 9), ("3if-spread", 128, 4, 6),
+                                        ("16if-compact", 256, 4, 4), ("3if-spread", 256, 2, 13)])
 def test_screened_peak_is_the_largest_cell(name, J, P, R, precision):
     f0, windows = LATTICES[name], [1, 2, 5]
     note(f"screen {name} J={J} P={P} R={R} {precision}")
