@@ -287,15 +287,18 @@ void screen_kernel(ScreenArgs a) {
           const char *sl = ring + use_at * SL::STRIDE;
           const float2 *pw = reinterpret_cast<const float2 *>(sl + SL::BYTES + wave * 256);
           const float4 *rows = reinterpret_cast<const float4 *>(sl);
+          int rw = row, gr = g;
+          // (RX >= 8: the addresses are formed anew, not kept in registers from slab to slab)
+          if constexpr (RX >= 8) asm volatile("" : "+v"(rw), "+v"(gr));
           auto part = [&](auto pt) {
             constexpr int PT = decltype(pt)::value;
             static_for<0, SL::NTS>([&](auto ti) {
               constexpr int tl = decltype(ti)::value, nt = SL::NTS < NK ? PT : tl;
-              const float2 w = pw[16 * nt + row];
+              const float2 w = pw[16 * nt + rw];
               static_for<0, SL::HS * RX / 2>([&](auto kk) {
                 constexpr int hl = decltype(kk)::value / (RX / 2), pp = decltype(kk)::value % (RX / 2);
                 constexpr int h = (SL::HS < 4 ? SL::HS * PT : 0) + hl;
-                const float4 x = rows[(16 * tl + row) * SL::CH + (((4 * hl + g) * (RX / 2) + pp) ^ row)];
+                const float4 x = rows[(16 * tl + rw) * SL::CH + (((4 * hl + gr) * (RX / 2) + pp) ^ rw)];
                 float *o = &y[nt][2 * pp][2 * h], *o2 = &y[nt][2 * pp + 1][2 * h];
                 o[0] = fmaf(x.x, w.x, fmaf(-x.y, w.y, o[0]));
                 o[1] = fmaf(x.x, w.y, fmaf(x.y, w.x, o[1]));
@@ -443,6 +446,14 @@ void screen_kernel(ScreenArgs a) {
     };
     operand(0, b);
     for (int c0 = 0; c0 * RX < units; c0 += CG) {
+      // of the two waves of a SIMD the older issues first; the one that is ahead
+      // steps back, so that both reach the ring's barrier together
+      if constexpr (RING) {
+        if (c0 == 0) __builtin_amdgcn_s_setprio(3);
+        else if (c0 == 1) __builtin_amdgcn_s_setprio(2);
+        else if (c0 == 2) __builtin_amdgcn_s_setprio(1);
+        else __builtin_amdgcn_s_setprio(0);
+      }
       // SBD of CG sub-grids -> A operands of the MBD product
       h8_t xa[U][NK];
       static_for<0, CG>([&](auto ci) {
@@ -494,6 +505,8 @@ void screen_kernel(ScreenArgs a) {
             });
             z2[kx] = z;
           });
+          // (one row tile's products and DFTs at a time: both together do not fit the registers)
+          if constexpr (RX >= 8) __builtin_amdgcn_sched_barrier(0);
         });
         static_for<0, RX>([&](auto ki) { x2 = fmaxf(x2, z2[decltype(ki)::value]); });
       });
