@@ -401,20 +401,27 @@ __device__ __forceinline__ void mbd_column_max(const float2 (&z)[MB], unsigned &
 }
 
 // ---------------------------------------------- candidates of a screened search
-// The units (16 SBD bins of one sub-grid) of a segment that its screening
+// The quads (four SBD bins of a sub-grid) of a segment that its screening
 // records leave standing: first the one with the largest screened |G|, then,
 // once that one's own |G| is known, every other that could exceed it.
 struct Candidates {
   const unsigned char *rec;   // the segment's R records
   int R, units, per_c;        // per_c = J / 16 units per sub-grid
-  // the unit with the largest screened |G| as (rate * P + sub-grid, unit of
+  __device__ __forceinline__ float2 bounds(int r) const {
+    return *reinterpret_cast<const float2 *>(rec + int64_t(r) * screen_rec_bytes(units));
+  }
+  // the four quads of unit u at rate r
+  __device__ __forceinline__ unsigned quads(int r, int u) const {
+    return reinterpret_cast<const unsigned *>(rec + int64_t(r) * screen_rec_bytes(units) + 8)[u];
+  }
+  // the quad with the largest screened |G| as (rate * P + sub-grid, quad of
   // the sub-grid); rc = -1 when no record knows one.  Every wave of the
   // work-group finds the same (R and units are at most 64).
-  __device__ __forceinline__ void first(int lane, int P, int &rc, int &sb) const {
+  __device__ __forceinline__ void first(int lane, int P, int &rc, int &qd) const {
     float top = -1.0f;
     int r = lane;
     if (lane < R && units > 0) {
-      const float2 ab = *reinterpret_cast<const float2 *>(rec + int64_t(lane) * screen_rec_bytes(units));
+      const float2 ab = bounds(lane);
       if (ab.y < __builtin_inff()) top = ab.x;
     }
     for (int off = 32; off > 0; off >>= 1) {
@@ -426,31 +433,44 @@ struct Candidates {
       }
     }
     rc = -1;
-    sb = 0;
+    qd = 0;
     if (!(top > 0.0f)) return;
-    const unsigned char *q = rec + int64_t(r) * screen_rec_bytes(units) + 8;
-    const unsigned long long is_top = __ballot(lane < units && q[lane < units ? lane : 0] == 1);
+    const unsigned w = lane < units ? quads(r, lane) : 0u;
+    int g = -1;
+    for (int k = 3; k >= 0; --k)
+      if (((w >> (8 * k)) & 255u) == 1u) g = k;
+    const unsigned long long is_top = __ballot(g >= 0);
     if (!is_top) return;
     const int u = __ffsll(is_top) - 1;
     rc = r * P + u / per_c;
-    sb = u - (u / per_c) * per_c;
+    qd = 4 * (u - (u / per_c) * per_c) + __shfl(g, u, 64);
   }
-  // the units whose |G| can reach `amp` (< 0: any), into the bit masks
-  // cand[rc] of the work-group's threads t of n (cleared before)
+  // f(rc, unit of the sub-grid, quads of the unit as 4 bits) for every unit
+  // with a quad whose |G| can reach `amp` (< 0: any), units t, t + n, ...
+  template <typename F>
+  __device__ __forceinline__ void each(int t, int n, int P, float amp, F &&f) const {
+    for (int i = t; i < R * units; i += n) {
+      const int r = i / units, u = i - (i / units) * units;
+      const unsigned w = quads(r, u);
+      if (w == 0u) continue;
+      const float2 ab = bounds(r);
+      const bool known = ab.y < __builtin_inff();
+      unsigned bits = 0u;
+      for (int k = 0; k < 4; ++k) {
+        const unsigned v = (w >> (8 * k)) & 255u;
+        if (v != 0u && (!known || ab.x - float(v - 1) * ab.y >= amp * 0.99999f)) bits |= 1u << k;
+      }
+      if (bits) f(r * P + u / per_c, u - (u / per_c) * per_c, bits);
+    }
+  }
+  // the units of `each` as bit masks cand[rc] of the work-group's threads
+  // (cleared before)
   __device__ __forceinline__ void mark(int t, int n, int P, float amp, unsigned *cand) const {
     if (units == 0) {
       for (int i = t; i < R * P; i += n) cand[i] = (1u << per_c) - 1u;
       return;
     }
-    for (int i = t; i < R * units; i += n) {
-      const int r = i / units, u = i - (i / units) * units;
-      const unsigned char *q = rec + int64_t(r) * screen_rec_bytes(units);
-      const float2 ab = *reinterpret_cast<const float2 *>(q);
-      const unsigned v = q[8 + u];
-      if (v == 0) continue;
-      const bool known = ab.y < __builtin_inff();
-      if (!known || ab.x - float(v - 1) * ab.y >= amp * 0.99999f) atomicOr(&cand[r * P + u / per_c], 1u << (u % per_c));
-    }
+    each(t, n, P, amp, [&](int rc, int u, unsigned) { atomicOr(&cand[rc], 1u << u); });
   }
 };
 
@@ -467,50 +487,29 @@ struct Candidates {
 // reads and transforms only those rows (a kernel specialised to the IF
 // lattice when the search starts; the same sums).
 // CAND (M = 256): only the candidate units of the segment's screening
-// records are transformed.  The result is the full search's: the sub-grid
+// records are transformed, for the segments that find_kernel leaves (every
+// unit a candidate, or many).  The result is the full search's: the sub-grid
 // with the largest |G|^2 (all bits; then the lowest), its cells keyed; with
 // fewer than 8 (rate, sub-grid) pairs the keys alone decide.
 // BLK = 64: one wave per segment, for shapes whose SBD pass has at most 64
 // lanes' work (N x JB): in a work-group of 256 most threads would wait at its
 // barriers, while four independent waves need none.
-template <int J, int M, bool DUMP, bool CL, bool LIST = false, unsigned ROWS = 0u, bool CAND = false, int BLK = kBlock>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(J <= 64 && !DUMP && !LIST ? 3 : 1)))
-void fringe_kernel(FringeArgs a) {
-  static_assert(BLK == kBlock || (BLK == 64 && !DUMP && !LIST), "one wave per segment: plain and candidate searches");
+template <int J, int M, bool DUMP, bool CL, bool LIST, unsigned ROWS, bool CAND, int BLK>
+__device__ __forceinline__ void fringe_segment(const FringeArgs &a, int dl, int seg, int lb, int ld, int slot,
+                                               float2 *lds_all, float *red_v, int32_t *red_i) {
   using S = FringeShape<J, M, BLK>;
   constexpr int JA = S::JA, JB = S::JB, MA = S::MA, MB = S::MB, G = S::G, COLS = S::COLS;
   constexpr unsigned RMASK = ROWS ? ROWS : (MA >= 32 ? ~0u : (1u << MA) - 1u);
   constexpr int NW = BLK / 64;              // waves per segment
-  constexpr int PER = kBlock / BLK;         // segments per work-group
-  extern __shared__ float2 lds_all[];
-  __shared__ float red_v_all[kBlock / 64];
-  __shared__ int32_t red_i_all[kBlock / 64];
 
   const int N = a.n_if, R = a.n_rate, P = a.sbd_pad;
   const int PJ = P * J;
   const int NJ = N * J;
   const int t = threadIdx.x % BLK;
-  const int slot = PER > 1 ? __builtin_amdgcn_readfirstlane(int(threadIdx.x) / BLK) : 0;
-  float *const red_v = red_v_all + slot * NW;
-  int32_t *const red_i = red_i_all + slot * NW;
   auto sync = [&]() {
     if constexpr (BLK == kBlock) __syncthreads();
     else wave_lds_sync();
   };
-
-  // ---- which segment: spread consecutive segments over the 8 XCDs in
-  // contiguous ranges so that overlapping segments share an L2.
-  int dl, seg;
-  int lb = 0, ld = 0;
-  if constexpr (LIST) {
-    lb = a.seg_list[3 * blockIdx.x];
-    ld = a.seg_list[3 * blockIdx.x + 1];
-    seg = a.seg_list[3 * blockIdx.x + 2];
-    dl = lb * a.n_dm + ld;   // cube row
-  } else {
-    block_segment(a, DUMP, dl, seg, PER, slot);
-    if (PER > 1 && dl >= a.n_dt) return;   // (no barriers follow)
-  }
   int wi = 0;
   while (wi + 1 < a.n_win && a.win_off[wi + 1] <= seg) ++wi;
   const int l = a.win_len[wi];
@@ -684,6 +683,7 @@ void fringe_kernel(FringeArgs a) {
     int32_t run_i = 0x7fffffff;
     int rc0, sb0;
     cs.first(t & 63, P, rc0, sb0);
+    sb0 >>= 2;   // the quad's unit
     for (int it = rc0 >= 0 ? -1 : 0; it < R * P; ++it) {
       if (it == 0) {   // what the first unit leaves
         sync();   // cand is cleared
@@ -824,6 +824,260 @@ void fringe_kernel(FringeArgs a) {
     const int64_t o = int64_t(dl) * a.seg_total + seg;
     a.power[o] = bv >= 0.0f ? sqrtf(bv) : __builtin_nanf("");
     a.pidx[o] = bv >= 0.0f ? bi : -1;
+  }
+}
+
+// One work-group per segment of the tile (BLK = 64: per four segments); LIST:
+// per entry of a.seg_list; CAND: over the segments of a.left_list.
+template <int J, int M, bool DUMP, bool CL, bool LIST = false, unsigned ROWS = 0u, bool CAND = false, int BLK = kBlock>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(J <= 64 && !DUMP && !LIST ? 3 : 1)))
+void fringe_kernel(FringeArgs a) {
+  static_assert(BLK == kBlock || (BLK == 64 && !DUMP && !LIST && !CAND), "one wave per segment: plain searches");
+  constexpr int PER = kBlock / BLK;         // segments per work-group
+  extern __shared__ float2 lds_all[];
+  __shared__ float red_v[kBlock / 64];
+  __shared__ int32_t red_i[kBlock / 64];
+  const int slot = PER > 1 ? __builtin_amdgcn_readfirstlane(int(threadIdx.x) / BLK) : 0;
+  if constexpr (CAND) {
+    const int n = a.left_n ? *a.left_n : a.n_dt * a.seg_total;
+    for (int i = blockIdx.x; i < n; i += gridDim.x) {
+      const int at = a.left_n ? a.left_list[i] : i;
+      fringe_segment<J, M, DUMP, CL, LIST, ROWS, CAND, BLK>(a, at / a.seg_total, at % a.seg_total, 0, 0, slot, lds_all,
+                                                            red_v, red_i);
+      __syncthreads();
+    }
+  } else {
+    int dl, seg, lb = 0, ld = 0;
+    if constexpr (LIST) {
+      lb = a.seg_list[3 * blockIdx.x];
+      ld = a.seg_list[3 * blockIdx.x + 1];
+      seg = a.seg_list[3 * blockIdx.x + 2];
+      dl = lb * a.n_dm + ld;   // cube row
+    } else {
+      // spread runs of consecutive segments over the 8 XCDs so that
+      // overlapping segments share an L2
+      block_segment(a, DUMP, dl, seg, PER, slot);
+      if (PER > 1 && dl >= a.n_dt) return;   // (no barriers follow)
+    }
+    fringe_segment<J, M, DUMP, CL, LIST, ROWS, CAND, BLK>(a, dl, seg, lb, ld, slot, lds_all, red_v + slot * (BLK / 64),
+                                                          red_i + slot * (BLK / 64));
+  }
+}
+
+// ---------------------------------------------------- candidates of a segment
+// The screened float32 search (M = 256) of a segment by one wave: each
+// candidate quad by itself, in fringe_kernel's arithmetic.  Of the SBD
+// transform's J bins a quad needs four, which share one output of its second
+// pass: the first pass runs for every IF and stores its four outputs, the
+// second keeps one bin of each, and the MBD pass takes the four columns at
+// once, 16 lanes each.  A work-group per segment spent most of its time at the
+// barriers of two or three such candidates, of 16 bins each; a wave needs none,
+// and twelve segments are in flight on a CU.  What bounds it now is the latency
+// of a wave's own chain (records, spectra, two LDS transposes).  41184 segments
+// of 32 IFs x 64 channels, 8 rates: 1.76 -> 0.97 ms; 163840 of 8 IFs x 32
+// channels, one rate: 1.35 -> 0.69 ms.
+// Segments about which the records know nothing, or with so many candidates
+// that the whole transform is cheaper, go to a.left_list.
+constexpr int kFindScratch(int n_if, int jb, bool compact) {
+  const int t = n_if * 4 * (jb + 1), m = compact ? 0 : 4 * (256 + 16);
+  return t > m ? t : m;
+}
+constexpr int kFindStride(int n_if, int jb, bool compact, int masks) {   // float2 per wave
+  return kFindScratch(n_if, jb, compact) + (compact ? 16 : n_if + 1) * 5 + masks;
+}
+
+// The cells keep fringe_kernel's last bits: the values of a transform are
+// formed before one is chosen (left to itself the compiler moves additions
+// into the branches), and the twiddles of the first JA / 4 outputs add their
+// products in the order in which it adds them there.
+template <int NP>
+__device__ __forceinline__ void formed(float2 (&x)[NP]) {
+#pragma unroll
+  for (int i = 0; i < NP; ++i) asm volatile("" : "+v"(x[i].x), "+v"(x[i].y));
+}
+
+template <int J, bool CL, unsigned ROWS = 0u>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3)))
+void find_kernel(FringeArgs a) {
+  constexpr int M = 256, MA = 16, MB = 16, G = 16;
+  constexpr int JA = Split<J>::A, JB = Split<J>::B;
+  constexpr unsigned RMASK = ROWS ? ROWS : 0xFFFFu;
+  extern __shared__ float2 lds_all[];
+  const int N = a.n_if, R = a.n_rate, P = a.sbd_pad, PJ = P * J, NJ = N * J;
+  const int t = threadIdx.x & 63, slot = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+  int dl, seg;
+  block_segment(a, false, dl, seg, kBlock / 64, slot);
+  if (dl >= a.n_dt) return;
+  const int64_t at = int64_t(dl) * a.seg_total + seg;
+  float2 *const Sc = lds_all + slot * kFindStride(N, JB, CL, R * P);
+  float2 *const X = Sc + kFindScratch(N, JB, CL);   // [row][5], columns 0-3
+  unsigned long long *const quads = reinterpret_cast<unsigned long long *>(X + (CL ? 16 : N + 1) * 5);   // [R P]
+
+  // ---- candidates: leave the segment to fringe_kernel if nothing is known
+  const Candidates cs{a.screen + at * R * screen_rec_bytes(a.screen_units), R, a.screen_units, J / 16};
+  int rc0, qd0;
+  cs.first(t, P, rc0, qd0);
+  const bool unknown = __any(t < R && !(cs.bounds(t < R ? t : 0).y < __builtin_inff()));
+  auto leave = [&]() {
+    if (t == 0) a.left_list[atomicAdd(a.left_n, 1)] = int(at);
+  };
+  if (rc0 < 0 || unknown) {
+    leave();
+    return;
+  }
+  int wi = 0;
+  while (wi + 1 < a.n_win && a.win_off[wi + 1] <= seg) ++wi;
+  const int l = a.win_len[wi];
+  const int64_t k0 = a.win_k0[wi] + int64_t(seg - a.win_off[wi]) * a.win_hop[wi];
+  const float2 *wd = a.w + int64_t(dl) * a.w_dm_stride + k0 * NJ;
+  const float2 *rph = a.rate_ph + a.rate_off[wi];
+
+  for (int i = t; i < R * P; i += 64) quads[i] = 0ull;
+  for (int i = t; i < (CL ? 16 : N + 1) * 5; i += 64) X[i] = make_float2(0.f, 0.f);   // rows without an IF stay zero
+  const int grp = t / G, gl = t - grp * G;
+  float2 twm[16];
+  int rowoff[CL ? 1 : MA];
+  if constexpr (CL) {
+    static_for<0, MB>([&](auto i) { twm[decltype(i)::value] = a.tw_mbd[(gl * decltype(i)::value) & (M - 1)]; });
+  } else {
+    static_for<0, MA>([&](auto k) {
+      constexpr int kk = decltype(k)::value;
+      twm[kk] = a.tw_mbd[(gl * kk) & (M - 1)];
+      if constexpr ((RMASK >> kk) & 1u) rowoff[kk] = a.mbd_row[MB * kk + gl] * 5;
+    });
+  }
+  float2 *const Sg = Sc + grp * (MA * MB + 16);
+
+  const bool scan = R * P >= 8;   // (as in fringe_kernel)
+  unsigned top = 0u;              // largest |G|^2 (bits) so far and its (rate, sub-grid)
+  int top_rc = 0x7fffffff;
+  float run_v = -1.0f, best_v;    // the lane's keyed peak over what counts so far, and of this sub-grid
+  int32_t run_i = 0x7fffffff, best_i;
+
+  for (int it = -1; it < R * P; ++it) {
+    if (it == 0) {   // what the first quad leaves
+      wave_lds_sync();
+      int n_q = 0;
+      cs.each(t, 64, P, sqrtf(__uint_as_float(top)), [&](int rc, int u, unsigned bits) {
+        atomicOr(&quads[rc], (unsigned long long)bits << (4 * u));
+        n_q += __popc(bits);
+      });
+      for (int off = 32; off > 0; off >>= 1) n_q += __shfl_xor(n_q, off, 64);
+      const int all = R * P * (J / 4);
+      if (n_q > max(all / 6, min(all / 2, 16))) {
+        leave();
+        return;
+      }
+      wave_lds_sync();
+    }
+    const int rc = it < 0 ? rc0 : it;
+    // (the first quad's sub-grid: again with the first only if others are left)
+    unsigned long long mask = it < 0 ? 1ull << qd0 : quads[rc];
+    if (it >= 0 && rc == rc0 && mask == 1ull << qd0) mask = 0ull;
+    mask = (unsigned long long)unsigned(__builtin_amdgcn_readfirstlane(int(mask >> 32))) << 32 |
+           unsigned(__builtin_amdgcn_readfirstlane(int(mask)));
+    if (!mask) continue;
+    const int r = rc / P, c = rc - (rc / P) * P;
+    unsigned blk = 0u;
+    best_v = -1.0f;
+    best_i = 0x7fffffff;
+    for (; mask; mask &= mask - 1) {
+      const int qd = __ffsll(mask) - 1, a0 = 4 * qd;
+      const int kb = a0 & (JA - 1), k2 = a0 / JA;   // bins a0 .. a0 + 3 = kb .. kb + 3 of the first pass, k2 of the second
+      wave_lds_sync();
+      for (int v = t; v < N * JB; v += 64) {
+        const int n1 = v / JB, i2 = v - (v / JB) * JB;
+        float2 x[JA];
+        segment_sum<JA, JB>(x, wd, rph, r, N, J, l, R, true, n1, i2);
+        static_for<0, JA>([&](auto i) {
+          constexpr int ii = decltype(i)::value;
+          x[ii] = cmul(x[ii], a.pre_sbd[c * JA + ii]);
+        });
+        dft<JA>(x);
+        formed(x);
+        static_for<0, JA / 4>([&](auto b) {
+          constexpr int k0b = 4 * decltype(b)::value;
+          if (kb == k0b) {
+            static_for<0, 4>([&](auto i) {
+              constexpr int kk = k0b + decltype(i)::value;
+              const float2 w = a.tw_sbd[(i2 * (c + P * kk)) & (PJ - 1)];
+              const float2 y = cmul(x[kk], w);
+              Sc[(n1 * 4 + decltype(i)::value) * (JB + 1) + i2] =
+                  kk < JA / 4 ? make_float2(y.x, fmaf(x[kk].x, w.y, x[kk].y * w.x)) : y;
+            });
+          }
+        });
+      }
+      wave_lds_sync();
+      for (int v = t; v < N * 4; v += 64) {
+        const int n2 = v >> 2, i = v & 3;
+        float2 z[JB];
+        static_for<0, JB>([&](auto q) { z[decltype(q)::value] = Sc[(n2 * 4 + i) * (JB + 1) + decltype(q)::value]; });
+        dft<JB>(z);
+        formed(z);
+        const int xrow = CL ? a.mbd_pos[n2] : n2;
+        static_for<0, JB>([&](auto q) {
+          if (k2 == decltype(q)::value) X[xrow * 5 + i] = z[decltype(q)::value];
+        });
+      }
+      wave_lds_sync();
+      float2 z[MB];
+      if constexpr (CL) {
+        z[0] = X[grp];
+        static_for<1, MB>([&](auto i) {
+          constexpr int ii = decltype(i)::value;
+          z[ii] = cmul(X[ii * 5 + grp], twm[ii]);
+        });
+      } else {
+        float2 x[MA];
+        static_for<0, MA>([&](auto i) {
+          constexpr int ii = decltype(i)::value;
+          if constexpr ((RMASK >> ii) & 1u) x[ii] = X[rowoff[ii] + grp];
+          else x[ii] = make_float2(0.f, 0.f);
+        });
+        dft_masked<MA, RMASK>(x);
+        static_for<0, MA>([&](auto k) {
+          constexpr int kk = decltype(k)::value;
+          // w_M^(i2 k1) is 1 at k1 = 0
+          Sg[kk * MB + (gl ^ (kk & (MB - 1)))] = kk == 0 ? x[0] : cmul(x[kk], twm[kk]);
+        });
+        wave_lds_sync();
+        static_for<0, MB>([&](auto i) {
+          constexpr int ii = decltype(i)::value;
+          z[ii] = Sg[gl * MB + (ii ^ (gl & (MB - 1)))];
+        });
+      }
+      dft<MB>(z);
+      mbd_column_peak<M, MA, MB, false>(z, r, c, a0 + grp, gl, P, PJ, nullptr, best_v, best_i);
+      mbd_column_max<MB>(z, blk);
+    }
+    for (int off = 32; off > 0; off >>= 1) blk = max(blk, unsigned(__shfl_xor(int(blk), off, 64)));
+    const bool better = blk > top || (blk == top && rc < top_rc);
+    if (scan && better && rc != top_rc) {
+      run_v = best_v;
+      run_i = best_i;
+    } else if (!scan || rc == top_rc) {
+      if (best_v > run_v || (best_v == run_v && best_i < run_i)) {
+        run_v = best_v;
+        run_i = best_i;
+      }
+    }
+    if (better) {
+      top = blk;
+      top_rc = rc;
+    }
+  }
+  for (int off = 32; off > 0; off >>= 1) {
+    const float ov = __shfl_xor(run_v, off, 64);
+    const int32_t oi = __shfl_xor(run_i, off, 64);
+    if (ov > run_v || (ov == run_v && oi < run_i)) {
+      run_v = ov;
+      run_i = oi;
+    }
+  }
+  if (t == 0) {
+    a.power[at] = run_v >= 0.0f ? sqrtf(run_v) : __builtin_nanf("");
+    a.pidx[at] = run_v >= 0.0f ? run_i : -1;
   }
 }
 

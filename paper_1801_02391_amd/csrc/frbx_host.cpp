@@ -84,7 +84,7 @@ struct frbx_ctx {
   int specialise = 1;            // float32 general form: kernel compiled for the lattice's rows
   int sbd_mfma = 0;              // float16 form: SBD transform on the matrix cores as well
   unsigned rows_mask = 0;        // rows of the kernel in use (0: the statically built kernel)
-  hipFunction_t rows_fn = nullptr;
+  hipFunction_t rows_fn = nullptr, rows_find = nullptr;
   std::string rows_note;         // why the specialised kernel is not in use
   int scr_blocks = 0;            // screened search: work-groups of the screening pass (0: not screened),
   bool scr_half = false;         // its form, operand rows and the errors of its rounded matrices
@@ -401,14 +401,26 @@ bool many_segments(const frbx_ctx *c) {
 
 // The float32 search takes one wave per segment where the shape allows it and
 // the four segments of a work-group fit its LDS.
+// (A screened one has find_kernel.)
 bool use_wave(const frbx_ctx *c, bool screened) {
-  return frbx::fringe_wave(c->J, c->N) && many_segments(c) &&
-         frbx::fringe_lds_bytes(c->J, c->n_mbd, c->N, c->sbd_pad, true, screened ? c->n_rate * c->sbd_pad : 0) <= 80 * 1024;
+  return !screened && frbx::fringe_wave(c->J, c->N) && many_segments(c) &&
+         frbx::fringe_lds_bytes(c->J, c->n_mbd, c->N, c->sbd_pad, true) <= 80 * 1024;
 }
 
 size_t fringe_lds(const frbx_ctx *c, bool screened) {
   return frbx::fringe_lds_bytes(c->J, c->n_mbd, c->N, c->sbd_pad, use_wave(c, screened),
                                 screened ? c->n_rate * c->sbd_pad : 0);
+}
+
+// A screened float32 search evaluates its candidates with find_kernel up to 64
+// channels.  With more, a quad's first pass takes the wave two to four rounds
+// per rate, and fringe_kernel evaluates the candidates of every segment: 32
+// IFs x 128 channels 1.92 against 2.44 ms per tile, 16 x 256 1.5 against 2.5.
+bool use_find(const frbx_ctx *c) { return c->precision == FRBX_PREC_F32 && c->J <= 64; }
+
+size_t find_lds(const frbx_ctx *c) {
+  if (!use_find(c)) return 0;
+  return frbx::find_lds_bytes(c->J, c->N, c->n_rate * c->sbd_pad, !c->mbd_pos.empty());
 }
 
 // The halved MBD product: more than 16 IFs, at most 16 of them on even and 16
@@ -436,7 +448,7 @@ bool use_screen(const frbx_ctx *c, int tiles) {
   if (use_gemm(c) || !frbx::screen_supported(c->J, c->n_mbd, c->N, c->n_rate, half, tiles, c->sbd_pad)) return false;
   if (c->n_rate * c->sbd_pad * c->J / 16 < (tiles < 16 ? 8 : 16) || !many_segments(c)) return false;
   if (c->precision == FRBX_PREC_F16 && !(half && c->J <= 64)) return false;
-  if (c->precision == FRBX_PREC_F32) return fringe_lds(c, true) <= 150 * 1024;
+  if (c->precision == FRBX_PREC_F32) return fringe_lds(c, true) <= 150 * 1024 && find_lds(c) <= 150 * 1024;
   const size_t lds = frbx::fringe_mfma_lds_bytes(c->J, c->N, c->sbd_pad, c->precision == FRBX_PREC_F16X3 ? 3 : 1);
   return lds + size_t(c->n_rate) * c->sbd_pad * 4 <= 150 * 1024;
 }
@@ -793,7 +805,7 @@ frbx_status prepare(frbx_ctx *c) {
   // first MBD pass that hold an IF (the same sums, only those rows read
   // and transformed); the statically built kernel when every row holds an
   // IF or the run-time compiler cannot build it.
-  c->rows_fn = nullptr;
+  c->rows_fn = c->rows_find = nullptr;
   c->rows_mask = 0;
   c->rows_note.clear();
   const int MB = frbx::fringe_compact_rows(M);
@@ -804,7 +816,7 @@ frbx_status prepare(frbx_ctx *c) {
     const unsigned all = MA >= 32 ? ~0u : (1u << MA) - 1u;
     if (rows != all) {
       c->rows_fn = frbx::fringe_rows_kernel(c->device, J, M, rows, c->scr_blocks > 0, use_wave(c, c->scr_blocks > 0),
-                                            &c->rows_note);
+                                            &c->rows_find, &c->rows_note);
       if (c->rows_fn) c->rows_mask = rows;
     }
   }
@@ -1384,8 +1396,13 @@ frbx_status recheck_pass(frbx_ctx *c, const PassSpec &ps, frbx::StatsArgs &st, s
 }
 
 // bytes of the screening records of one DM trial of S segments
+// Screening records of S segments, and for find_kernel their part of the list
+// of those that it leaves (an int each; their number
+// is in kLeftCount bytes of its own).
+constexpr size_t kLeftCount = 256;
 size_t rec_bytes(const frbx_ctx *c, int64_t S) {
-  return size_t(S) * c->n_rate * frbx::screen_rec_bytes(c->sbd_pad * c->J / 16);
+  return size_t(S) * (size_t(c->n_rate) * frbx::screen_rec_bytes(c->sbd_pad * c->J / 16) +
+                      (use_find(c) ? sizeof(int32_t) : 0));
 }
 
 // Dedispersion and fringe search of every (baseline, DM tile): the DM
@@ -1406,6 +1423,12 @@ frbx_status search_tiles(frbx_ctx *c, const PassSpec &ps, float2 *wbuf, int dt, 
   const size_t lds = fringe_lds(c, screened);
   const float scale = mfma_scale(c);
   const size_t in_bytes = ps.vis_f16 ? 4 : 8;
+  int32_t *left_list = nullptr, *left_n = nullptr;
+  if (screened && rec && use_find(c)) {
+    left_n = reinterpret_cast<int32_t *>(rec);
+    left_list = left_n + kLeftCount / sizeof(int32_t);
+    rec = reinterpret_cast<unsigned char *>(left_list) + size_t(dt) * S * sizeof(int32_t) + (size_t(dt) * S & 1) * sizeof(int32_t);
+  }
   if (S > 0 && k_eff > 0) {
     const int nb = std::max(1, dt / D);   // baselines per tile
     for (int b = 0; b < B; b += nb) {
@@ -1426,6 +1449,7 @@ frbx_status search_tiles(frbx_ctx *c, const PassSpec &ps, float2 *wbuf, int dt, 
           da.k_eff = k_eff;
           da.nj = NJ;
           da.group = c->dd_group;
+          da.zero = left_n;
           sp = c->span_begin(1, int64_t(n_d) * k_eff);
           if (sp >= 0) {
             // writes: n_d x k_eff spectra; reads: each channel's span of
@@ -1502,10 +1526,23 @@ frbx_status search_tiles(frbx_ctx *c, const PassSpec &ps, float2 *wbuf, int dt, 
           sa.rec = rec;
           if ((s = c->hip(frbx::launch_screen(J, sa, c->scr_blocks, c->stream), "screening launch")) != FRBX_OK) return s;
         }
-        const hipError_t le =
-            use_mfma    ? launch_matrix_core(c, fa, int(ndt * S))
-            : c->rows_fn ? frbx::launch_fringe_rows(c->rows_fn, fa, wave, lds, int(ndt * S), c->stream)
-                         : frbx::launch_fringe(J, M, fa, wave, lds, int(ndt * S), c->stream);
+        const int n_seg = int(ndt * S);
+        hipError_t le = hipSuccess;
+        if (use_mfma) {
+          le = launch_matrix_core(c, fa, n_seg);
+        } else {
+          int grid = n_seg, per = wave ? 4 : 1;
+          if (left_n) {
+            fa.left_list = left_list;
+            fa.left_n = left_n;
+            le = c->rows_fn ? frbx::launch_fringe_rows(c->rows_find, fa, 4, find_lds(c), n_seg, c->stream)
+                            : frbx::launch_find(J, fa, find_lds(c), n_seg, c->stream);
+            grid = std::min(n_seg, frbx::kLeftBlocks);
+          }
+          if (le == hipSuccess)
+            le = c->rows_fn ? frbx::launch_fringe_rows(c->rows_fn, fa, per, lds, grid, c->stream)
+                            : frbx::launch_fringe(J, M, fa, wave, lds, grid, c->stream);
+        }
         if ((s = c->hip(le, "fringe launch")) != FRBX_OK) return s;
         c->span_end(sp);
       }
@@ -1544,7 +1581,7 @@ frbx_status device_pass(frbx_ctx *c, const PassSpec &ps, std::vector<DevCrossing
   unsigned char *rec = nullptr;
   if (c->scr_blocks > 0 && S * c->dt * per_seg <= (int64_t(1) << 31) - 1) {
     const std::string msg = c->err;
-    if (ensure(c, c->d_rec, c->rec_cap, rec_bytes(c, S) * c->dt) == FRBX_OK) rec = c->d_rec;
+    if (ensure(c, c->d_rec, c->rec_cap, rec_bytes(c, S) * c->dt + kLeftCount + 8) == FRBX_OK) rec = c->d_rec;
     else c->err = msg, (void)hipGetLastError();
   }
   const size_t cube = size_t(B) * D * std::max<int64_t>(S, 1);
@@ -1686,12 +1723,14 @@ frbx_status frbx_run_cube_noalloc(frbx_ctx *c, float *power, int32_t *idx, int64
                                      " bytes) exceeds the no-alloc workspace (" +
                                      std::to_string(frbx::kNoAllocBytes) + " bytes)");
   // screening records behind the tiles, where both fit
+  constexpr size_t kMost = frbx::kNoAllocBytes - kLeftCount - 8;
   const size_t per_rec = c->scr_blocks > 0 ? (rec_bytes(c, S) + 255) & ~size_t(255) : 0;
   const int64_t per_seg = c->scr_blocks > 0 ? c->n_rate : 1;
-  const bool rec_fit = per_rec > 0 && per_dm + per_rec <= frbx::kNoAllocBytes && S * per_seg <= (int64_t(1) << 31) - 1;
-  int dt = int(std::min<size_t>(size_t(D), frbx::kNoAllocBytes / (per_dm + (rec_fit ? per_rec : 0))));
+  const bool rec_fit = per_rec > 0 && per_dm + per_rec <= kMost && S * per_seg <= (int64_t(1) << 31) - 1;
+  int dt = int(std::min<size_t>(size_t(D), rec_fit ? kMost / (per_dm + per_rec) : frbx::kNoAllocBytes / per_dm));
   while (dt > 1 && int64_t(dt) * S * (rec_fit ? per_seg : 1) > (int64_t(1) << 31) - 1) dt /= 2;
-  dt = whole_baselines(c, dt, per_dm + (rec_fit ? per_rec : 0), S * (rec_fit ? per_seg : 1), frbx::kNoAllocBytes);
+  dt = whole_baselines(c, dt, per_dm + (rec_fit ? per_rec : 0), S * (rec_fit ? per_seg : 1),
+                       rec_fit ? kMost : frbx::kNoAllocBytes);
   if (int64_t(dt) * S > (int64_t(1) << 31) - 1) return c->fail(FRBX_E_INVAL, "too many segments per DM trial");
   const int nw = int(c->windows.size());
   PassSpec ps;

@@ -44,6 +44,7 @@ struct DedisperseArgs {
   float2 *out;         // [n_dt][k_eff][NJ]
   int64_t k_eff;       // K - dk_max
   int32_t nj;          // N * J
+  int32_t *zero;       // set to 0 by the launch (may be null)
   int32_t group;       // DM trials sharing one staged input tile (>= 1); the
                        // AP offsets of a group differ by < kDedispSpread
 };
@@ -111,6 +112,10 @@ struct FringeArgs {
   int32_t screened;
   const unsigned char *screen;
   int32_t screen_units;      // P J / 16; 0: no records, every unit is a candidate
+  // segments (d n_seg + segment) that find_kernel leaves to fringe_kernel:
+  // their list and number (null: all of them)
+  int32_t *left_list;
+  int32_t *left_n;
   // matrix-core SBD transform (float16 form): the real-embedded J-point DFT
   // matrix as MFMA A operands, [2J/16 row tiles][J/16 K chunks][64 lanes] x
   // 8 halves
@@ -125,11 +130,12 @@ struct FringeArgs {
 constexpr int kScreenWaves = 8;          // waves per work-group
 constexpr int kScreenUnitsMax = 64;
 // One record per (segment, rate): float T and float step, then one byte per
-// unit: 0 where the unit cannot hold the segment's largest |G|, else v >= 1
-// with its |G| at most T - (v - 1) step, 1 for the largest screened unit.
+// quad (SBD bins a = 4 q .. 4 q + 3 of a sub-grid; four quads to a unit): 0
+// where the quad cannot hold the segment's largest |G|, else v >= 1 with its
+// |G| at most T - (v - 1) step, 1 for the largest screened quad.
 // step = +inf: nothing is known (not finite, zero or extreme input) and
-// every unit is a candidate.
-constexpr int screen_rec_bytes(int units) { return 8 + ((units + 7) & ~7); }
+// every quad is a candidate.
+constexpr int screen_rec_bytes(int units) { return 8 + ((4 * units + 7) & ~7); }
 
 struct ScreenArgs {
   const float2 *w;           // [n_dt][k_eff][NJ], as for the fringe search
@@ -188,6 +194,11 @@ hipError_t launch_fringe(int n_chan, int n_mbd, const FringeArgs &a, bool wave, 
                          int grid, hipStream_t s);
 size_t fringe_lds_bytes(int n_chan, int n_mbd, int n_if, int sbd_pad, bool wave = false, int masks = 0);
 bool fringe_wave(int n_chan, int n_if);
+// Float32 search of a screened tile: find_kernel on every segment of the
+// tile, then fringe_kernel on those it leaves.
+hipError_t launch_find(int n_chan, const FringeArgs &a, size_t lds_bytes, int n_seg, hipStream_t s);
+size_t find_lds_bytes(int n_chan, int n_if, int masks, bool compact);
+constexpr int kLeftBlocks = 1024;   // work-groups of fringe_kernel over the list
 bool fringe_supported(int n_chan, int n_mbd, int n_if, int sbd_pad);
 // Lattice rows of the compact MBD form for n_mbd points (0 if unsupported).
 int fringe_compact_rows(int n_mbd);
@@ -308,9 +319,11 @@ hipError_t noalloc_workspace(int device, void **ptr);
 // frbx_jit.cpp).  The first call for a (device, n_chan, n_mbd, rows)
 // compiles and loads it; later calls return the loaded function.  nullptr
 // with the reason in *err when it cannot be built.
+// screened: *find receives the find_kernel of the same rows.
 hipFunction_t fringe_rows_kernel(int device, int n_chan, int n_mbd, unsigned rows, bool screened, bool wave,
-                                 std::string *err);
-hipError_t launch_fringe_rows(hipFunction_t fn, const FringeArgs &a, bool wave, size_t lds_bytes, int grid,
+                                 hipFunction_t *find, std::string *err);
+// per: segments per work-group (1 or 4)
+hipError_t launch_fringe_rows(hipFunction_t fn, const FringeArgs &a, int per, size_t lds_bytes, int grid,
                               hipStream_t s);
 #endif  // !__HIPCC_RTC__
 

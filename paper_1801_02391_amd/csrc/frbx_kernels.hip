@@ -73,6 +73,7 @@ __global__ __launch_bounds__(kBlock) void dedisperse_kernel(DedisperseArgs a) {
   constexpr int SW = kDedispAp + kDedispSpread + 1;   // staged APs per channel (+1 pad)
   __shared__ float2 tile[kDedispCh][SW];
   __shared__ int32_t shs[kDedispMaxGroup][kDedispCh];  // offset of trial g0 + j minus trial g0's
+  if (a.zero && threadIdx.x == 0 && (blockIdx.x | blockIdx.y | blockIdx.z) == 0) *a.zero = 0;
   const int64_t kt = int64_t(blockIdx.x) * kDedispAp;
   const int ct = blockIdx.y * kDedispCh;
   const int g0 = blockIdx.z * a.group;                  // first trial of the group (tile-local)
@@ -444,6 +445,7 @@ void fringe_mfma_kernel(FringeArgs a) {
     for (int i = t; i < R * P; i += kBlock) cand[i] = 0u;
     int rc0, sb0, cur_r = -1;
     cs.first(lane, P, rc0, sb0);
+    sb0 >>= 2;   // the quad's unit
     for (int it = rc0 >= 0 ? -1 : 0; it < R * P; ++it) {
       if (it == 0) {   // what the first unit leaves
         float amp = -1.0f;
@@ -1253,20 +1255,22 @@ struct LaunchFn {
   size_t lds;
   int grid;
   hipStream_t s;
-  template <int J, int M, bool CL, bool CAND> hipError_t plain() {
+  template <int J, int M, bool CL> hipError_t plain() {
     if constexpr (J <= 64)
-      if (wave) return launch_fringe_t<J, M, false, CL, false, CAND, 64>(a, lds, grid, s);
-    return launch_fringe_t<J, M, false, CL, false, CAND>(a, lds, grid, s);
+      if (wave) return launch_fringe_t<J, M, false, CL, false, false, 64>(a, lds, grid, s);
+    return launch_fringe_t<J, M, false, CL>(a, lds, grid, s);
   }
   template <int J, int M> hipError_t operator()() {
     if (a.screened) {
-      if constexpr (M == 256 && J >= 16) return a.mbd_pos ? plain<J, M, true, true>() : plain<J, M, false, true>();
+      if constexpr (M == 256 && J >= 16)
+        return a.mbd_pos ? launch_fringe_t<J, M, false, true, false, true>(a, lds, grid, s)
+                         : launch_fringe_t<J, M, false, false, false, true>(a, lds, grid, s);
       return hipErrorInvalidValue;
     }
     if (a.dump)
       return a.mbd_pos ? launch_fringe_t<J, M, true, true>(a, lds, grid, s)
                        : launch_fringe_t<J, M, true, false>(a, lds, grid, s);
-    return a.mbd_pos ? plain<J, M, true, false>() : plain<J, M, false, false>();
+    return a.mbd_pos ? plain<J, M, true>() : plain<J, M, false>();
   }
   hipError_t fail() { return hipErrorInvalidValue; }
 };
@@ -1297,12 +1301,41 @@ struct SupportFn {
 
 hipError_t launch_fringe(int n_chan, int n_mbd, const FringeArgs &a, bool wave, size_t lds_bytes, int grid,
                          hipStream_t s) {
-  if (wave && (a.dump || !fringe_wave(n_chan, a.n_if))) return hipErrorInvalidValue;
+  if (wave && (a.dump || a.screened || !fringe_wave(n_chan, a.n_if))) return hipErrorInvalidValue;
   return dispatch(n_chan, n_mbd, LaunchFn{a, wave, lds_bytes, grid, s});
 }
 
 size_t fringe_lds_bytes(int n_chan, int n_mbd, int n_if, int sbd_pad, bool wave, int masks) {
   return dispatch(n_chan, n_mbd, LdsFn{n_if, sbd_pad, wave, masks});
+}
+
+template <int J, bool CL>
+static hipError_t launch_find_t(const FringeArgs &a, size_t lds, int n_seg, hipStream_t s) {
+  (void)hipGetLastError();
+  if (lds > 64 * 1024) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&find_kernel<J, CL>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+    if (e != hipSuccess) return e;
+  }
+  constexpr int PER = kBlock / 64;
+  hipLaunchKernelGGL((find_kernel<J, CL>), dim3((n_seg + PER - 1) / PER), dim3(kBlock), lds, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_find(int n_chan, const FringeArgs &a, size_t lds, int n_seg, hipStream_t s) {
+  if (n_seg <= 0) return hipSuccess;
+  if (!a.screen || a.screen_units < 1 || !a.left_list || !a.left_n || a.dump) return hipErrorInvalidValue;
+  switch (n_chan) {
+    case 16: return a.mbd_pos ? launch_find_t<16, true>(a, lds, n_seg, s) : launch_find_t<16, false>(a, lds, n_seg, s);
+    case 32: return a.mbd_pos ? launch_find_t<32, true>(a, lds, n_seg, s) : launch_find_t<32, false>(a, lds, n_seg, s);
+    case 64: return a.mbd_pos ? launch_find_t<64, true>(a, lds, n_seg, s) : launch_find_t<64, false>(a, lds, n_seg, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+size_t find_lds_bytes(int n_chan, int n_if, int masks, bool compact) {
+  const int jb = n_chan <= 32 ? 4 : 8;   // Split<n_chan>::B
+  return size_t(kFindStride(n_if, jb, compact, masks)) * sizeof(float2) * (kBlock / 64);
 }
 
 bool fringe_wave(int n_chan, int n_if) {

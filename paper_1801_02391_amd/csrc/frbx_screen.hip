@@ -57,18 +57,21 @@ __device__ __forceinline__ h8_t pack(const float (&re)[4], const float (&im)[4])
 }
 
 // Largest value of the wave, in every lane (v >= 0: its bits order like it).
+template <int C>
+__device__ __forceinline__ unsigned dpp_max(unsigned m) {
+  return max(m, unsigned(__builtin_amdgcn_update_dpp(0, int(m), C, 0xf, 0xf, true)));
+}
+// largest (as bits) of the 16 lanes of a row, in all of them
+__device__ __forceinline__ unsigned row_max16(float v) {
+  unsigned m = dpp_max<0xb1>(__float_as_uint(v));   // quad_perm 1 0 3 2
+  m = dpp_max<0x4e>(m);                             // quad_perm 2 3 0 1
+  m = dpp_max<0x141>(m);                            // row_half_mirror
+  return dpp_max<0x140>(m);                         // row_mirror
+}
 __device__ __forceinline__ float wave_max(float v) {
-  unsigned m = __float_as_uint(v);
-  auto step = [&](auto ctrl) {
-    constexpr int c = decltype(ctrl)::value;
-    m = max(m, unsigned(__builtin_amdgcn_update_dpp(0, int(m), c, 0xf, 0xf, true)));
-  };
-  step(Index<0xb1>{});    // quad_perm 1 0 3 2
-  step(Index<0x4e>{});    // quad_perm 2 3 0 1
-  step(Index<0x141>{});   // row_half_mirror
-  step(Index<0x140>{});   // row_mirror
-  step(Index<0x142>{});   // row_bcast15
-  step(Index<0x143>{});   // row_bcast31
+  unsigned m = row_max16(v);
+  m = dpp_max<0x142>(m);   // row_bcast15
+  m = dpp_max<0x143>(m);   // row_bcast31
   return __uint_as_float(unsigned(__builtin_amdgcn_readlane(int(m), 63)));
 }
 
@@ -415,7 +418,7 @@ void screen_kernel(ScreenArgs a) {
     // outside this range |G|^2 could leave the float32 range
     if (!(s1 < 1e15f) || !(s1 > 1e-12f)) {
       if (lane == 0) *reinterpret_cast<float2 *>(rec) = make_float2(0.f, __builtin_inff());
-      if (lane < units) rec[8 + lane] = 1;
+      if (lane < units) reinterpret_cast<unsigned *>(rec + 8)[lane] = 0x01010101u;
       continue;
     }
     // power-of-two scale with row_max * scale < 2^15
@@ -435,7 +438,10 @@ void screen_kernel(ScreenArgs a) {
       ya[nt][p] = pack(re, im);
     });
 
-    float mine = 0.f;   // largest |G|^2 of unit `lane`
+    // QUADS: largest |G|^2 (bits) of quad g of the units 16 k + row; else of
+    // unit `lane`, for its four quads
+    constexpr bool QUADS = RX <= 4;
+    unsigned keep[QUADS ? 4 : 1] = {};
     float x2 = 0.f;     // largest sum of |X|^2 over this lane's IFs
     h8_t b[NK][2], bn[NK][2];   // MBD operands of a tile (tile 0 here and after every pass) and the next
     auto operand = [&](int ct, h8_t (&o)[NK][2]) {
@@ -562,11 +568,24 @@ void screen_kernel(ScreenArgs a) {
           b[q / 2][q % 2] = bn[q / 2][q % 2];
         });
       }
-      static_for<0, U>([&](auto ui) {
-        constexpr int u = decltype(ui)::value;
-        const float m = wave_max(mx[u]);
-        mine = lane == c0 * RX + u ? m : mine;
-      });
+      if constexpr (QUADS) {
+        // a lane's powers are of the quad g of the unit; U divides 16
+        unsigned part = 0u;
+        static_for<0, U>([&](auto ui) {
+          constexpr int u = decltype(ui)::value;
+          const unsigned m = row_max16(mx[u]);
+          part = row == ((c0 * RX + u) & 15) ? m : part;
+        });
+        static_for<0, 4>([&](auto k) {
+          if ((c0 * RX) >> 4 == decltype(k)::value) keep[decltype(k)::value] = max(keep[decltype(k)::value], part);
+        });
+      } else {
+        static_for<0, U>([&](auto ui) {
+          constexpr int u = decltype(ui)::value;
+          const unsigned m = __float_as_uint(wave_max(mx[u]));
+          keep[0] = lane == c0 * RX + u ? m : keep[0];
+        });
+      }
     }
     // |screened G - G| <= eps_y sum |y| + eps_x sqrt(N) max_s |X(s)|_2 + ...
     x2 = fmaxf(x2, __shfl_xor(x2, 1, 64));
@@ -576,14 +595,24 @@ void screen_kernel(ScreenArgs a) {
     x2 += __shfl_xor(x2, 16, 64);
     x2 += __shfl_xor(x2, 32, 64);
     const float bound = a.eps_y * s1 * sc + a.eps_x * sqrtf(x2 * float(N)) + a.abs_scaled + a.abs_plain * sc;
-    // the record: a unit with screened maximum u has |G| <= gamma (u + bound);
+    // the record: a quad with screened maximum u has |G| <= gamma (u + bound);
     // it counts where that reaches A - bound, below the segment's largest |G|
-    const float A = sqrtf(wave_max(mine));
+    unsigned most = keep[0];
+    if constexpr (QUADS) most = max(max(keep[0], keep[1]), max(keep[2], keep[3]));
+    const float A = sqrtf(wave_max(__uint_as_float(most)));
     const float width = A + bound - (A - bound) / a.gamma;
     if (lane == 0) *reinterpret_cast<float2 *>(rec) = make_float2(a.gamma * (A + bound) / sc, a.gamma * width / (254.f * sc));
-    if (lane < units) {
-      const float d = (A - sqrtf(mine)) * (254.f / width);
-      rec[8 + lane] = d <= 254.f ? (unsigned char)(1 + int(d)) : (unsigned char)0;
+    auto mark = [&](unsigned v) {
+      const float d = (A - sqrtf(__uint_as_float(v))) * (254.f / width);
+      return d <= 254.f ? 1u + unsigned(d) : 0u;
+    };
+    if constexpr (QUADS) {
+      static_for<0, 4>([&](auto k) {
+        constexpr int kk = decltype(k)::value;
+        if (16 * kk + row < units) rec[8 + 4 * (16 * kk + row) + g] = (unsigned char)mark(keep[kk]);
+      });
+    } else {
+      if (lane < units) reinterpret_cast<unsigned *>(rec + 8)[lane] = mark(keep[0]) * 0x01010101u;
     }
   }
 }

@@ -136,3 +136,23 @@ def test_screened_search_of_zeros_and_non_finite_samples(precision):
     assert np.array_equal(~np.isfinite(Pn[0, 0]), hit)
     if precision == "f32":   # (the float16 operand scale follows the largest finite component)
         assert np.array_equal(Pn[0, 0, ~hit], P[0, 0, ~hit]) and np.array_equal(In[0, 0, ~hit], I[0, 0, ~hit])
+
+
+@pytest.mark.parametrize("name,J", [("5if-compact", 16), ("16if-compact", 32), ("9if-compact", 64), ("17if", 16),
+                                    ("3if-spread", 32), ("32if-vgos", 64)])
+def test_segments_with_few_and_with_all_cells_alike(name, J):
+    """Noise first (a few candidates per segment, evaluated one by one), then
+    one channel only, where |G| is the same in every SBD bin and a segment is
+    searched as a whole: the segments of one tile go both ways."""
+    f0, windows = LATTICES[name], [1, 3]
+    note(f"screen alike {name} J={J}")
+    V = _noise(len(f0), J, 70, 17)
+    V[:, :, : J // 2 + 1, 35:] = 0.0
+    V[:, :, J // 2 + 2 :, 35:] = 0.0
+    s = _search(f0, J, 4, 3, "f32", V, windows)
+    _check(s, windows)
+    P, I = s.power_cube()
+    p, i = torch.empty(P.size, device="cuda:0"), torch.empty(P.size, dtype=torch.int32, device="cuda:0")
+    assert s.run_cube_noalloc(p, i) == P.size
+    torch.cuda.synchronize()
+    assert np.array_equal(p.cpu().numpy(), P.ravel()) and np.array_equal(i.cpu().numpy(), I.ravel())
