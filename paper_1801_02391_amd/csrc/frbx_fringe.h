@@ -239,10 +239,14 @@ __host__ __device__ inline void fringe_lds_plan(int n_if, int sbd_pad, int &x_of
 
 // ------------------------------------------------------- shared fringe steps
 // Which segment a work-group handles.  Work-groups are dealt to the 8 XCDs
-// round-robin; every XCD gets runs of kXcdRun consecutive ones, so that
-// overlapping segments share an L2 and the windows of a DM trial (longer
-// windows cost more) are spread over all XCDs.
-constexpr int kXcdRun = 32;
+// round-robin; in sweeps over the XCDs each gets a run of kXcdRun consecutive
+// ones, so that overlapping segments share an L2.  Which XCD takes which run
+// of a sweep varies from sweep to sweep: the windows of a DM trial cost more
+// the longer they are, and a trial of about 256 segments would otherwise give
+// one XCD the longest of every trial.  Fewer than kXcdSweeps sweeps do not even
+// that out and go one by one (1265 segments of 16 IFs x 256 channels: 3.86 ms
+// in runs, 3.3 ms one by one).
+constexpr int kXcdRun = 32, kXcdSweeps = 16;
 // A work-group that takes `per` segments takes consecutive ones (slot w).
 __device__ __forceinline__ void block_segment(const FringeArgs &a, bool dump, int &dl, int &seg, int per = 1,
                                               int w = 0) {
@@ -254,9 +258,9 @@ __device__ __forceinline__ void block_segment(const FringeArgs &a, bool dump, in
   const int nb = gridDim.x;
   const int bx = blockIdx.x;
   const int i = bx >> 3;
-  const int run = bx < nb / (8 * kXcdRun) * (8 * kXcdRun)
-                      ? ((i / kXcdRun) * 8 + (bx & 7)) * kXcdRun + i % kXcdRun
-                      : bx;
+  const int sweeps = nb / (8 * kXcdRun), sweep = i / kXcdRun;
+  const int turn = int(unsigned(sweep) * 0x9E3779B1u >> 29);   // (any spread-out sequence of 0 to 7)
+  const int run = sweeps >= kXcdSweeps && sweep < sweeps ? (sweep * 8 + ((bx + turn) & 7)) * kXcdRun + i % kXcdRun : bx;
   const int lb = run * per + w;
   dl = lb / a.seg_total;
   seg = lb - dl * a.seg_total;

@@ -395,8 +395,10 @@ bool use_gemm(const frbx_ctx *c) {
 // times over (grids set for a run shorter than the stream's chunks: unknown,
 // taken as enough).  A search of 978 segments takes 219 us with a work-group
 // per segment and no screening pass, 223 us with a wave each and one.
-bool many_segments(const frbx_ctx *c) {
-  return c->seg_total <= 0 || int64_t(c->B) * c->n_dm * c->seg_total >= 4096;
+// (A screening pass has n_rate tasks per segment: 1265 segments with 13 rates
+// of 16 IFs x 256 channels take 1.4 ms screened, 3.3 without.)
+bool many_segments(const frbx_ctx *c, int per = 1) {
+  return c->seg_total <= 0 || int64_t(c->B) * c->n_dm * c->seg_total * per >= 4096;
 }
 
 // The float32 search takes one wave per segment where the shape allows it and
@@ -437,7 +439,7 @@ bool screen_half(const frbx_ctx *c) {
 // shape (and the candidate masks fit beside the kernel's LDS plan) and a
 // segment has enough units: with 16 the candidates are a tenth of the search,
 // with 8 on a coarse MBD grid (one rate, 32 channels, sbd_pad 4: 8 IFs x 1 s x
-// 64 DM trials 3.19 -> 2.46 ms, the paper's set-up x 20 s 1.59 -> 1.29 ms) a
+// 64 DM trials 3.04 -> 1.72 ms, the paper's set-up x 20 s 1.59 -> 0.95 ms) a
 // fifth; on the full grid the pass itself then costs what it saves.  The
 // float16 form's own products are the screening pass's but for the halved MBD
 // product, so it is screened only where that applies, up to 64 channels (one
@@ -446,7 +448,7 @@ bool screen_half(const frbx_ctx *c) {
 bool use_screen(const frbx_ctx *c, int tiles) {
   const bool half = screen_half(c);
   if (use_gemm(c) || !frbx::screen_supported(c->J, c->n_mbd, c->N, c->n_rate, half, tiles, c->sbd_pad)) return false;
-  if (c->n_rate * c->sbd_pad * c->J / 16 < (tiles < 16 ? 8 : 16) || !many_segments(c)) return false;
+  if (c->n_rate * c->sbd_pad * c->J / 16 < (tiles < 16 ? 8 : 16) || !many_segments(c, c->n_rate)) return false;
   if (c->precision == FRBX_PREC_F16 && !(half && c->J <= 64)) return false;
   if (c->precision == FRBX_PREC_F32) return fringe_lds(c, true) <= 150 * 1024 && find_lds(c) <= 150 * 1024;
   const size_t lds = frbx::fringe_mfma_lds_bytes(c->J, c->N, c->sbd_pad, c->precision == FRBX_PREC_F16X3 ? 3 : 1);

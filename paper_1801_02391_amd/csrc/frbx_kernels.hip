@@ -6,7 +6,8 @@
 //                      segment sums of the fringe kernel read whole spectra.
 //                      HBM-bound; LDS-tiled transpose, coalesced both ways.
 //   fringe_kernel      Eq. 5 with the Eq. 4 rate term, Sec. 5.1: one
-//                      work-group per segment; for each rate bin it forms the
+//                      work-group (small shapes: one wave) per segment; for
+//                      each rate bin it forms the
 //                      segment sums in registers, runs the zero-padded SBD
 //                      transform per IF as P sub-DFTs of J points (two
 //                      in-register passes with an LDS transpose), then the
@@ -15,7 +16,12 @@
 //                      transpose; one pass for compact IF lattices) and
 //                      keeps the peak of |G|^2.  VALU-bound.  List launches
 //                      search selected segments, gathering their sums from
-//                      the input (re-evaluation near the threshold).
+//                      the input (re-evaluation near the threshold);
+//                      candidate launches only the units that the screening
+//                      pass (frbx_screen.hip) leaves standing.
+//   find_kernel        those candidates of the float32 search up to 64
+//                      channels, four SBD bins at a time, one wave per
+//                      segment.
 //   fringe_mfma_kernel the same search with the MBD transform as a
 //                      real-embedded complex GEMM on the matrix cores (float16
 //                      operands, float32 accumulation; one product, or three

@@ -4,13 +4,17 @@
 // The search keeps one number per segment, the largest |G| over (rate, SBD,
 // MBD), so all but a few cells are needed only to know that they are smaller.
 // screen_kernel evaluates every cell in float16 (float32 accumulation) and
-// reports, per segment and rate, the units (16 SBD bins of one sub-grid x
-// all MBD bins) whose largest |G| lies within twice a rigorous error bound
-// of the rate's largest; the search's own kernel then evaluates those units,
-// in its own arithmetic, and nothing else.  Since the bound covers every
-// rounding of this pass, the unit that holds the search's maximum is always
-// among them and the search's result is what it is without this pass, bit
-// for bit.
+// reports, per segment and rate, the quads (4 SBD bins of one sub-grid x all
+// MBD bins; from 128 channels on units of 16 bins) whose largest |G| lies
+// within twice a rigorous error bound of the rate's largest; the search's own
+// kernel then evaluates those, in its own arithmetic, and nothing else.  Since
+// the bound covers every rounding of this pass, the cell that is the search's
+// maximum is always among them and the search's result is what it is without
+// this pass, bit for bit.
+//
+// Matrix-core bound (power): 41184 segments of 32 IFs x 64 channels with 8
+// rates take 4.8 ms, 1.1 PFLOP/s of products, the rate of an 8192^3 library
+// product on this card; evaluating every cell in float32 took 14.0 ms.
 //
 // Both transforms are real-embedded complex GEMMs chained in registers:
 //   SBD  X[n][s] = sum_j y[n][j] w_PJ^(j s): A = the segment sums (rows n, K =
