@@ -170,7 +170,11 @@ frbx_status frbx_set_detection(frbx_ctx *ctx, double threshold, int32_t n_win_mi
  * of the stream buffer).  0 (default) = 6 GiB, at least one trial per tile.
  * A positive budget below one trial's tile makes the search fail with
  * FRBX_E_NOMEM (the message gives both sizes); an allocation that the device
- * refuses returns FRBX_E_NOMEM as well.  FRBX_E_INVAL for bytes < 0. */
+ * refuses returns FRBX_E_NOMEM as well.  The records of the screening pass
+ * (see frbx_set_precision: about n_rate x (12 + sbd_pad x n_chan / 4) bytes
+ * per segment of a tile) are allocated beside the tiles; where the device
+ * refuses them every cell is evaluated without that pass, with the same
+ * results.  FRBX_E_INVAL for bytes < 0. */
 frbx_status frbx_set_tile_budget(frbx_ctx *ctx, int64_t bytes);
 
 /* Arithmetic of the fringe transform.
@@ -179,7 +183,12 @@ frbx_status frbx_set_tile_budget(frbx_ctx *ctx, int64_t bytes);
  *                       lattice position lies within one row of the first
  *                       MBD pass (16 positions at n_mbd = 256) after a
  *                       common shift, that pass is skipped (a phase factor
- *                       on G; |G| is unchanged).
+ *                       on G; |G| is unchanged).  Searches of many segments
+ *                       (4096 or more) on n_mbd = 256 grids run a float16
+ *                       matrix-core pass first that only rules cells out, by
+ *                       a bound on its own error; every reported power and
+ *                       cell is evaluated in float32 as described.  The
+ *                       other forms do the same where it is faster.
  *   FRBX_PREC_F16X3     float32 segment sums and SBD transform; the MBD
  *                       transform on the matrix cores as three float16
  *                       products (high x high + high x low + low x high of a
