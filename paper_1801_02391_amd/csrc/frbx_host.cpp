@@ -577,7 +577,15 @@ ScreenTables screen_tables(const frbx_ctx *c, int grid_tiles) {
 // 2^-11 the float16 rounding:
 //   eps_y sum |y|: the sums rounded (u) against the rounded SBD matrix
 //   (Cauchy-Schwarz over each lane's channels: err_s), float32 accumulation
-//   of both products (2 x 128 terms) and the float32 search's own rounding;
+//   of both products (2 x 128 terms) and the float32 search's own rounding
+//   of its transforms;
+//   eps_y eps_sum l q for each of a lane's 4 RX NK channels: the two ways of
+//   adding up a segment's APs.  With q the largest component of any partial
+//   sum, a term is at most sqrt(8) q, a component of it 2 q; per AP and
+//   component nested FMAs round values of at most q + sqrt(8) q and q, a
+//   complex product (its parts rounded one by one) and an addition
+//   2 sqrt(8) q, 2 q and q: 13.5 q 2^-24, times sqrt(2) for both components
+//   (20 with what the two partial sums themselves differ by);
 //   eps_x sqrt(N) max |X|_2 >= (u + err_m) sum |X|: X rounded against the
 //   rounded MBD matrix; twice u more where the search's form rounds both;
 //   absolute: float16 operands below 2^-14, taken as lost, in units of this
@@ -593,6 +601,7 @@ void screen_bounds(const frbx_ctx *c, float scale, frbx::ScreenArgs &sa) {
     sa.abs_plain = known ? float(c->N * tiny / scale) : std::numeric_limits<float>::infinity();
   }
   sa.eps_y = float((u + c->scr_err_s) * 1.002 + 5e-5);
+  sa.eps_sum = float(20.0 * std::ldexp(1.0, -24) * 4 * (c->J / 16) * (c->N <= 16 ? 1 : 2) / sa.eps_y);
   sa.eps_x = float(ex * 1.005);
   sa.abs_scaled = float(c->N * (c->J + 1) * tiny);
 }

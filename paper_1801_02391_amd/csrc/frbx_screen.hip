@@ -266,7 +266,7 @@ void screen_kernel(ScreenArgs a) {
       task = int(at);
     }
     const int sg = task / R, r = task - sg * R;
-    int l;
+    int l = 1;
     const float2 *wd, *ph;
     if constexpr (!RING) {
       segment(sg, l, wd, ph);
@@ -276,6 +276,11 @@ void screen_kernel(ScreenArgs a) {
     // ---- segment sums (Eq. 3 with the Eq. 4 rotation): lane (row, g) holds
     // row 16 nt + row, channels RX (4 h + g) + p, h < 4: y[nt][p][2 h + re/im]
     float y[NK][RX][8];
+    // largest component of any of them after any AP, the j = 0 point's apart:
+    // what the float32 rounding of the sums scales with (far above the sums
+    // themselves where the APs of a window cancel)
+    float sum_max = 0.f, sum_max0 = 0.f;
+    auto grow = [](float &m, float re, float im) { m = fmaxf(fmaxf(m, fabsf(re)), fabsf(im)); };
     if constexpr (RING) {
       static_for<0, NK * RX * 8>([&](auto kk) {
         constexpr int q = decltype(kk)::value;
@@ -291,6 +296,7 @@ void screen_kernel(ScreenArgs a) {
         asm volatile("" ::: "memory");
         fetch_next();
         if (use.sg == sg && live) {
+          l = use.l;
           const char *sl = ring + use_at * SL::STRIDE;
           const float2 *pw = reinterpret_cast<const float2 *>(sl + SL::BYTES + wave * 256);
           const float4 *rows = reinterpret_cast<const float4 *>(sl);
@@ -311,6 +317,8 @@ void screen_kernel(ScreenArgs a) {
                 o[1] = fmaf(x.x, w.y, fmaf(x.y, w.x, o[1]));
                 o2[0] = fmaf(x.z, w.x, fmaf(-x.w, w.y, o2[0]));
                 o2[1] = fmaf(x.z, w.y, fmaf(x.w, w.x, o2[1]));
+                grow(pp == 0 && h == 0 ? sum_max0 : sum_max, o[0], o[1]);
+                grow(sum_max, o2[0], o2[1]);
               });
             });
           };
@@ -376,10 +384,12 @@ void screen_kernel(ScreenArgs a) {
           float *o = &y[nt][2 * pp < RX ? 2 * pp : 0][2 * h];
           o[0] = fmaf(x.x, w.x, SET ? -x.y * w.y : fmaf(-x.y, w.y, o[0]));
           o[1] = fmaf(x.x, w.y, SET ? x.y * w.x : fmaf(x.y, w.x, o[1]));
+          grow(pp == 0 && h == 0 ? sum_max0 : sum_max, o[0], o[1]);
           if constexpr (RX > 1) {
             float *o2 = &y[nt][2 * pp + 1 < RX ? 2 * pp + 1 : 0][2 * h];
             o2[0] = fmaf(x.z, w.x, SET ? -x.w * w.y : fmaf(-x.w, w.y, o2[0]));
             o2[1] = fmaf(x.z, w.y, SET ? x.w * w.x : fmaf(x.w, w.x, o2[1]));
+            grow(sum_max, o2[0], o2[1]);
           }
         });
       });
@@ -414,13 +424,21 @@ void screen_kernel(ScreenArgs a) {
       row_max = fmaxf(row_max, t);
       s1 += t;
     });
+    // the rounding of the sums, in units of eps_y: a.eps_sum l for every
+    // channel's largest partial sum (screen_bounds)
+    sum_max = g == 0 ? sum_max : fmaxf(sum_max, sum_max0);
+    if (NK == 1 && rif[0] < 0) sum_max = 0.f;
+    sum_max += __shfl_xor(sum_max, 16, 64);
+    sum_max += __shfl_xor(sum_max, 32, 64);
+    float s1p = fmaf(a.eps_sum * float(l), sum_max, s1);
     for (int o = 8; o > 0; o >>= 1) {
       s1 += __shfl_xor(s1, o, 64);
+      s1p += __shfl_xor(s1p, o, 64);
       row_max = fmaxf(row_max, __shfl_xor(row_max, o, 64));
     }
     unsigned char *rec = a.rec + int64_t(task) * screen_rec_bytes(units);
     // outside this range |G|^2 could leave the float32 range
-    if (!(s1 < 1e15f) || !(s1 > 1e-12f)) {
+    if (!(s1p < 1e15f) || !(s1 > 1e-12f)) {
       if (lane == 0) *reinterpret_cast<float2 *>(rec) = make_float2(0.f, __builtin_inff());
       if (lane < units) reinterpret_cast<unsigned *>(rec + 8)[lane] = 0x01010101u;
       continue;
@@ -591,14 +609,14 @@ void screen_kernel(ScreenArgs a) {
         });
       }
     }
-    // |screened G - G| <= eps_y sum |y| + eps_x sqrt(N) max_s |X(s)|_2 + ...
+    // |screened G - G| <= eps_y (sum |y| + rounding of the sums) + eps_x sqrt(N) max_s |X(s)|_2 + ...
     x2 = fmaxf(x2, __shfl_xor(x2, 1, 64));
     x2 = fmaxf(x2, __shfl_xor(x2, 2, 64));
     x2 = fmaxf(x2, __shfl_xor(x2, 4, 64));
     x2 = fmaxf(x2, __shfl_xor(x2, 8, 64));
     x2 += __shfl_xor(x2, 16, 64);
     x2 += __shfl_xor(x2, 32, 64);
-    const float bound = a.eps_y * s1 * sc + a.eps_x * sqrtf(x2 * float(N)) + a.abs_scaled + a.abs_plain * sc;
+    const float bound = a.eps_y * s1p * sc + a.eps_x * sqrtf(x2 * float(N)) + a.abs_scaled + a.abs_plain * sc;
     // the record: a quad with screened maximum u has |G| <= gamma (u + bound);
     // it counts where that reaches A - bound, below the segment's largest |G|
     unsigned most = keep[0];
