@@ -844,8 +844,8 @@ void fringe_kernel(FringeArgs a) {
   const int slot = PER > 1 ? __builtin_amdgcn_readfirstlane(int(threadIdx.x) / BLK) : 0;
   if constexpr (CAND) {
     const int n = a.left_n ? *a.left_n : a.n_dt * a.seg_total;
-    for (int i = blockIdx.x; i < n; i += gridDim.x) {
-      const int at = a.left_n ? a.left_list[i] : i;
+    for (int64_t i = blockIdx.x; i < n; i += gridDim.x) {
+      const int at = a.left_n ? a.left_list[i] : int(i);
       fringe_segment<J, M, DUMP, CL, LIST, ROWS, CAND, BLK>(a, at / a.seg_total, at % a.seg_total, 0, 0, slot, lds_all,
                                                             red_v, red_i);
       __syncthreads();

@@ -21,6 +21,7 @@
 
 #include "../../include/frbx.h"
 #include "frbx_internal.h"
+#include "frbx_plan.h"
 
 using frbx::DevCrossing;
 
@@ -1562,17 +1563,6 @@ frbx_status search_tiles(frbx_ctx *c, const PassSpec &ps, float2 *wbuf, int dt, 
   return FRBX_OK;
 }
 
-// A tile that holds every DM trial of a baseline takes further baselines as
-// long as it stays within `most` bytes (and its tasks within an int): few
-// trials of a short scan would otherwise be one small launch per baseline.
-int whole_baselines(const frbx_ctx *c, int dt, size_t per_dm, int64_t per_trial, size_t most) {
-  const int D = c->n_dm;
-  if (dt < D || per_dm == 0) return dt;
-  int nb = int(std::min<size_t>(size_t(c->B), std::max<size_t>(1, most / (per_dm * size_t(D)))));
-  while (nb > 1 && int64_t(nb) * D * per_trial > (int64_t(1) << 31) - 1) --nb;
-  return nb * D;
-}
-
 frbx_status device_pass(frbx_ctx *c, const PassSpec &ps, std::vector<DevCrossing> &hc) {
   frbx_status s;
   const int B = c->B, D = c->n_dm, NJ = c->N * c->J, nw = int(c->windows.size());
@@ -1582,15 +1572,14 @@ frbx_status device_pass(frbx_ctx *c, const PassSpec &ps, std::vector<DevCrossing
   if (c->w_budget_strict && per_dm * sizeof(float2) > c->w_budget)
     return c->fail(FRBX_E_NOMEM, "tile budget of " + std::to_string(c->w_budget) + " bytes is below one DM trial's " +
                                      "dedispersed tile (" + std::to_string(per_dm * sizeof(float2)) + " bytes)");
-  c->dt = per_dm ? int(std::max<size_t>(1, std::min<size_t>(D, c->w_budget / (per_dm * sizeof(float2))))) : 1;
   // (a screened tile has n_rate tasks per segment)
   const int64_t per_seg = c->scr_blocks > 0 ? c->n_rate : 1;
-  while (c->dt > 1 && int64_t(c->dt) * S * per_seg > (int64_t(1) << 31) - 1) c->dt /= 2;
-  c->dt = whole_baselines(c, c->dt, per_dm * sizeof(float2), S * per_seg, std::min(c->w_budget, kTileBaselines));
+  c->dt = frbx::tile_trials(c->w_budget, per_dm * sizeof(float2), D, S * per_seg);
+  c->dt = frbx::whole_baselines(c->dt, per_dm * sizeof(float2), D, B, S * per_seg, std::min(c->w_budget, kTileBaselines));
   if ((s = ensure(c, c->d_w, c->w_cap, per_dm * c->dt)) != FRBX_OK) return s;
   // the screening records; without memory for them every unit is evaluated
   unsigned char *rec = nullptr;
-  if (c->scr_blocks > 0 && S * c->dt * per_seg <= (int64_t(1) << 31) - 1) {
+  if (c->scr_blocks > 0 && S * c->dt * per_seg <= frbx::kLaunchMost) {
     const std::string msg = c->err;
     if (ensure(c, c->d_rec, c->rec_cap, rec_bytes(c, S) * c->dt + kLeftCount + 8) == FRBX_OK) rec = c->d_rec;
     else c->err = msg, (void)hipGetLastError();
@@ -1737,12 +1726,11 @@ frbx_status frbx_run_cube_noalloc(frbx_ctx *c, float *power, int32_t *idx, int64
   constexpr size_t kMost = frbx::kNoAllocBytes - kLeftCount - 8;
   const size_t per_rec = c->scr_blocks > 0 ? (rec_bytes(c, S) + 255) & ~size_t(255) : 0;
   const int64_t per_seg = c->scr_blocks > 0 ? c->n_rate : 1;
-  const bool rec_fit = per_rec > 0 && per_dm + per_rec <= kMost && S * per_seg <= (int64_t(1) << 31) - 1;
-  int dt = int(std::min<size_t>(size_t(D), rec_fit ? kMost / (per_dm + per_rec) : frbx::kNoAllocBytes / per_dm));
-  while (dt > 1 && int64_t(dt) * S * (rec_fit ? per_seg : 1) > (int64_t(1) << 31) - 1) dt /= 2;
-  dt = whole_baselines(c, dt, per_dm + (rec_fit ? per_rec : 0), S * (rec_fit ? per_seg : 1),
-                       rec_fit ? kMost : frbx::kNoAllocBytes);
-  if (int64_t(dt) * S > (int64_t(1) << 31) - 1) return c->fail(FRBX_E_INVAL, "too many segments per DM trial");
+  const bool rec_fit = per_rec > 0 && per_dm + per_rec <= kMost && S * per_seg <= frbx::kLaunchMost;
+  const size_t most = rec_fit ? kMost : frbx::kNoAllocBytes, per_trial = per_dm + (rec_fit ? per_rec : 0);
+  const int64_t tasks = S * (rec_fit ? per_seg : 1);
+  int dt = frbx::tile_trials(most, per_trial, D, tasks);
+  dt = frbx::whole_baselines(dt, per_trial, D, c->B, tasks, most);
   const int nw = int(c->windows.size());
   PassSpec ps;
   ps.vis = c->d_vis;
