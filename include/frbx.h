@@ -164,17 +164,20 @@ frbx_status frbx_set_windows(frbx_ctx *ctx, const int32_t *len_frames, int32_t n
 frbx_status frbx_set_detection(frbx_ctx *ctx, double threshold, int32_t n_win_min,
                                int32_t n_bl_min);
 
-/* Device memory for the dedispersed DM tiles of frbx_run / frbx_stream_push,
- * in bytes: the DM trials are dedispersed floor(bytes / tile) at a time, one
- * trial's tile being (K - dk_max) x N x J x 8 bytes (K: the APs of the run or
- * of the stream buffer).  0 (default) = 6 GiB, at least one trial per tile.
- * A positive budget below one trial's tile makes the search fail with
- * FRBX_E_NOMEM (the message gives both sizes); an allocation that the device
- * refuses returns FRBX_E_NOMEM as well.  The records of the screening pass
- * (see frbx_set_precision: about n_rate x (12 + sbd_pad x n_chan / 4) bytes
- * per segment of a tile) are allocated beside the tiles; where the device
- * refuses them every cell is evaluated without that pass, with the same
- * results.  FRBX_E_INVAL for bytes < 0. */
+/* Device memory for the dedispersed DM tiles of frbx_run / frbx_stream_push
+ * and the records of their screening pass, in bytes: the DM trials are
+ * searched floor(bytes / trial) at a time, a trial being (K - dk_max) x N x J
+ * x 8 bytes of spectra (K: the APs of the run or of the stream buffer) and,
+ * where the search is screened (see frbx_set_precision), n_rate x (8 +
+ * sbd_pad x n_chan / 4) + 4 bytes of records per segment.  0 (default) =
+ * 6 GiB, at least one trial per tile.  A positive budget below one trial's
+ * spectra makes the search fail with FRBX_E_NOMEM (the message gives both
+ * sizes); an allocation that the device refuses returns FRBX_E_NOMEM as
+ * well.  Records that do not fit beside one trial's spectra, or that the
+ * device refuses, only cost the screening: every cell is then evaluated, with
+ * the same results; records held from an earlier search are given back when
+ * another allocation of the context needs their memory.  FRBX_E_INVAL for
+ * bytes < 0. */
 frbx_status frbx_set_tile_budget(frbx_ctx *ctx, int64_t bytes);
 
 /* Arithmetic of the fringe transform.

@@ -267,6 +267,20 @@ struct frbx_ctx {
 
 namespace {
 
+// hipMalloc for a context.  Where the device refuses, the screening records,
+// which a search can do without, are given back first.
+template <typename T>
+hipError_t dev_alloc(frbx_ctx *c, T **p, size_t bytes) {
+  hipError_t e = hipMalloc(reinterpret_cast<void **>(p), bytes);
+  if (e != hipSuccess && c->d_rec) {
+    dfree(c->d_rec);   // (waits for kernels that use them)
+    c->rec_cap = 0;
+    (void)hipGetLastError();
+    e = hipMalloc(reinterpret_cast<void **>(p), bytes);
+  }
+  return e;
+}
+
 frbx_status check_layout(const frbx_layout *L, std::string &why) {
   if (!L) return why = "layout is NULL", FRBX_E_INVAL;
   if (L->n_baselines < 1 || L->n_if < 1 || L->n_frames < 1)
@@ -711,7 +725,7 @@ frbx_status prepare(frbx_ctx *c) {
     dfree(dptr);
     const size_t bytes = vec.size() * sizeof(vec[0]);
     if (bytes == 0) return FRBX_OK;
-    if (hipMalloc(reinterpret_cast<void **>(&dptr), bytes) != hipSuccess)
+    if (dev_alloc(c, &dptr, bytes) != hipSuccess)
       return c->fail(FRBX_E_NOMEM, "device allocation of a table failed");
     return c->hip(hipMemcpy(dptr, vec.data(), bytes, hipMemcpyHostToDevice), "table upload");
   };
@@ -853,7 +867,7 @@ frbx_status ensure(frbx_ctx *c, T *&p, size_t &cap, size_t need) {
   dfree(p);
   cap = 0;
   if (need == 0) return FRBX_OK;
-  if (hipMalloc(reinterpret_cast<void **>(&p), need * sizeof(T)) != hipSuccess)
+  if (dev_alloc(c, &p, need * sizeof(T)) != hipSuccess)
     return c->fail(FRBX_E_NOMEM, "device allocation failed");
   cap = need;
   return FRBX_OK;
@@ -1170,7 +1184,7 @@ static frbx_status load_impl(frbx_ctx *c, const void *vis, int is_device, int f1
     c->d_vis = vis;
   } else {
     dfree(c->d_vis_own);
-    if (hipMalloc(&c->d_vis_own, bytes) != hipSuccess)
+    if (dev_alloc(c, &c->d_vis_own, bytes) != hipSuccess)
       return c->fail(FRBX_E_NOMEM, "device allocation for the cross spectra failed");
     frbx_status s = c->hip(hipMemcpyAsync(c->d_vis_own, vis, bytes, hipMemcpyHostToDevice, c->stream),
                            "upload of cross spectra");
@@ -1183,7 +1197,7 @@ static frbx_status load_impl(frbx_ctx *c, const void *vis, int is_device, int f1
 
 // largest component, for the float16 operand scale of the matrix-core forms
 static frbx_status finish_load(frbx_ctx *c, size_t n_cplx, int f16) {
-  if (!c->d_absmax && hipMalloc(reinterpret_cast<void **>(&c->d_absmax), sizeof(unsigned int)) != hipSuccess)
+  if (!c->d_absmax && dev_alloc(c, &c->d_absmax, sizeof(unsigned int)) != hipSuccess)
     return c->fail(FRBX_E_NOMEM, "device allocation failed");
   unsigned int am = 0;
   frbx_status s = c->hip(hipMemsetAsync(c->d_absmax, 0, sizeof(unsigned int), c->stream), "memset");
@@ -1217,7 +1231,7 @@ frbx_status frbx_load_e4m3(frbx_ctx *c, const void *codes, const float *scale, i
       return s;
     src = c->stage;
     dfree(c->d_scale);
-    if (hipMalloc(reinterpret_cast<void **>(&c->d_scale), size_t(rows) * sizeof(float)) != hipSuccess)
+    if (dev_alloc(c, &c->d_scale, size_t(rows) * sizeof(float)) != hipSuccess)
       return c->fail(FRBX_E_NOMEM, "device allocation failed");
     if ((s = c->hip(hipMemcpyAsync(c->d_scale, scale, size_t(rows) * sizeof(float), hipMemcpyHostToDevice, c->stream),
                     "scale upload")) != FRBX_OK)
@@ -1226,7 +1240,7 @@ frbx_status frbx_load_e4m3(frbx_ctx *c, const void *codes, const float *scale, i
   }
   // decoded exactly into an owned complex64 copy, searched like frbx_load's input
   dfree(c->d_vis_own);
-  if (hipMalloc(&c->d_vis_own, n_cplx * sizeof(float2)) != hipSuccess)
+  if (dev_alloc(c, &c->d_vis_own, n_cplx * sizeof(float2)) != hipSuccess)
     return c->fail(FRBX_E_NOMEM, "device allocation for the cross spectra failed");
   if ((s = c->hip(frbx::launch_ingest(src, FRBX_IN_E4M3, sc, c->K, rows, static_cast<float2 *>(c->d_vis_own), c->K, 0,
                                       c->stream), "fp8 decode")) != FRBX_OK)
@@ -1331,7 +1345,7 @@ frbx_status stats_pass(frbx_ctx *c, frbx::StatsArgs &st, size_t rows, int64_t S,
     if (int64_t(ncr) <= c->cross_cap) break;
     dfree(c->d_cross);
     c->cross_cap = 0;
-    if (hipMalloc(reinterpret_cast<void **>(&c->d_cross), size_t(ncr) * sizeof(DevCrossing)) != hipSuccess)
+    if (dev_alloc(c, &c->d_cross, size_t(ncr) * sizeof(DevCrossing)) != hipSuccess)
       return c->fail(FRBX_E_NOMEM, "device allocation for crossings failed");
     c->cross_cap = int64_t(ncr);
     st.out = c->d_cross;
@@ -1407,11 +1421,11 @@ frbx_status recheck_pass(frbx_ctx *c, const PassSpec &ps, frbx::StatsArgs &st, s
   return c->hip(frbx::launch_fringe_list(J, M, fa, lds, int(n), c->stream), "recheck launch");
 }
 
-// bytes of the screening records of one DM trial of S segments
 // Screening records of S segments, and for find_kernel their part of the list
-// of those that it leaves (an int each; their number
-// is in kLeftCount bytes of its own).
-constexpr size_t kLeftCount = 256;
+// of those that it leaves (an int each).  The number of the list's entries
+// stands before it (kLeftCount bytes), and the records after it at a multiple
+// of 8 bytes (kRecExtra in all).
+constexpr size_t kLeftCount = 256, kRecExtra = kLeftCount + 8;
 size_t rec_bytes(const frbx_ctx *c, int64_t S) {
   return size_t(S) * (size_t(c->n_rate) * frbx::screen_rec_bytes(c->sbd_pad * c->J / 16) +
                       (use_find(c) ? sizeof(int32_t) : 0));
@@ -1573,33 +1587,49 @@ frbx_status device_pass(frbx_ctx *c, const PassSpec &ps, std::vector<DevCrossing
     return c->fail(FRBX_E_NOMEM, "tile budget of " + std::to_string(c->w_budget) + " bytes is below one DM trial's " +
                                      "dedispersed tile (" + std::to_string(per_dm * sizeof(float2)) + " bytes)");
   // (a screened tile has n_rate tasks per segment)
-  const int64_t per_seg = c->scr_blocks > 0 ? c->n_rate : 1;
-  c->dt = frbx::tile_trials(c->w_budget, per_dm * sizeof(float2), D, S * per_seg);
-  c->dt = frbx::whole_baselines(c->dt, per_dm * sizeof(float2), D, B, S * per_seg, std::min(c->w_budget, kTileBaselines));
-  if ((s = ensure(c, c->d_w, c->w_cap, per_dm * c->dt)) != FRBX_OK) return s;
-  // the screening records; without memory for them every unit is evaluated
-  unsigned char *rec = nullptr;
-  if (c->scr_blocks > 0 && S * c->dt * per_seg <= frbx::kLaunchMost) {
-    const std::string msg = c->err;
-    if (ensure(c, c->d_rec, c->rec_cap, rec_bytes(c, S) * c->dt + kLeftCount + 8) == FRBX_OK) rec = c->d_rec;
-    else c->err = msg, (void)hipGetLastError();
-  }
+  const frbx::TilePlan tp =
+      frbx::plan_tiles(c->w_budget, c->w_budget_strict, kTileBaselines, per_dm * sizeof(float2),
+                       c->scr_blocks > 0 ? rec_bytes(c, S) : 0, kRecExtra, D, B, S, c->n_rate);
+  c->dt = tp.dt;
   const size_t cube = size_t(B) * D * std::max<int64_t>(S, 1);
-  if ((s = ensure(c, c->d_power, c->cube_cap, cube)) != FRBX_OK) return s;
-  if ((s = ensure(c, c->d_pidx, c->pidx_cap, cube)) != FRBX_OK) return s;
   const size_t rows = size_t(B) * D * nw;
-  if ((s = ensure(c, c->d_mean, c->mean_cap, rows)) != FRBX_OK) return s;
-  if ((s = ensure(c, c->d_sd, c->sd_cap, rows)) != FRBX_OK) return s;
-  if ((s = ensure(c, c->d_cnt, c->cnt_cap, rows)) != FRBX_OK) return s;
-  if (!c->d_ncross && hipMalloc(reinterpret_cast<void **>(&c->d_ncross), sizeof(unsigned long long)) != hipSuccess)
-    return c->fail(FRBX_E_NOMEM, "device allocation failed");
   const int64_t want_cap = std::max<int64_t>(int64_t(1) << 16, int64_t(cube / 64));
-  if (c->cross_cap < want_cap) {
-    dfree(c->d_cross);
-    c->cross_cap = 0;
-    if (hipMalloc(reinterpret_cast<void **>(&c->d_cross), size_t(want_cap) * sizeof(DevCrossing)) != hipSuccess)
+  // what a run cannot do without
+  auto allocate = [&]() -> frbx_status {
+    if ((s = ensure(c, c->d_w, c->w_cap, per_dm * c->dt)) != FRBX_OK) return s;
+    if ((s = ensure(c, c->d_power, c->cube_cap, cube)) != FRBX_OK) return s;
+    if ((s = ensure(c, c->d_pidx, c->pidx_cap, cube)) != FRBX_OK) return s;
+    if ((s = ensure(c, c->d_mean, c->mean_cap, rows)) != FRBX_OK) return s;
+    if ((s = ensure(c, c->d_sd, c->sd_cap, rows)) != FRBX_OK) return s;
+    if ((s = ensure(c, c->d_cnt, c->cnt_cap, rows)) != FRBX_OK) return s;
+    if (!c->d_ncross && dev_alloc(c, &c->d_ncross, sizeof(unsigned long long)) != hipSuccess)
       return c->fail(FRBX_E_NOMEM, "device allocation failed");
-    c->cross_cap = want_cap;
+    if (c->cross_cap < want_cap) {
+      dfree(c->d_cross);
+      c->cross_cap = 0;
+      if (dev_alloc(c, &c->d_cross, size_t(want_cap) * sizeof(DevCrossing)) != hipSuccess)
+        return c->fail(FRBX_E_NOMEM, "device allocation failed");
+      c->cross_cap = want_cap;
+    }
+    return FRBX_OK;
+  };
+  const std::string msg = c->err;
+  s = allocate();
+  if (s == FRBX_E_NOMEM && c->dt > D) {   // one baseline a tile
+    c->err = msg;
+    (void)hipGetLastError();
+    dfree(c->d_w);
+    c->w_cap = 0;
+    c->dt = D;
+    s = allocate();
+  }
+  if (s != FRBX_OK) return s;
+  // and the screening records, after it; without memory for them every unit
+  // is evaluated
+  unsigned char *rec = nullptr;
+  if (tp.records) {
+    if (ensure(c, c->d_rec, c->rec_cap, rec_bytes(c, S) * c->dt + kRecExtra) == FRBX_OK) rec = c->d_rec;
+    else c->err = msg, (void)hipGetLastError();
   }
   const bool use_mfma = c->precision != FRBX_PREC_F32;
   if ((s = search_tiles(c, ps, c->d_w, c->dt, rec, c->d_power, c->d_pidx)) != FRBX_OK) return s;
@@ -1723,14 +1753,8 @@ frbx_status frbx_run_cube_noalloc(frbx_ctx *c, float *power, int32_t *idx, int64
                                      " bytes) exceeds the no-alloc workspace (" +
                                      std::to_string(frbx::kNoAllocBytes) + " bytes)");
   // screening records behind the tiles, where both fit
-  constexpr size_t kMost = frbx::kNoAllocBytes - kLeftCount - 8;
-  const size_t per_rec = c->scr_blocks > 0 ? (rec_bytes(c, S) + 255) & ~size_t(255) : 0;
-  const int64_t per_seg = c->scr_blocks > 0 ? c->n_rate : 1;
-  const bool rec_fit = per_rec > 0 && per_dm + per_rec <= kMost && S * per_seg <= frbx::kLaunchMost;
-  const size_t most = rec_fit ? kMost : frbx::kNoAllocBytes, per_trial = per_dm + (rec_fit ? per_rec : 0);
-  const int64_t tasks = S * (rec_fit ? per_seg : 1);
-  int dt = frbx::tile_trials(most, per_trial, D, tasks);
-  dt = frbx::whole_baselines(dt, per_trial, D, c->B, tasks, most);
+  const frbx::TilePlan tp = frbx::plan_tiles(frbx::kNoAllocBytes, true, frbx::kNoAllocBytes, per_dm,
+                                             c->scr_blocks > 0 ? rec_bytes(c, S) : 0, kRecExtra, D, c->B, S, c->n_rate);
   const int nw = int(c->windows.size());
   PassSpec ps;
   ps.vis = c->d_vis;
@@ -1744,8 +1768,8 @@ frbx_status frbx_run_cube_noalloc(frbx_ctx *c, float *power, int32_t *idx, int64
   // no timing events (their pool may grow): launches only
   const bool tm = c->timing;
   c->timing = false;
-  unsigned char *rec = rec_fit ? static_cast<unsigned char *>(c->d_noalloc) + size_t(dt) * per_dm : nullptr;
-  const frbx_status s = search_tiles(c, ps, static_cast<float2 *>(c->d_noalloc), dt, rec, power, idx);
+  unsigned char *rec = tp.records ? static_cast<unsigned char *>(c->d_noalloc) + size_t(tp.dt) * per_dm : nullptr;
+  const frbx_status s = search_tiles(c, ps, static_cast<float2 *>(c->d_noalloc), tp.dt, rec, power, idx);
   c->timing = tm;
   return s;
 }
@@ -1764,7 +1788,7 @@ frbx_status frbx_stream_begin(frbx_ctx *c, int64_t chunk_frames) {
   const size_t n = size_t(c->B) * c->N * c->J * size_t(c->buf_frames);
   for (int i = 0; i < 2; ++i) {
     dfree(c->sbuf[i]);
-    if (hipMalloc(reinterpret_cast<void **>(&c->sbuf[i]), n * sizeof(float2)) != hipSuccess)
+    if (dev_alloc(c, &c->sbuf[i], n * sizeof(float2)) != hipSuccess)
       return c->fail(FRBX_E_NOMEM, "device allocation for the stream buffers failed");
     if ((s = c->hip(hipMemset(c->sbuf[i], 0, n * sizeof(float2)), "memset")) != FRBX_OK) return s;
   }
@@ -1802,7 +1826,7 @@ frbx_status frbx_stream_push(frbx_ctx *c, const void *chunk, int32_t kind, const
       return s;
     src = c->stage;
     if (kind == FRBX_IN_E4M3) {
-      if (!c->d_scale && hipMalloc(reinterpret_cast<void **>(&c->d_scale), size_t(rows) * sizeof(float)) != hipSuccess)
+      if (!c->d_scale && dev_alloc(c, &c->d_scale, size_t(rows) * sizeof(float)) != hipSuccess)
         return c->fail(FRBX_E_NOMEM, "device allocation failed");
       if ((s = c->hip(hipMemcpyAsync(c->d_scale, scale, size_t(rows) * sizeof(float), hipMemcpyHostToDevice, c->stream),
                       "scale upload")) != FRBX_OK)
@@ -1825,7 +1849,7 @@ frbx_status frbx_stream_push(frbx_ctx *c, const void *chunk, int32_t kind, const
   c->frames_in += c->chunk;
   // float16 operand scale of the matrix-core forms from this buffer
   if (c->precision != FRBX_PREC_F32) {
-    if (!c->d_absmax && hipMalloc(reinterpret_cast<void **>(&c->d_absmax), sizeof(unsigned int)) != hipSuccess)
+    if (!c->d_absmax && dev_alloc(c, &c->d_absmax, sizeof(unsigned int)) != hipSuccess)
       return c->fail(FRBX_E_NOMEM, "device allocation failed");
     unsigned int am = 0;
     s = c->hip(hipMemsetAsync(c->d_absmax, 0, sizeof(unsigned int), c->stream), "memset");
@@ -2064,11 +2088,11 @@ frbx_status frbx_power_sum(frbx_ctx *c, const int32_t *bl, int32_t n_bl, frbx_ca
     double *d_m = nullptr, *d_s = nullptr;
     int64_t *d_c = nullptr;
     auto cleanup = [&]() { dfree(d_sum); dfree(d_bl); dfree(d_m); dfree(d_s); dfree(d_c); };
-    if (hipMalloc(reinterpret_cast<void **>(&d_sum), size_t(len) * sizeof(float)) != hipSuccess ||
-        hipMalloc(reinterpret_cast<void **>(&d_bl), size_t(n_bl) * sizeof(int32_t)) != hipSuccess ||
-        hipMalloc(reinterpret_cast<void **>(&d_m), size_t(rows) * sizeof(double)) != hipSuccess ||
-        hipMalloc(reinterpret_cast<void **>(&d_s), size_t(rows) * sizeof(double)) != hipSuccess ||
-        hipMalloc(reinterpret_cast<void **>(&d_c), size_t(rows) * sizeof(int64_t)) != hipSuccess) {
+    if (dev_alloc(c, &d_sum, size_t(len) * sizeof(float)) != hipSuccess ||
+        dev_alloc(c, &d_bl, size_t(n_bl) * sizeof(int32_t)) != hipSuccess ||
+        dev_alloc(c, &d_m, size_t(rows) * sizeof(double)) != hipSuccess ||
+        dev_alloc(c, &d_s, size_t(rows) * sizeof(double)) != hipSuccess ||
+        dev_alloc(c, &d_c, size_t(rows) * sizeof(int64_t)) != hipSuccess) {
       cleanup();
       return c->fail(FRBX_E_NOMEM, "device allocation failed");
     }
@@ -2100,7 +2124,7 @@ frbx_status frbx_power_sum(frbx_ctx *c, const int32_t *bl, int32_t n_bl, frbx_ca
       if (s != FRBX_OK || int64_t(ncr) <= c->cross_cap) break;
       dfree(c->d_cross);
       c->cross_cap = 0;
-      if (hipMalloc(reinterpret_cast<void **>(&c->d_cross), size_t(ncr) * sizeof(DevCrossing)) != hipSuccess) {
+      if (dev_alloc(c, &c->d_cross, size_t(ncr) * sizeof(DevCrossing)) != hipSuccess) {
         cleanup();
         return c->fail(FRBX_E_NOMEM, "device allocation for crossings failed");
       }
@@ -2151,7 +2175,7 @@ frbx_status frbx_calibrate(frbx_ctx *c, int32_t b, int64_t k0, int32_t len, doub
   if (s != FRBX_OK) return s;
   const int N = c->N, J = c->J, NJ = N * J;
   float2 *d_y = nullptr;
-  if (hipMalloc(reinterpret_cast<void **>(&d_y), size_t(NJ) * sizeof(float2)) != hipSuccess)
+  if (dev_alloc(c, &d_y, size_t(NJ) * sizeof(float2)) != hipSuccess)
     return c->fail(FRBX_E_NOMEM, "device allocation failed");
   const void *vb = static_cast<const char *>(c->d_vis) + size_t(b) * NJ * size_t(c->K) * (c->vis_f16 ? 4 : 8);
   std::vector<float2> hy(NJ);

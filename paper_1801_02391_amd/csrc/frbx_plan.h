@@ -34,6 +34,33 @@ inline int whole_baselines(int dt, size_t per_trial, int D, int B, int64_t tasks
   return nb * D;
 }
 
+// The tile of a search: its DM trials (a multiple of D where it holds whole
+// baselines) and whether it is screened.
+struct TilePlan {
+  int dt = 1;
+  bool records = false;
+};
+
+// per_tile, per_rec: bytes of a DM trial's dedispersed spectra and of its
+// screening records (0: not screened), rec_extra bytes of records once; S
+// segments of a trial with n_rate screening tasks each.  Tiles and records
+// share the budget.  Where a trial's do not fit together it is searched without
+// records; a budget that is not strict holds any one trial, whose records may
+// then take as much again as its spectra.  Baselines share a tile up to `merge`
+// bytes of spectra.
+inline TilePlan plan_tiles(size_t budget, bool strict, size_t merge, size_t per_tile, size_t per_rec, size_t rec_extra,
+                           int D, int B, int64_t S, int n_rate) {
+  TilePlan p;
+  const size_t room = strict ? budget : std::max(budget, 2 * per_tile);
+  p.records = per_rec > 0 && S * n_rate <= kLaunchMost && per_tile + per_rec + rec_extra <= room;
+  const size_t per = per_tile + (p.records ? per_rec : 0), most = budget - std::min(budget, p.records ? rec_extra : 0);
+  const int64_t tasks = S * (p.records ? n_rate : 1);
+  p.dt = tile_trials(most, per, D, tasks);
+  p.dt = std::min(whole_baselines(p.dt, per, D, B, tasks, most),
+                  whole_baselines(p.dt, per_tile, D, B, tasks, std::min(budget, merge)));
+  return p;
+}
+
 }  // namespace frbx
 
 #endif
