@@ -424,7 +424,7 @@ struct Candidates {
   __device__ __forceinline__ void first(int lane, int P, int &rc, int &qd) const {
     float top = -1.0f;
     int r = lane;
-    if (lane < R && units > 0) {
+    if (lane < R) {
       const float2 ab = bounds(lane);
       if (ab.y < __builtin_inff()) top = ab.x;
     }
@@ -470,10 +470,6 @@ struct Candidates {
   // the units of `each` as bit masks cand[rc] of the work-group's threads
   // (cleared before)
   __device__ __forceinline__ void mark(int t, int n, int P, float amp, unsigned *cand) const {
-    if (units == 0) {
-      for (int i = t; i < R * P; i += n) cand[i] = (1u << per_c) - 1u;
-      return;
-    }
     each(t, n, P, amp, [&](int rc, int u, unsigned) { atomicOr(&cand[rc], 1u << u); });
   }
 };

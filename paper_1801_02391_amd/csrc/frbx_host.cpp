@@ -84,10 +84,13 @@ struct frbx_ctx {
   int32_t mbd_shift = -1;        // that shift, -1 for the general form
   int specialise = 1;            // float32 general form: kernel compiled for the lattice's rows
   int sbd_mfma = 0;              // float16 form: SBD transform on the matrix cores as well
+  unsigned rows_want = 0;        // rows to compile the kernel for (0: the statically built kernel)
   unsigned rows_mask = 0;        // rows of the kernel in use (0: the statically built kernel)
-  hipFunction_t rows_fn = nullptr, rows_find = nullptr;
+  hipFunction_t rows_fn = nullptr, rows_cand = nullptr, rows_find = nullptr;   // unscreened; screened
   std::string rows_note;         // why the specialised kernel is not in use
-  int scr_blocks = 0;            // screened search: work-groups of the screening pass (0: not screened),
+  int64_t form_segs = -1;        // choose_form: segments per DM trial it was asked for, and its answer
+  bool screened = false, wave = false;
+  int scr_blocks = 0;            // screening pass: its work-groups (0: its tables are not built),
   bool scr_half = false;         // its form, operand rows and the errors of its rounded matrices
   int32_t scr_row_if[32];
   int scr_tiles = 16;            // its MBD grid
@@ -406,26 +409,25 @@ bool use_gemm(const frbx_ctx *c) {
          frbx::fringe_gemm_supported(c->J, c->n_mbd, c->N, c->sbd_pad);
 }
 
-// Whether a run has enough segments to fill the device's 1024 SIMDs several
-// times over (grids set for a run shorter than the stream's chunks: unknown,
-// taken as enough).  A search of 978 segments takes 219 us with a work-group
-// per segment and no screening pass, 223 us with a wave each and one.
+// Whether a search of S segments per DM trial has enough of them to fill the
+// device's 1024 SIMDs several times over (grids set for a run shorter than the
+// stream's chunks: unknown, taken as enough).  A search of 978 segments takes
+// 219 us with a work-group per segment and no screening pass, 223 us with a
+// wave each and one.
 // (A screening pass has n_rate tasks per segment: 1265 segments with 13 rates
 // of 16 IFs x 256 channels take 1.4 ms screened, 3.3 without.)
-bool many_segments(const frbx_ctx *c, int per = 1) {
-  return c->seg_total <= 0 || int64_t(c->B) * c->n_dm * c->seg_total * per >= 4096;
-}
+bool many_tasks(const frbx_ctx *c, int64_t S, int per) { return S <= 0 || int64_t(c->B) * c->n_dm * S * per >= 4096; }
 
-// The float32 search takes one wave per segment where the shape allows it and
-// the four segments of a work-group fit its LDS.
-// (A screened one has find_kernel.)
-bool use_wave(const frbx_ctx *c, bool screened) {
-  return !screened && frbx::fringe_wave(c->J, c->N) && many_segments(c) &&
+// The unscreened float32 search takes one wave per segment where the shape
+// allows it, there are enough of them and the four segments of a work-group
+// fit its LDS.
+bool use_wave(const frbx_ctx *c, int64_t S) {
+  return frbx::fringe_wave(c->J, c->N) && many_tasks(c, S, 1) &&
          frbx::fringe_lds_bytes(c->J, c->n_mbd, c->N, c->sbd_pad, true) <= 80 * 1024;
 }
 
 size_t fringe_lds(const frbx_ctx *c, bool screened) {
-  return frbx::fringe_lds_bytes(c->J, c->n_mbd, c->N, c->sbd_pad, use_wave(c, screened),
+  return frbx::fringe_lds_bytes(c->J, c->n_mbd, c->N, c->sbd_pad, !screened && c->wave,
                                 screened ? c->n_rate * c->sbd_pad : 0);
 }
 
@@ -460,10 +462,10 @@ bool screen_half(const frbx_ctx *c) {
 // product, so it is screened only where that applies, up to 64 channels (one
 // baseline, 16 IFs or fewer: 3.38 against 3.11 ms; with 128 channels the pass
 // takes longer than the form itself).
-bool use_screen(const frbx_ctx *c, int tiles) {
+bool use_screen(const frbx_ctx *c, int tiles, int64_t S) {
   const bool half = screen_half(c);
   if (use_gemm(c) || !frbx::screen_supported(c->J, c->n_mbd, c->N, c->n_rate, half, tiles, c->sbd_pad)) return false;
-  if (c->n_rate * c->sbd_pad * c->J / 16 < (tiles < 16 ? 8 : 16) || !many_segments(c, c->n_rate)) return false;
+  if (c->n_rate * c->sbd_pad * c->J / 16 < (tiles < 16 ? 8 : 16) || !many_tasks(c, S, c->n_rate)) return false;
   if (c->precision == FRBX_PREC_F16 && !(half && c->J <= 64)) return false;
   if (c->precision == FRBX_PREC_F32) return fringe_lds(c, true) <= 150 * 1024 && find_lds(c) <= 150 * 1024;
   const size_t lds = frbx::fringe_mfma_lds_bytes(c->J, c->N, c->sbd_pad, c->precision == FRBX_PREC_F16X3 ? 3 : 1);
@@ -621,6 +623,83 @@ void screen_bounds(const frbx_ctx *c, float scale, frbx::ScreenArgs &sa) {
   sa.abs_scaled = float(c->N * (c->J + 1) * tiny);
 }
 
+// a table into device memory of its own
+template <typename T, typename V>
+frbx_status upload(frbx_ctx *c, T *&dptr, const V &vec) {
+  dfree(dptr);
+  const size_t bytes = vec.size() * sizeof(vec[0]);
+  if (bytes == 0) return FRBX_OK;
+  if (dev_alloc(c, &dptr, bytes) != hipSuccess) return c->fail(FRBX_E_NOMEM, "device allocation of a table failed");
+  return c->hip(hipMemcpy(dptr, vec.data(), bytes, hipMemcpyHostToDevice), "table upload");
+}
+
+// Screening records of S segments, and for find_kernel their part of the list
+// of those that it leaves (an int each).  The number of the list's entries
+// stands before it (kLeftCount bytes), and the records after it at a multiple
+// of 8 bytes (kRecExtra in all).
+constexpr size_t kLeftCount = 256, kRecExtra = kLeftCount + 8;
+size_t rec_bytes(const frbx_ctx *c, int64_t S) {
+  return size_t(S) * (size_t(c->n_rate) * frbx::screen_rec_bytes(c->sbd_pad * c->J / 16) +
+                      (use_find(c) ? sizeof(int32_t) : 0));
+}
+
+// Bytes of a DM trial's dedispersed spectra.
+size_t dm_bytes(const frbx_ctx *c) { return size_t(std::max<int64_t>(c->k_eff, 0)) * c->N * c->J * sizeof(float2); }
+
+// Tiles of frbx_run_cube_noalloc: screening records behind the tiles, where
+// both fit the workspace.
+frbx::TilePlan noalloc_plan(const frbx_ctx *c) {
+  const size_t per_dm = dm_bytes(c);
+  return frbx::plan_tiles(frbx::kNoAllocBytes, true, frbx::kNoAllocBytes, per_dm,
+                          c->screened ? rec_bytes(c, c->seg_total) : 0, kRecExtra, c->n_dm, c->B, c->seg_total,
+                          c->n_rate);
+}
+
+// The float32 search's kernel compiled for the lattice's rows (compiled once
+// per process; null: the statically built one), screened with find_kernel.
+hipFunction_t rows_kernel(frbx_ctx *c, bool screened, hipFunction_t *find = nullptr) {
+  if (!c->rows_want) return nullptr;
+  return frbx::fringe_rows_kernel(c->device, c->J, c->n_mbd, c->rows_want, screened, !screened && c->wave, find,
+                                  &c->rows_note);
+}
+
+// Whether a search of S segments per DM trial is screened, and which kernels
+// it takes.  A screened search also has the unscreened kernel where the
+// workspace of frbx_run_cube_noalloc, which compiles nothing, may lack the room
+// for the records.
+frbx_status choose_form(frbx_ctx *c, int64_t S) {
+  if (S == c->form_segs) return FRBX_OK;
+  frbx_status s;
+  const ScreenGrid SG = screen_grid(c);
+  const bool first = c->form_segs < 0, was_screened = c->screened, was_wave = c->wave;
+  c->form_segs = -1;
+  c->wave = use_wave(c, S);
+  c->screened = use_screen(c, SG.tiles, S);
+  if (c->screened && !c->scr_blocks) {
+    const ScreenTables T = screen_tables(c, SG.tiles);
+    std::copy(T.row_if, T.row_if + 32, c->scr_row_if);
+    c->scr_half = T.half;
+    c->scr_tiles = SG.tiles;
+    c->scr_gamma = SG.gamma;
+    c->scr_err_s = T.err_s;
+    c->scr_err_m = T.err_m;
+    if ((s = upload(c, c->d_scr_sbd, T.fs)) != FRBX_OK || (s = upload(c, c->d_scr_mbd, T.fm)) != FRBX_OK) return s;
+    if ((s = c->hip(frbx::screen_blocks(c->J, c->N, c->n_rate, T.half, SG.tiles, c->sbd_pad, c->device, &c->scr_blocks),
+                    "screening pass")) != FRBX_OK)
+      return s;
+  }
+  if (first || c->screened != was_screened || c->wave != was_wave) {
+    c->rows_fn = c->rows_cand = c->rows_find = nullptr;
+    c->rows_note.clear();
+    if (c->screened) c->rows_cand = rows_kernel(c, true, &c->rows_find);
+    const bool noalloc = dm_bytes(c) <= frbx::kNoAllocBytes;
+    if (!c->screened || (noalloc && !noalloc_plan(c).records)) c->rows_fn = rows_kernel(c, false);
+    c->rows_mask = (c->screened ? c->rows_cand : c->rows_fn) ? c->rows_want : 0;
+  }
+  c->form_segs = S;
+  return FRBX_OK;
+}
+
 frbx_status prepare(frbx_ctx *c) {
   if (!c->dirty) return FRBX_OK;
   c->rbegun = false;  // a refinement's cells and tables follow the grids
@@ -721,14 +800,7 @@ frbx_status prepare(frbx_ctx *c) {
                            c->phi0[b * N + n] / kTwoPi;
         cal[(size_t(b) * N + n) * J + j] = cis_cycles(cyc);
       }
-  auto up = [&](auto *&dptr, const auto &vec) -> frbx_status {
-    dfree(dptr);
-    const size_t bytes = vec.size() * sizeof(vec[0]);
-    if (bytes == 0) return FRBX_OK;
-    if (dev_alloc(c, &dptr, bytes) != hipSuccess)
-      return c->fail(FRBX_E_NOMEM, "device allocation of a table failed");
-    return c->hip(hipMemcpy(dptr, vec.data(), bytes, hipMemcpyHostToDevice), "table upload");
-  };
+  auto up = [&](auto *&dptr, const auto &vec) { return upload(c, dptr, vec); };
   frbx_status s;
   if ((s = up(c->d_dk, c->dk)) != FRBX_OK) return s;
   if ((s = up(c->d_rate, rate)) != FRBX_OK) return s;
@@ -812,40 +884,22 @@ frbx_status prepare(frbx_ctx *c) {
       if ((s = up(c->d_sbd_a, fa)) != FRBX_OK) return s;
     }
   }
-  c->scr_blocks = 0;
-  const ScreenGrid SG = screen_grid(c);
-  if (use_screen(c, SG.tiles)) {
-    const ScreenTables T = screen_tables(c, SG.tiles);
-    std::copy(T.row_if, T.row_if + 32, c->scr_row_if);
-    c->scr_half = T.half;
-    c->scr_tiles = SG.tiles;
-    c->scr_gamma = SG.gamma;
-    c->scr_err_s = T.err_s;
-    c->scr_err_m = T.err_m;
-    if ((s = up(c->d_scr_sbd, T.fs)) != FRBX_OK || (s = up(c->d_scr_mbd, T.fm)) != FRBX_OK) return s;
-    if ((s = c->hip(frbx::screen_blocks(J, N, c->n_rate, T.half, SG.tiles, c->sbd_pad, c->device, &c->scr_blocks),
-                    "screening pass")) != FRBX_OK)
-      return s;
-  }
-  // Float32 general form: the fringe kernel compiled for the rows of the
+  // Float32 general form: the fringe kernels are compiled for the rows of the
   // first MBD pass that hold an IF (the same sums, only those rows read
-  // and transformed); the statically built kernel when every row holds an
-  // IF or the run-time compiler cannot build it.
-  c->rows_fn = c->rows_find = nullptr;
-  c->rows_mask = 0;
-  c->rows_note.clear();
+  // and transformed); the statically built ones when every row holds an
+  // IF or the run-time compiler cannot build them.
+  c->rows_want = 0;
   const int MB = frbx::fringe_compact_rows(M);
   if (c->specialise && c->precision == FRBX_PREC_F32 && c->mbd_pos.empty() && MB > 0) {
     const int MA = M / MB;
     unsigned rows = 0;
     for (int n = 0; n < N; ++n) rows |= 1u << (c->q_if[n] / MB);
     const unsigned all = MA >= 32 ? ~0u : (1u << MA) - 1u;
-    if (rows != all) {
-      c->rows_fn = frbx::fringe_rows_kernel(c->device, J, M, rows, c->scr_blocks > 0, use_wave(c, c->scr_blocks > 0),
-                                            &c->rows_find, &c->rows_note);
-      if (c->rows_fn) c->rows_mask = rows;
-    }
+    if (rows != all) c->rows_want = rows;
   }
+  c->scr_blocks = 0;
+  c->form_segs = -1;
+  if ((s = choose_form(c, c->seg_total)) != FRBX_OK) return s;
   c->dirty = false;
   return FRBX_OK;
 }
@@ -1421,21 +1475,12 @@ frbx_status recheck_pass(frbx_ctx *c, const PassSpec &ps, frbx::StatsArgs &st, s
   return c->hip(frbx::launch_fringe_list(J, M, fa, lds, int(n), c->stream), "recheck launch");
 }
 
-// Screening records of S segments, and for find_kernel their part of the list
-// of those that it leaves (an int each).  The number of the list's entries
-// stands before it (kLeftCount bytes), and the records after it at a multiple
-// of 8 bytes (kRecExtra in all).
-constexpr size_t kLeftCount = 256, kRecExtra = kLeftCount + 8;
-size_t rec_bytes(const frbx_ctx *c, int64_t S) {
-  return size_t(S) * (size_t(c->n_rate) * frbx::screen_rec_bytes(c->sbd_pad * c->J / 16) +
-                      (use_find(c) ? sizeof(int32_t) : 0));
-}
-
 // Dedispersion and fringe search of every (baseline, DM tile): the DM
 // trials are taken dt at a time through the dedispersed-tile buffer wbuf
 // ([dt][k_eff][N J]; dt a multiple of D: whole baselines), and every
-// segment's peak goes into the cube power / pidx ([B][D][S]).  A screened search writes the screening records
-// of a tile to rec (null: none, every unit of every segment is evaluated).
+// segment's peak goes into the cube power / pidx ([B][D][S]).  A screened
+// search writes the screening records of a tile to rec (null: the search is
+// not screened).
 frbx_status search_tiles(frbx_ctx *c, const PassSpec &ps, float2 *wbuf, int dt, unsigned char *rec, float *power,
                          int32_t *pidx) {
   const int B = c->B, D = c->n_dm, NJ = c->N * c->J, nw = int(c->windows.size());
@@ -1444,13 +1489,13 @@ frbx_status search_tiles(frbx_ctx *c, const PassSpec &ps, float2 *wbuf, int dt, 
   const int J = c->J, M = c->n_mbd;
   frbx_status s;
   const bool use_mfma = c->precision != FRBX_PREC_F32;
-  const bool screened = c->scr_blocks > 0;
-  const bool wave = use_wave(c, screened);
+  const bool screened = c->screened && rec, wave = !screened && c->wave;
+  const hipFunction_t rows_fn = screened ? c->rows_cand : c->rows_fn;
   const size_t lds = fringe_lds(c, screened);
   const float scale = mfma_scale(c);
   const size_t in_bytes = ps.vis_f16 ? 4 : 8;
   int32_t *left_list = nullptr, *left_n = nullptr;
-  if (screened && rec && use_find(c)) {
+  if (screened && use_find(c)) {
     left_n = reinterpret_cast<int32_t *>(rec);
     left_list = left_n + kLeftCount / sizeof(int32_t);
     rec = reinterpret_cast<unsigned char *>(left_list) + size_t(dt) * S * sizeof(int32_t) + (size_t(dt) * S & 1) * sizeof(int32_t);
@@ -1521,7 +1566,7 @@ frbx_status search_tiles(frbx_ctx *c, const PassSpec &ps, float2 *wbuf, int dt, 
         fa.mfma_scale = scale;
         fa.screened = screened ? 1 : 0;
         sp = c->span_begin(0, int64_t(ndt) * S);
-        if (screened && rec) {
+        if (screened) {
           fa.screen = rec;
           fa.screen_units = c->sbd_pad * J / 16;
           frbx::ScreenArgs sa{};
@@ -1561,13 +1606,13 @@ frbx_status search_tiles(frbx_ctx *c, const PassSpec &ps, float2 *wbuf, int dt, 
           if (left_n) {
             fa.left_list = left_list;
             fa.left_n = left_n;
-            le = c->rows_fn ? frbx::launch_fringe_rows(c->rows_find, fa, 4, find_lds(c), n_seg, c->stream)
-                            : frbx::launch_find(J, fa, find_lds(c), n_seg, c->stream);
+            le = rows_fn ? frbx::launch_fringe_rows(c->rows_find, fa, 4, find_lds(c), n_seg, c->stream)
+                         : frbx::launch_find(J, fa, find_lds(c), n_seg, c->stream);
             grid = std::min(n_seg, frbx::kLeftBlocks);
           }
           if (le == hipSuccess)
-            le = c->rows_fn ? frbx::launch_fringe_rows(c->rows_fn, fa, per, lds, grid, c->stream)
-                            : frbx::launch_fringe(J, M, fa, wave, lds, grid, c->stream);
+            le = rows_fn ? frbx::launch_fringe_rows(rows_fn, fa, per, lds, grid, c->stream)
+                         : frbx::launch_fringe(J, M, fa, wave, lds, grid, c->stream);
         }
         if ((s = c->hip(le, "fringe launch")) != FRBX_OK) return s;
         c->span_end(sp);
@@ -1589,7 +1634,7 @@ frbx_status device_pass(frbx_ctx *c, const PassSpec &ps, std::vector<DevCrossing
   // (a screened tile has n_rate tasks per segment)
   const frbx::TilePlan tp =
       frbx::plan_tiles(c->w_budget, c->w_budget_strict, kTileBaselines, per_dm * sizeof(float2),
-                       c->scr_blocks > 0 ? rec_bytes(c, S) : 0, kRecExtra, D, B, S, c->n_rate);
+                       c->screened ? rec_bytes(c, S) : 0, kRecExtra, D, B, S, c->n_rate);
   c->dt = tp.dt;
   const size_t cube = size_t(B) * D * std::max<int64_t>(S, 1);
   const size_t rows = size_t(B) * D * nw;
@@ -1624,13 +1669,14 @@ frbx_status device_pass(frbx_ctx *c, const PassSpec &ps, std::vector<DevCrossing
     s = allocate();
   }
   if (s != FRBX_OK) return s;
-  // and the screening records, after it; without memory for them every unit
-  // is evaluated
+  // and the screening records, after it; without memory for them the search is
+  // not screened
   unsigned char *rec = nullptr;
   if (tp.records) {
     if (ensure(c, c->d_rec, c->rec_cap, rec_bytes(c, S) * c->dt + kRecExtra) == FRBX_OK) rec = c->d_rec;
     else c->err = msg, (void)hipGetLastError();
   }
+  if (!rec && c->screened && S > 0 && !c->rows_fn) c->rows_fn = rows_kernel(c, false);
   const bool use_mfma = c->precision != FRBX_PREC_F32;
   if ((s = search_tiles(c, ps, c->d_w, c->dt, rec, c->d_power, c->d_pidx)) != FRBX_OK) return s;
   // Eq. 6 statistics and threshold crossings
@@ -1739,22 +1785,19 @@ frbx_status frbx_run_cube_noalloc(frbx_ctx *c, float *power, int32_t *idx, int64
                                  "setter; frbx_run_cube_noalloc builds nothing");
   if (!c->d_noalloc) return c->fail(FRBX_E_DEVICE, c->noalloc_err.empty() ? "no-alloc workspace unavailable" : c->noalloc_err);
   if (hipSetDevice(c->device) != hipSuccess) return c->fail(FRBX_E_DEVICE, "hipSetDevice failed");
-  const int D = c->n_dm, NJ = c->N * c->J;
+  const int D = c->n_dm;
   const int64_t S = c->seg_total;
   const int64_t len = int64_t(c->B) * D * S;
   if (n) *n = len;
   if (cap < len) return c->fail(FRBX_E_RANGE, "output capacity below B x D x segments");
   if (len == 0) return FRBX_OK;
   if (!power || !idx) return c->fail(FRBX_E_INVAL, "null output pointer");
-  const int64_t k_eff = c->K - c->dk_max;
-  const size_t per_dm = size_t(k_eff) * NJ * sizeof(float2);
+  const size_t per_dm = dm_bytes(c);
   if (per_dm > frbx::kNoAllocBytes)
     return c->fail(FRBX_E_INVAL, "one DM trial's dedispersed tile (" + std::to_string(per_dm) +
                                      " bytes) exceeds the no-alloc workspace (" +
                                      std::to_string(frbx::kNoAllocBytes) + " bytes)");
-  // screening records behind the tiles, where both fit
-  const frbx::TilePlan tp = frbx::plan_tiles(frbx::kNoAllocBytes, true, frbx::kNoAllocBytes, per_dm,
-                                             c->scr_blocks > 0 ? rec_bytes(c, S) : 0, kRecExtra, D, c->B, S, c->n_rate);
+  const frbx::TilePlan tp = noalloc_plan(c);
   const int nw = int(c->windows.size());
   PassSpec ps;
   ps.vis = c->d_vis;

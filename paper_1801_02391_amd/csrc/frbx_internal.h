@@ -111,7 +111,7 @@ struct FringeArgs {
   // records of screen_rec_bytes(units)
   int32_t screened;
   const unsigned char *screen;
-  int32_t screen_units;      // P J / 16; 0: no records, every unit is a candidate
+  int32_t screen_units;      // P J / 16
   // segments (d n_seg + segment) that find_kernel leaves to fringe_kernel:
   // their list and number (null: all of them)
   int32_t *left_list;

@@ -1268,6 +1268,7 @@ struct LaunchFn {
   }
   template <int J, int M> hipError_t operator()() {
     if (a.screened) {
+      if (!a.screen || a.screen_units < 1) return hipErrorInvalidValue;
       if constexpr (M == 256 && J >= 16)
         return a.mbd_pos ? launch_fringe_t<J, M, false, true, false, true>(a, lds, grid, s)
                          : launch_fringe_t<J, M, false, false, false, true>(a, lds, grid, s);
@@ -1410,6 +1411,7 @@ static hipError_t launch_mfma_t(const FringeArgs &a, size_t lds, int grid, hipSt
     return hipGetLastError();
   };
   if (a.dump) return go(&fringe_mfma_kernel<J, NK, NP, true>);
+  if (a.screened && (!a.screen || a.screen_units < 1)) return hipErrorInvalidValue;
   if (a.screened) return go(&fringe_mfma_kernel<J, NK, NP, false, true>);
   return go(&fringe_mfma_kernel<J, NK, NP, false>);
 }

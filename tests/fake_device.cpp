@@ -5,11 +5,12 @@
 // being run.  Then one search through the C ABI, from key=value arguments:
 //   if=f0,f1,...  J= K= B= D= dm_step= P= M= R= W=l0,l1,...  prec= recheck=
 //   jit=0|1 (run-time compilation succeeds) budget=bytes quota=bytes
-//   rec_refused=0|1 (refuse what is allocated while records are wanted: the
-//   `refuse`-th allocation from frbx_run on)
+//   refuse=n (the n-th allocation from the search on fails)
 //   mode=run|noalloc|stream chunk=APs pushes=n
-// Output: one line "kernel <name> grid <g> lds <bytes>" per launch, "mark
-// <what>" between the steps, and "status", "peak" (bytes) and "left" at the end.
+// Output: "compiled <expression>" for what is compiled at run time, "prepared"
+// when the search begins, from then on "kernel <name> grid <g> lds <bytes>" for
+// every launch and "refused <bytes>", "mark <what>" between the steps, and
+// "segments", "peak" (bytes) and "status" at the end.
 #include <math.h>
 #include <stdint.h>
 #include <stdio.h>
@@ -196,8 +197,7 @@ int hiprtcAddNameExpression(void *prog, const char *expr) {
   return kOk;
 }
 int hiprtcCompileProgram(void *prog, int, const char **) {
-  if (fake().log)
-    for (const std::string &e : fake().programs[prog]) printf("compiled %s\n", e.c_str());
+  for (const std::string &e : fake().programs[prog]) printf("compiled %s\n", e.c_str());
   return fake().jit ? 0 : 6;
 }
 int hiprtcGetLoweredName(void *, const char *expr, const char **name) {

@@ -1,0 +1,57 @@
+"""Which kernels a search takes, on the CPU: the library's host code against a
+stand-in device that names the launches (fake_device.cpp)."""
+import re
+
+import pytest
+
+from screen_shapes import K, LATTICES, N_DM, PRECISION, SCREENED, WHOLE, WINDOWS
+from test_host_memory import MANY_RATES, device, spectra  # noqa: F401  (a fixture)
+
+
+def kernels(text):
+    """The search kernels of a run: screening pass, find_kernel, and the form's
+    own kernel as (channels, evaluates candidates, threads per segment)."""
+    out = set()
+    for name in re.findall(r"^kernel (.*) grid", text, re.M):
+        if m := re.search(r"(screen|find)_kernel", name):
+            out.add(m.group(1))
+        elif m := re.search(r"fringe_kernel(?:ILi|<)(\d+)(?:ELi|, )\d+(?:ELb|, )\w+(?:ELb|, )\w+(?:ELb|, )\w+(?:ELj|, )"
+                            r"\d+u?(?:ELb|, )(\w+)(?:ELi|, )(\d+)", name):
+            out.add((int(m.group(1)), m.group(2) in ("1", "true"), int(m.group(3))))
+        elif m := re.search(r"fringe_mfma_kernelILi(\d+)ELi\dELi\dELb0ELb(\d)E", name):
+            out.add((int(m.group(1)), m.group(2) == "1", 256))
+    return out
+
+
+def form(precision):
+    return dict(prec=PRECISION[precision])
+
+
+@pytest.mark.parametrize("jit", [0, 1])
+@pytest.mark.parametrize("precision", ["f32", "f16x3"])
+def test_without_records_every_cell_by_the_plain_kernel(device, precision, jit):  # noqa: F811
+    """The records do not fit the budget, the device refuses them, or they do
+    not fit beside the spectra in the no-alloc workspace (which compiles
+    nothing)."""
+    shape = dict(MANY_RATES, jit=jit, **form(precision))
+    wave = 64 if precision == "f32" else 256
+    r = device(**shape, budget=spectra(shape))
+    assert r["status"] == 0 and kernels(r["text"]) == {(16, False, wave)}
+    r = device(**shape)
+    assert r["status"] == 0 and "screen" in kernels(r["text"])
+    n = next(k for k in range(1, 12) if device(**shape, refuse=k)["status"] == 0)
+    r = device(**shape, refuse=n)
+    first = r["text"].split("mark again")[0]
+    assert r["refused"] == 1 and kernels(first) == {(16, False, wave)}
+    r = device(**shape, mode="noalloc")
+    assert r["status"] == 0 and kernels(r["text"]) == {(16, False, wave)}
+    assert "compiled" not in r["text"].split("prepared")[1]
+    assert ("jit:" in r["text"]) == (jit == 1 and precision == "f32")
+
+
+def test_a_screened_search_compiles_the_plain_kernel_only_where_it_may_need_it(device):  # noqa: F811
+    vgos = dict(J=64, P=4, R=8, W="2,4,8", **{"if": ",".join(map(str, LATTICES["32if-vgos"]))})
+    for arg in (dict(K=400, D=4), dict(K=400, D=4, mode="noalloc"), dict(K=6000, D=2)):
+        r = device(**vgos, **arg)
+        assert kernels(r["text"]) == {"screen", "find", (64, True, 256)}
+        assert re.findall(r"^compiled frbx::(\w+)<", r["text"], re.M) == ["fringe_kernel", "find_kernel"]
