@@ -409,20 +409,24 @@ bool use_gemm(const frbx_ctx *c) {
          frbx::fringe_gemm_supported(c->J, c->n_mbd, c->N, c->sbd_pad);
 }
 
-// Whether a search of S segments per DM trial has enough of them to fill the
-// device's 1024 SIMDs several times over (grids set for a run shorter than the
-// stream's chunks: unknown, taken as enough).  A search of 978 segments takes
-// 219 us with a work-group per segment and no screening pass, 223 us with a
-// wave each and one.
+// (segment, rate) tasks of a search of S segments per DM trial (per 1: segments).
+int64_t tasks(const frbx_ctx *c, int64_t S, int per) {
+  // (grids set for a run shorter than the stream's chunks: unknown, taken as enough)
+  return S > 0 ? int64_t(c->B) * c->n_dm * S * per : std::numeric_limits<int64_t>::max();
+}
+
+// Tasks that fill the device's 1024 SIMDs several times over.  A search of 978
+// segments takes 219 us with a work-group per segment and no screening pass,
+// 223 us with a wave each and one.
 // (A screening pass has n_rate tasks per segment: 1265 segments with 13 rates
 // of 16 IFs x 256 channels take 1.4 ms screened, 3.3 without.)
-bool many_tasks(const frbx_ctx *c, int64_t S, int per) { return S <= 0 || int64_t(c->B) * c->n_dm * S * per >= 4096; }
+constexpr int64_t kManyTasks = 4096;
 
 // The unscreened float32 search takes one wave per segment where the shape
 // allows it, there are enough of them and the four segments of a work-group
 // fit its LDS.
 bool use_wave(const frbx_ctx *c, int64_t S) {
-  return frbx::fringe_wave(c->J, c->N) && many_tasks(c, S, 1) &&
+  return frbx::fringe_wave(c->J, c->N) && tasks(c, S, 1) >= kManyTasks &&
          frbx::fringe_lds_bytes(c->J, c->n_mbd, c->N, c->sbd_pad, true) <= 80 * 1024;
 }
 
@@ -453,20 +457,34 @@ bool screen_half(const frbx_ctx *c) {
 // A screened search: the float16 screening pass names the candidate units of
 // every segment and the search's kernel evaluates those.  Every form but the
 // one with the SBD transform on the matrix cores, where the pass has the
-// shape (and the candidate masks fit beside the kernel's LDS plan) and a
-// segment has enough units: with 16 the candidates are a tenth of the search,
-// with 8 on a coarse MBD grid (one rate, 32 channels, sbd_pad 4: 8 IFs x 1 s x
-// 64 DM trials 3.04 -> 1.72 ms, the paper's set-up x 20 s 1.59 -> 0.95 ms) a
-// fifth; on the full grid the pass itself then costs what it saves.  The
-// float16 form's own products are the screening pass's but for the halved MBD
-// product, so it is screened only where that applies, up to 64 channels (one
-// baseline, 16 IFs or fewer: 3.38 against 3.11 ms; with 128 channels the pass
-// takes longer than the form itself).
+// shape (and the candidate masks fit beside the kernel's LDS plan) and where it
+// pays, by the units of a segment (about two of them are evaluated whatever
+// their number) and by the number of tasks.
 bool use_screen(const frbx_ctx *c, int tiles, int64_t S) {
-  const bool half = screen_half(c);
+  const bool half = screen_half(c), coarse = tiles < 16;
   if (use_gemm(c) || !frbx::screen_supported(c->J, c->n_mbd, c->N, c->n_rate, half, tiles, c->sbd_pad)) return false;
-  if (c->n_rate * c->sbd_pad * c->J / 16 < (tiles < 16 ? 8 : 16) || !many_tasks(c, S, c->n_rate)) return false;
-  if (c->precision == FRBX_PREC_F16 && !(half && c->J <= 64)) return false;
+  const int units = c->n_rate * c->sbd_pad * c->J / 16;
+  const int64_t n = tasks(c, S, c->n_rate);
+  // float32: with 16 units the candidates are a tenth of the search, with 8 on
+  // a coarse MBD grid (one rate, 32 channels, sbd_pad 4: 8 IFs x 1 s x 64 DM
+  // trials 3.04 -> 1.72 ms, the paper's set-up x 20 s 1.59 -> 0.95 ms) a fifth;
+  // on the full grid the pass itself then costs what it saves.
+  if (c->precision == FRBX_PREC_F32 && units < (coarse ? 8 : 16)) return false;
+  // f16x3, whose own products are but three times the pass's (86272 segments,
+  // ms screened against unscreened): 16 units of 32 IFs x 64 channels 3.3
+  // against 3.8, of 16 compact IFs x 64 channels 1.98 against 2.23; but 8 units
+  // of 8 compact IFs x 32 channels 1.35 against 1.19, 16 units on the full grid
+  // 2.00 against 1.92 (32: 2.9 against 3.5), 16 units of 128 channels 2.85
+  // against 2.40 (32 units: 7.1 against 7.7).
+  if (c->precision == FRBX_PREC_F16X3 && units < ((coarse || half) && c->J <= 64 ? 16 : 32)) return false;
+  // float16, whose own products are the pass's but for the halved MBD product:
+  // only where that applies, up to 64 channels (with 128 the pass takes longer
+  // than the form itself).  32 IFs x 64 channels, 86272 segments: 16 units 2.75
+  // against 2.13 ms, 32 units 4.0 against 3.6, 64 units 6.6 against 6.8, 128
+  // units 11.1 against 12.9; with 64 units and 9536 tasks 0.34 against 0.32.
+  if (c->precision == FRBX_PREC_F16 && (!half || c->J > 64 || units < 64 || (units < 128 && n < 4 * kManyTasks)))
+    return false;
+  if (n < kManyTasks) return false;
   if (c->precision == FRBX_PREC_F32) return fringe_lds(c, true) <= 150 * 1024 && find_lds(c) <= 150 * 1024;
   const size_t lds = frbx::fringe_mfma_lds_bytes(c->J, c->N, c->sbd_pad, c->precision == FRBX_PREC_F16X3 ? 3 : 1);
   return lds + size_t(c->n_rate) * c->sbd_pad * 4 <= 150 * 1024;

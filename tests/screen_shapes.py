@@ -30,7 +30,7 @@ SCREENED = [
 ]
 # evaluated whole: too few units for the form, or a shape the pass does not have
 WHOLE = [
-    ("5if-compact", 16, 4, 1, "f32"), ("3if-spread", 32, 4, 1, "f32"), ("32if-vgos", 256, 4, 2, "f32"),
+    ("5if-compact", 16, 4, 1, "f32"), ("3if-spread", 32, 4, 1, "f32"), ("3if-spread", 256, 4, 2, "f32"),
     ("8if-compact", 32, 4, 1, "f16x3"), ("16if-compact", 16, 8, 1, "f16x3"), ("3if-spread", 32, 4, 2, "f16x3"),
     ("8if-compact", 128, 1, 2, "f16x3"),
     ("32if-vgos", 64, 4, 1, "f16"), ("32if-vgos", 64, 8, 1, "f16"), ("17if", 32, 4, 2, "f16"),

@@ -55,3 +55,21 @@ def test_a_screened_search_compiles_the_plain_kernel_only_where_it_may_need_it(d
         r = device(**vgos, **arg)
         assert kernels(r["text"]) == {"screen", "find", (64, True, 256)}
         assert re.findall(r"^compiled frbx::(\w+)<", r["text"], re.M) == ["fringe_kernel", "find_kernel"]
+
+
+def shape(name, J, P, R, precision, **kw):
+    return dict(J=J, P=P, R=R, W=",".join(map(str, WINDOWS)), **form(precision), **{"if": ",".join(map(str, LATTICES[name]))}, **kw)
+
+
+@pytest.mark.parametrize("case", SCREENED)
+def test_searches_that_are_screened(device, case):  # noqa: F811
+    s = shape(*case, K=K, D=N_DM)
+    own = {k for k in kernels(device(**s)["text"]) if isinstance(k, tuple)}
+    assert own == {(case[1], True, 256)} and "screen" in kernels(device(**s)["text"])
+    assert "screen" not in kernels(device(**s, budget=spectra(s))["text"])   # no room for the records
+
+
+@pytest.mark.parametrize("case", WHOLE)
+def test_searches_that_are_evaluated_whole(device, case):  # noqa: F811
+    k, = kernels(device(**shape(*case, K=K, D=N_DM))["text"])
+    assert k[:2] == (case[1], False)
