@@ -328,9 +328,8 @@ void fringe_mfma_kernel(FringeArgs a) {
   unsigned best_key = 0u;
   int best_blk = 0;
 
-  float2 y[JA];
-  // SBD transform of sub-grid c -> A operand rows
-  auto sbd = [&](int c) {
+  // SBD transform of sub-grid c of the sums y -> A operand rows
+  auto sbd = [&](const float2 (&y)[JA], int c) {
     __syncthreads();
     sbd_pass1<JA, JB>(y, a.pre_sbd, TW, Sc, c, P, PJ, s_p1, n1, i2s);
     __syncthreads();
@@ -449,6 +448,7 @@ void fringe_mfma_kernel(FringeArgs a) {
     const Candidates cs{a.screen + (int64_t(dl) * a.seg_total + seg) * R * screen_rec_bytes(a.screen_units), R,
                         a.screen_units, NSB};
     for (int i = t; i < R * P; i += kBlock) cand[i] = 0u;
+    float2 y[JA];
     int rc0, sb0, cur_r = -1;
     cs.first(lane, P, rc0, sb0);
     sb0 >>= 2;   // the quad's unit
@@ -476,15 +476,16 @@ void fringe_mfma_kernel(FringeArgs a) {
         segment_sum<JA, JB>(y, wd, rph, r, N, J, l, R, s_p1, n1, i2s);
         cur_r = r;
       }
-      sbd(c);
+      sbd(y, c);
       for (unsigned m = mask; m; m &= m - 1) unit(r, c, __ffs(int(m)) - 1);
     }
     __syncthreads();   // red_v has been read
   } else {
     for (int r = 0; r < R; ++r) {
+      float2 y[JA];
       segment_sum<JA, JB>(y, wd, rph, r, N, J, l, R, s_p1, n1, i2s);
       for (int c = 0; c < P; ++c) {
-        sbd(c);
+        sbd(y, c);
         for (int sb = 0; sb < NSB; ++sb) unit(r, c, sb);
       }
     }
