@@ -88,7 +88,8 @@ struct frbx_ctx {
   unsigned rows_mask = 0;        // rows of the kernel in use (0: the statically built kernel)
   hipFunction_t rows_fn = nullptr, rows_cand = nullptr, rows_find = nullptr;   // unscreened; screened
   std::string rows_note;         // why the specialised kernel is not in use
-  int64_t form_segs = -1;        // choose_form: segments per DM trial it was asked for, and its answer
+  int64_t form_segs = -1;        // choose_form: segments per DM trial and kind of search it was asked for,
+  bool form_stream = false;      // and its answer
   bool screened = false, wave = false;
   int scr_blocks = 0;            // screening pass: its work-groups (0: its tables are not built),
   bool scr_half = false;         // its form, operand rows and the errors of its rounded matrices
@@ -410,10 +411,7 @@ bool use_gemm(const frbx_ctx *c) {
 }
 
 // (segment, rate) tasks of a search of S segments per DM trial (per 1: segments).
-int64_t tasks(const frbx_ctx *c, int64_t S, int per) {
-  // (grids set for a run shorter than the stream's chunks: unknown, taken as enough)
-  return S > 0 ? int64_t(c->B) * c->n_dm * S * per : std::numeric_limits<int64_t>::max();
-}
+int64_t tasks(const frbx_ctx *c, int64_t S, int per) { return int64_t(c->B) * c->n_dm * S * per; }
 
 // Tasks that fill the device's 1024 SIMDs several times over.  A search of 978
 // segments takes 219 us with a work-group per segment and no screening pass,
@@ -460,7 +458,7 @@ bool screen_half(const frbx_ctx *c) {
 // shape (and the candidate masks fit beside the kernel's LDS plan) and where it
 // pays, by the units of a segment (about two of them are evaluated whatever
 // their number) and by the number of tasks.
-bool use_screen(const frbx_ctx *c, int tiles, int64_t S) {
+bool use_screen(const frbx_ctx *c, int tiles, int64_t S, bool stream) {
   const bool half = screen_half(c), coarse = tiles < 16;
   if (use_gemm(c) || !frbx::screen_supported(c->J, c->n_mbd, c->N, c->n_rate, half, tiles, c->sbd_pad)) return false;
   const int units = c->n_rate * c->sbd_pad * c->J / 16;
@@ -484,7 +482,10 @@ bool use_screen(const frbx_ctx *c, int tiles, int64_t S) {
   // units 11.1 against 12.9; with 64 units and 9536 tasks 0.34 against 0.32.
   if (c->precision == FRBX_PREC_F16 && (!half || c->J > 64 || units < 64 || (units < 128 && n < 4 * kManyTasks)))
     return false;
-  if (n < kManyTasks) return false;
+  // Few tasks: a stream's pushes of four rates or more are screened whatever
+  // their size (48 segments of 32 IFs x 64 channels, 8 rates: 262 -> 165 us a
+  // push; with one or two rates the pass costs such a push 10 to 60 us).
+  if (n < kManyTasks && !(stream && c->n_rate >= 4)) return false;
   if (c->precision == FRBX_PREC_F32) return fringe_lds(c, true) <= 150 * 1024 && find_lds(c) <= 150 * 1024;
   const size_t lds = frbx::fringe_mfma_lds_bytes(c->J, c->N, c->sbd_pad, c->precision == FRBX_PREC_F16X3 ? 3 : 1);
   return lds + size_t(c->n_rate) * c->sbd_pad * 4 <= 150 * 1024;
@@ -685,14 +686,14 @@ hipFunction_t rows_kernel(frbx_ctx *c, bool screened, hipFunction_t *find = null
 // it takes.  A screened search also has the unscreened kernel where the
 // workspace of frbx_run_cube_noalloc, which compiles nothing, may lack the room
 // for the records.
-frbx_status choose_form(frbx_ctx *c, int64_t S) {
-  if (S == c->form_segs) return FRBX_OK;
+frbx_status choose_form(frbx_ctx *c, int64_t S, bool stream) {
+  if (S == c->form_segs && stream == c->form_stream) return FRBX_OK;
   frbx_status s;
   const ScreenGrid SG = screen_grid(c);
   const bool first = c->form_segs < 0, was_screened = c->screened, was_wave = c->wave;
   c->form_segs = -1;
   c->wave = use_wave(c, S);
-  c->screened = use_screen(c, SG.tiles, S);
+  c->screened = use_screen(c, SG.tiles, S, stream);
   if (c->screened && !c->scr_blocks) {
     const ScreenTables T = screen_tables(c, SG.tiles);
     std::copy(T.row_if, T.row_if + 32, c->scr_row_if);
@@ -715,6 +716,7 @@ frbx_status choose_form(frbx_ctx *c, int64_t S) {
     c->rows_mask = (c->screened ? c->rows_cand : c->rows_fn) ? c->rows_want : 0;
   }
   c->form_segs = S;
+  c->form_stream = stream;
   return FRBX_OK;
 }
 
@@ -917,7 +919,7 @@ frbx_status prepare(frbx_ctx *c) {
   }
   c->scr_blocks = 0;
   c->form_segs = -1;
-  if ((s = choose_form(c, c->seg_total)) != FRBX_OK) return s;
+  if ((s = choose_form(c, c->seg_total, false)) != FRBX_OK) return s;
   c->dirty = false;
   return FRBX_OK;
 }
@@ -1772,7 +1774,7 @@ frbx_status frbx_run(frbx_ctx *c) {
   c->spans.clear();
   c->ev_used = 0;
   frbx_status s = prepare(c);
-  if (s != FRBX_OK) return s;
+  if (s != FRBX_OK || (s = choose_form(c, c->seg_total, false)) != FRBX_OK) return s;
   c->streaming = false;
   const int nw = int(c->windows.size());
   PassSpec ps;
@@ -1843,6 +1845,10 @@ frbx_status frbx_stream_begin(frbx_ctx *c, int64_t chunk_frames) {
   if (s != FRBX_OK) return s;
   int lmax = 1;
   for (int l : c->windows) lmax = std::max(lmax, l);
+  // the segments that a push completes once the carry is full
+  int64_t push_segs = 0;
+  for (int h : c->hop) push_segs += (chunk_frames + h - 1) / h;
+  if ((s = choose_form(c, push_segs, true)) != FRBX_OK) return s;
   c->chunk = chunk_frames;
   c->carry = c->dk_max + lmax - 1;
   c->buf_frames = c->carry + chunk_frames;

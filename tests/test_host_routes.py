@@ -73,3 +73,27 @@ def test_searches_that_are_screened(device, case):  # noqa: F811
 def test_searches_that_are_evaluated_whole(device, case):  # noqa: F811
     k, = kernels(device(**shape(*case, K=K, D=N_DM))["text"])
     assert k[:2] == (case[1], False)
+
+
+# (lattice, channels, sbd_pad, rates, precision), MBD points, DM trials, APs a push: kernels
+PUSHES = [
+    (("32if-vgos", 64, 4, 1, "f32"), 256, 2, 64, {(64, False, 256)}),
+    (("32if-vgos", 64, 4, 1, "f32"), 256, 8, 4096, {"screen", "find", (64, True, 256)}),
+    (("32if-vgos", 64, 4, 8, "f32"), 256, 2, 16, {"screen", "find", (64, True, 256)}),
+    (("8if-compact", 32, 4, 1, "f32"), 256, 8, 16, {(32, False, 256)}),
+    (("8if-compact", 32, 4, 1, "f32"), 256, 8, 4096, {"screen", "find", (32, True, 256)}),
+    (("8if-compact", 64, 8, 8, "f32"), 128, 2, 64, {(64, False, 256)}),
+    (("8if-compact", 64, 8, 8, "f32"), 128, 4, 4096, {(64, False, 64)}),
+    (("32if-vgos", 64, 4, 1, "f16x3"), 256, 2, 64, {(64, False, 256)}),
+    (("32if-vgos", 64, 4, 8, "f16x3"), 256, 2, 16, {"screen", (64, True, 256)}),
+    (("32if-vgos", 64, 4, 8, "f16"), 256, 2, 16, {"screen", (64, True, 256)}),
+    (("32if-vgos", 64, 4, 4, "f16"), 256, 2, 64, {(64, False, 256)}),
+]
+
+
+@pytest.mark.parametrize("frames", [50, 20000])
+@pytest.mark.parametrize("case,M,D,chunk,want", PUSHES)
+def test_a_push_takes_the_kernels_of_its_own_size(device, case, M, D, chunk, want, frames):  # noqa: F811
+    """Whatever the number of frames of the layout."""
+    r = device(**shape(*case, M=M, D=D, K=frames), mode="stream", chunk=chunk)
+    assert r["status"] == 0 and kernels(r["text"].split("mark push 1")[1]) == want
