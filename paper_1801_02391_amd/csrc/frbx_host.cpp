@@ -682,6 +682,21 @@ hipFunction_t rows_kernel(frbx_ctx *c, bool screened, hipFunction_t *find = null
                                   &c->rows_note);
 }
 
+// The screening pass's tables and launch size (once per grids).
+frbx_status build_screen(frbx_ctx *c, const ScreenGrid &SG) {
+  frbx_status s;
+  const ScreenTables T = screen_tables(c, SG.tiles);
+  std::copy(T.row_if, T.row_if + 32, c->scr_row_if);
+  c->scr_half = T.half;
+  c->scr_tiles = SG.tiles;
+  c->scr_gamma = SG.gamma;
+  c->scr_err_s = T.err_s;
+  c->scr_err_m = T.err_m;
+  if ((s = upload(c, c->d_scr_sbd, T.fs)) != FRBX_OK || (s = upload(c, c->d_scr_mbd, T.fm)) != FRBX_OK) return s;
+  return c->hip(frbx::screen_blocks(c->J, c->N, c->n_rate, T.half, SG.tiles, c->sbd_pad, c->device, &c->scr_blocks),
+                "screening pass");
+}
+
 // Whether a search of S segments per DM trial is screened, and which kernels
 // it takes.  A screened search also has the unscreened kernel where the
 // workspace of frbx_run_cube_noalloc, which compiles nothing, may lack the room
@@ -690,31 +705,18 @@ frbx_status choose_form(frbx_ctx *c, int64_t S, bool stream) {
   if (S == c->form_segs && stream == c->form_stream) return FRBX_OK;
   frbx_status s;
   const ScreenGrid SG = screen_grid(c);
-  const bool first = c->form_segs < 0, was_screened = c->screened, was_wave = c->wave;
   c->form_segs = -1;
+  c->rows_fn = c->rows_cand = c->rows_find = nullptr;
+  c->rows_note.clear();
+  c->screened = false;
   c->wave = use_wave(c, S);
-  c->screened = use_screen(c, SG.tiles, S, stream);
-  if (c->screened && !c->scr_blocks) {
-    const ScreenTables T = screen_tables(c, SG.tiles);
-    std::copy(T.row_if, T.row_if + 32, c->scr_row_if);
-    c->scr_half = T.half;
-    c->scr_tiles = SG.tiles;
-    c->scr_gamma = SG.gamma;
-    c->scr_err_s = T.err_s;
-    c->scr_err_m = T.err_m;
-    if ((s = upload(c, c->d_scr_sbd, T.fs)) != FRBX_OK || (s = upload(c, c->d_scr_mbd, T.fm)) != FRBX_OK) return s;
-    if ((s = c->hip(frbx::screen_blocks(c->J, c->N, c->n_rate, T.half, SG.tiles, c->sbd_pad, c->device, &c->scr_blocks),
-                    "screening pass")) != FRBX_OK)
-      return s;
-  }
-  if (first || c->screened != was_screened || c->wave != was_wave) {
-    c->rows_fn = c->rows_cand = c->rows_find = nullptr;
-    c->rows_note.clear();
-    if (c->screened) c->rows_cand = rows_kernel(c, true, &c->rows_find);
-    const bool noalloc = dm_bytes(c) <= frbx::kNoAllocBytes;
-    if (!c->screened || (noalloc && !noalloc_plan(c).records)) c->rows_fn = rows_kernel(c, false);
-    c->rows_mask = (c->screened ? c->rows_cand : c->rows_fn) ? c->rows_want : 0;
-  }
+  const bool screened = use_screen(c, SG.tiles, S, stream);
+  if (screened && !c->scr_blocks && (s = build_screen(c, SG)) != FRBX_OK) return s;
+  c->screened = screened;
+  if (c->screened) c->rows_cand = rows_kernel(c, true, &c->rows_find);
+  const bool noalloc = dm_bytes(c) <= frbx::kNoAllocBytes;
+  if (!c->screened || (noalloc && !noalloc_plan(c).records)) c->rows_fn = rows_kernel(c, false);
+  c->rows_mask = (c->screened ? c->rows_cand : c->rows_fn) ? c->rows_want : 0;
   c->form_segs = S;
   c->form_stream = stream;
   return FRBX_OK;

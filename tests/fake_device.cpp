@@ -6,7 +6,8 @@
 //   if=f0,f1,...  J= K= B= D= dm_step= P= M= R= W=l0,l1,...  prec= recheck=
 //   jit=0|1 (run-time compilation succeeds) budget=bytes quota=bytes
 //   refuse=n (the n-th allocation from the search on fails)
-//   mode=run|noalloc|stream chunk=APs pushes=n
+//   mode=run|noalloc|stream|mixed chunk=APs pushes=n (mixed: a stream is begun,
+//   which may fail, then the no-alloc search and a run)
 // Output: "compiled <expression>" for what is compiled at run time, "prepared"
 // when the search begins, from then on "kernel <name> grid <g> lds <bytes>" for
 // every launch and "refused <bytes>", "mark <what>" between the steps, and
@@ -281,12 +282,18 @@ int main(int argc, char **argv) {
   f.peak = f.used;
   if (num("quota")) f.quota = before + size_t(num("quota"));
   if (num("refuse")) f.refuse = f.n_malloc + num("refuse");
-  if (arg["mode"] == "noalloc") {
+  const bool mixed = arg["mode"] == "mixed";
+  if (mixed) printf("mark stream %d\n", int(frbx_stream_begin(c, num("chunk"))));
+  if (mixed || arg["mode"] == "noalloc") {
     const int64_t cap = len * lay.n_baselines * num("D");
     int64_t got = 0;
     s = frbx_run_cube_noalloc(c, reinterpret_cast<float *>(space(size_t(cap) * 4)),
                               reinterpret_cast<int32_t *>(space(size_t(cap) * 4)), cap, &got);
     check("noalloc");
+    if (mixed) {
+      printf("mark run\n");
+      s = frbx_run(c), check("run");
+    }
   } else if (stream) {
     const char *chunk = space(n * size_t(num("chunk")));
     for (int i = 0; i < num("pushes"); ++i) {

@@ -97,3 +97,15 @@ def test_a_push_takes_the_kernels_of_its_own_size(device, case, M, D, chunk, wan
     """Whatever the number of frames of the layout."""
     r = device(**shape(*case, M=M, D=D, K=frames), mode="stream", chunk=chunk)
     assert r["status"] == 0 and kernels(r["text"].split("mark push 1")[1]) == want
+
+
+@pytest.mark.parametrize("refuse", [0, 1, 2, 3])
+def test_a_run_after_a_stream_of_another_size(device, refuse):  # noqa: F811
+    """A run too small to be screened, after a stream whose pushes are: also
+    where the stream's tables or buffers were refused."""
+    case = ("32if-vgos", 64, 4, 1, "f32")
+    r = device(**shape(*case, K=50, D=8), mode="mixed", chunk=4096, refuse=refuse)
+    began, ran = re.split("mark run", r["text"].split("mark stream ")[1])
+    assert r["status"] == 0 and began[0] == ("4" if refuse else "0")
+    assert kernels(began) in ({(64, False, 256)}, {"screen", "find", (64, True, 256)})
+    assert kernels(ran) == {(64, False, 256)}
