@@ -108,7 +108,8 @@ FORM_COST = {"f32": 1.0, "f16x3": 1.1, "f16": 1.1, "f16-recheck": 1.2}
 # What the roofline's flop counts mean for a screened search.
 METHOD_FLOPS = ("the method's transforms over every cell; where the search is screened, float16 matrix-core "
                 "products rule most cells out and only candidates take the form's own arithmetic, so achieved "
-                "is the rate of the method's work (frac can exceed 1), not of the instructions issued")
+                "is the rate of the method's work (frac can exceed 1), not of the instructions issued; "
+                "a launch is then screen_kernel and the candidates' kernels together")
 # Time reserved for the refinement leg (library ascent, FP64 oracle
 # gradient check) and for loading a form's input onto the device.
 REFINE_RESERVE_S = 30.0

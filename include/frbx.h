@@ -186,12 +186,16 @@ frbx_status frbx_set_tile_budget(frbx_ctx *ctx, int64_t bytes);
  *                       lattice position lies within one row of the first
  *                       MBD pass (16 positions at n_mbd = 256) after a
  *                       common shift, that pass is skipped (a phase factor
- *                       on G; |G| is unchanged).  Searches of many segments
- *                       (4096 or more) on n_mbd = 256 grids run a float16
- *                       matrix-core pass first that only rules cells out, by
- *                       a bound on its own error; every reported power and
- *                       cell is evaluated in float32 as described.  The
- *                       other forms do the same where it is faster.
+ *                       on G; |G| is unchanged).  On n_mbd = 256 grids,
+ *                       searches of 4096 or more (segment, rate) pairs with
+ *                       16 or more units (n_rate x sbd_pad x n_chan / 16; 8
+ *                       on compact lattices) run a float16 matrix-core pass
+ *                       first that only rules cells out, by a bound on its
+ *                       own error; every reported power and cell is
+ *                       evaluated in float32 as described.  A stream's
+ *                       pushes count by themselves, those of four rates or
+ *                       more whatever their size.  The other forms do the
+ *                       same where it is faster, from more units on.
  *   FRBX_PREC_F16X3     float32 segment sums and SBD transform; the MBD
  *                       transform on the matrix cores as three float16
  *                       products (high x high + high x low + low x high of a

@@ -893,7 +893,9 @@ constexpr int kFindStride(int n_if, int jb, bool compact, int masks) {   // floa
 // The cells keep fringe_kernel's last bits: the values of a transform are
 // formed before one is chosen (left to itself the compiler moves additions
 // into the branches), and the twiddles of the first JA / 4 outputs add their
-// products in the order in which it adds them there.
+// products in the order in which it adds them there.  Nothing but the compiler
+// fixes that order: tests/test_gpu_screen_bits.py fails where another one
+// chooses differently.
 template <int NP>
 __device__ __forceinline__ void formed(float2 (&x)[NP]) {
 #pragma unroll

@@ -161,7 +161,7 @@ struct ScreenArgs {
   const void *f_sbd;         // [P][J / 16][re, im][64 lanes] x 8 halves
   const void *f_mbd;         // [tiles][n_if <= 16 ? 1 : 2][re, im][64 lanes] x 8 halves
   float eps_y;               // error bound per unit of sum |y|,
-  float eps_sum;            // of l x a lane's largest partial sum, in units of eps_y,
+  float eps_sum;             // of l x a lane's largest partial sum, in units of eps_y,
   float eps_x;               // of sqrt(N) times the largest 2-norm of X over the IFs,
   float abs_scaled;          // and absolute: in the units of the scaled operands,
   float abs_plain;           // in those of the data

@@ -1001,12 +1001,14 @@ __device__ __forceinline__ float2 cfma(float2 acc, float2 a, float w) {
 // forms the rate-rotated window sum of the interpolated frames (and the
 // derivative sums the mode needs), rotates by the delay phase and the
 // calibration, and accumulates; a block reduction gives G and its
-// derivatives, from which thread 0 writes the mode's output.  Bound by its
-// loads: a wave's lanes read 64 channel rows, one cache line each.  With the
+// derivatives, from which thread 0 writes the mode's output.  With the
 // interpolation's frames kept from one AP to the next (l + 3 loads instead
 // of 4 l, the loop unrolled so that several are in flight) a step of 1024
 // peaks (32 IFs x 64 channels, windows of 2 to 16 APs) takes 130 us, 309 us
-// before; the sums are formed in the same order.
+// before; the sums are formed in the same order.  Bound by latency at four
+// waves per SIMD: vector issue (the float64 phases) takes 38 % of the cycles
+// and the L2 26 % of its request slots (a wave's lanes read 64 channel rows,
+// one cache line each), while the waves wait for 35 to 40 % of theirs.
 template <int MODE>
 __global__ __launch_bounds__(kBlock) void refine_kernel(RefineArgs a) {
   constexpr int D = (MODE == kRefineForward || MODE == kRefineFinal) ? 0 : MODE == kRefineBackward ? 1 : 2;

@@ -12,9 +12,12 @@
 // maximum is always among them and the search's result is what it is without
 // this pass, bit for bit.
 //
-// Matrix-core bound (power): 41184 segments of 32 IFs x 64 channels with 8
-// rates take 4.8 ms, 1.1 PFLOP/s of products, the rate of an 8192^3 library
-// product on this card; evaluating every cell in float32 took 14.0 ms.
+// Bound by vector issue: 41184 segments of 32 IFs x 64 channels with 8 rates
+// take 4.8 ms (evaluating every cell in float32 took 14.0).  A task issues 7030
+// vector instructions, 592 of them matrix products (0.65 PFLOP/s): at four
+// cycles each 88 % of the SIMDs' cycles at 2.07 GHz, the matrix pipes busy in
+// 30 %.  With 128 channels 67 % and 18 % (0.40 PFLOP/s, 420 bytes of scratch
+// per lane, 8.7 ms for 22824 segments).
 //
 // Both transforms are real-embedded complex GEMMs chained in registers:
 //   SBD  X[n][s] = sum_j y[n][j] w_PJ^(j s): A = the segment sums (rows n, K =
